@@ -13,7 +13,7 @@ BUILD_DIR = os.path.join(ROOT, "_build")
 LIB_PATH = os.path.join(PKG, "libpfc.so")
 
 SOURCES = ["abi.hip", "sample.hip", "sample_noalloc.hip", "prep.hip", "fwd.hip", "bwd.hip",
-           "timing.hip", "bank.hip"]
+           "f32.hip", "timing.hip", "bank.hip"]
 ARCH = "gfx950"
 
 # Packed fp32 VALU instructions are disabled for every GPU object.

@@ -83,12 +83,12 @@ WsLayout ws_layout(int64_t B, int64_t d, int64_t C, int64_t cap, int compute) {
   L.sample_bytes = off;
 
   L.ld_cos = round_up(cap, 256);
-  L.n_ctiles = ceil_div(cap, kFwdClassTile);
+  L.n_ctiles = ceil_div(cap, compute == PFC_F32 ? kFwdClassTile32 : kFwdClassTile);
   L.ld_xt = round_up(B, 32);
   L.ld_g = round_up(B, 128);
   L.n_lgroups = L.ld_cos / kLogitGroup;
   if (compute == PFC_F32) {
-    L.n_split = 1;
+    L.n_split = split_f32(B, cap);
   } else {
     // Split-K of the feature-gradient contraction: ~256 workgroups of
     // 128 batch rows, one per CU.
@@ -115,6 +115,7 @@ WsLayout ws_layout(int64_t B, int64_t d, int64_t C, int64_t cap, int compute) {
   L.n_act_pad = round_up(cap, 128);   // whole forward class tiles (and dX chunks)
   L.off_act_pad = take(compute == PFC_F32 ? 0 : (size_t)L.n_act_pad * 4);
   L.off_dw_gate = take(compute == PFC_F32 ? 0 : (size_t)kDwGates * 4);
+  L.off_arrivals = take(4);
   L.bytes = off;
   return L;
 }
@@ -159,6 +160,7 @@ StepWs step_ws(void* ws, const WsLayout& L) {
   w.act_pad = (int32_t*)(b + L.off_act_pad);
   w.n_act_pad = L.n_act_pad;
   w.dw_gate = (int32_t*)(b + L.off_dw_gate);
+  w.arrivals = (uint32_t*)(b + L.off_arrivals);
   return w;
 }
 

@@ -1074,118 +1074,6 @@ __global__ void __launch_bounds__(512) k_dw16(
   });
 }
 
-// ---------------------------------------------------------------- fp32 path
-// Small problems only (parity scale): plain loops, one output per thread.
-
-__global__ void __launch_bounds__(256) k_dx32(const float* __restrict__ W,
-                                              const int32_t* __restrict__ active,
-                                              const int32_t* __restrict__ n_active_p,
-                                              const int32_t* __restrict__ yhat,
-                                              const float* __restrict__ row_lse,
-                                              const float* __restrict__ inv_w,
-                                              const float* __restrict__ cos32, int64_t ld_cos,
-                                              int B, int d, Margin mg, float* __restrict__ out) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int n = blockIdx.y;
-  if (i >= d || n >= B) return;
-  const int K = *n_active_p;
-  const int yh = yhat[n];
-  const float lse = row_lse[n];
-  float acc = 0.0f;
-  for (int j = 0; j < K; ++j) {
-    const float coef = grad_coef(mg, cos32[(int64_t)n * ld_cos + j], j == yh, lse) * inv_w[j];
-    acc = fmaf(coef, W[(int64_t)active[j] * d + i], acc);
-  }
-  out[(int64_t)n * d + i] = acc;
-}
-
-__global__ void __launch_bounds__(256) k_dx_final32(const float* __restrict__ dx_part,
-                                                    const float* __restrict__ X,
-                                                    const float* __restrict__ inv_x, int B, int d,
-                                                    float sB, float* __restrict__ dX) {
-  constexpr int kMaxPer = 16;  // d <= 1024
-  const int lane = threadIdx.x & 63;
-  const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (n >= B) return;
-  const float ix = inv_x[n];
-  float v[kMaxPer], xh[kMaxPer];
-  float dot = 0.0f;
-#pragma unroll
-  for (int k = 0; k < kMaxPer; ++k) {
-    const int i = lane + 64 * k;
-    v[k] = 0.0f;
-    xh[k] = 0.0f;
-    if (i < d) {
-      v[k] = sB * dx_part[(int64_t)n * d + i];
-      xh[k] = X[(int64_t)n * d + i] * ix;
-      dot = fmaf(xh[k], v[k], dot);
-    }
-  }
-  dot = wave_sum(dot);
-#pragma unroll
-  for (int k = 0; k < kMaxPer; ++k) {
-    const int i = lane + 64 * k;
-    if (i < d) dX[(int64_t)n * d + i] = ix * (v[k] - xh[k] * dot);
-  }
-}
-
-__global__ void __launch_bounds__(256) k_dw32(const float* __restrict__ X, float* __restrict__ W,
-                                              float* __restrict__ W_master, float* __restrict__ M,
-                                              const int32_t* __restrict__ active,
-                                              const int32_t* __restrict__ n_active_p,
-                                              const int32_t* __restrict__ yhat,
-                                              const float* __restrict__ row_lse,
-                                              const float* __restrict__ inv_x,
-                                              const float* __restrict__ inv_w,
-                                              const float* __restrict__ cos32, int64_t ld_cos,
-                                              int B, int d, Margin mg, float sB, float lr,
-                                              float mu) {
-  constexpr int kMaxB = 4096;
-  constexpr int kMaxPer = 4;  // d <= 1024
-  __shared__ float coef[kMaxB];
-  __shared__ float red[4];
-  const int64_t j = blockIdx.x;
-  if (j >= *n_active_p) return;
-  const float iw = inv_w[j];
-  for (int n = threadIdx.x; n < B; n += blockDim.x)
-    coef[n] = grad_coef(mg, cos32[(int64_t)n * ld_cos + j], j == yhat[n], row_lse[n]) * inv_x[n];
-  __syncthreads();
-  const int64_t a = active[j];
-  float dw[kMaxPer];
-  float dot = 0.0f;
-#pragma unroll
-  for (int k = 0; k < kMaxPer; ++k) {
-    const int i = threadIdx.x + 256 * k;
-    dw[k] = 0.0f;
-    if (i < d) {
-      float acc = 0.0f;
-      for (int n = 0; n < B; ++n) acc = fmaf(coef[n], X[(int64_t)n * d + i], acc);
-      dw[k] = sB * acc;
-      dot = fmaf(W[a * d + i] * iw, dw[k], dot);
-    }
-  }
-  dot = wave_sum(dot);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = dot;
-  __syncthreads();
-  dot = red[0] + red[1] + red[2] + red[3];
-#pragma unroll
-  for (int k = 0; k < kMaxPer; ++k) {
-    const int i = threadIdx.x + 256 * k;
-    if (i >= d) continue;
-    const float w = W[a * d + i];
-    const float gr = iw * (dw[k] - w * iw * dot);
-    const float m = mu * M[a * d + i] + gr;
-    M[a * d + i] = m;
-    if (W_master) {
-      const float p = W_master[a * d + i] - lr * m;
-      W_master[a * d + i] = p;
-      W[a * d + i] = p;
-    } else {
-      W[a * d + i] = w - lr * m;
-    }
-  }
-}
-
 // Compute units of the current device (0 if the query fails).
 int device_cu_count() {
   int dev = 0, n = 0;
@@ -1251,30 +1139,13 @@ void launch_bwd16_d(const StepArgs& a, const StepWs& w, const Margin& mg, float 
 }  // namespace
 
 hipError_t launch_backward(const StepArgs& a, const StepWs& w, hipStream_t stream) {
-  const int B = (int)a.B, d = (int)a.d;
+  if (a.dtype == 0) return launch_backward_f32(a, w, stream);
   Margin mg{a.s, a.m, cosf(a.m), sinf(a.m), a.margin};
   const float sB = a.s / (float)a.B;
-  if (a.dtype == 0) {
-    timing_start(4, stream);
-    hipLaunchKernelGGL(k_dx32, dim3((unsigned)ceil_div(d, 256), (unsigned)B), dim3(256), 0,
-                       stream, (const float*)a.W, a.active, a.n_active, a.labels_mapped,
-                       a.row_lse, w.inv_w, (const float*)w.lbuf, w.ld_cos, B, d, mg, w.dx_part);
-    timing_stop(4, stream);
-    timing_start(5, stream);
-    hipLaunchKernelGGL(k_dx_final32, dim3((unsigned)ceil_div(B, 4)), dim3(256), 0, stream,
-                       w.dx_part, (const float*)a.X, w.inv_x, B, d, sB, a.dX);
-    timing_stop(5, stream);
-    timing_start(6, stream);
-    hipLaunchKernelGGL(k_dw32, dim3((unsigned)a.cap), dim3(256), 0, stream, (const float*)a.X,
-                       (float*)a.W, a.W_master, a.M, a.active, a.n_active, a.labels_mapped,
-                       a.row_lse, w.inv_x, w.inv_w, (const float*)w.lbuf, w.ld_cos, B, d, mg, sB,
-                       a.lr, a.mu);
-    timing_stop(6, stream);
-  } else if (a.dtype == 1) {
+  if (a.dtype == 1)
     launch_bwd16_d<Bf16Tag>(a, w, mg, sB, stream);
-  } else {
+  else
     launch_bwd16_d<F16Tag>(a, w, mg, sB, stream);
-  }
   return hipGetLastError();
 }
 

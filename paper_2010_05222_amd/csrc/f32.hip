@@ -1,0 +1,555 @@
+// The step on fp32 operands (stages 3-6): normalised logits, margin softmax,
+// both gradients and the momentum update (Partial FC Sec. 3.1, Sec. 3.2.1,
+// Eq. proxy_update, Eq. pfc_center_update).
+//
+// Three contractions on v_mfma_f32_16x16x4_f32 (fp32 products and sums; the
+// matrix pipe's fp32 rate is the vector units', but an operand register feeds
+// sixteen products, so LDS and the load units keep up).  d is any multiple of
+// 8 up to 1024 and the batch any size up to 4096; every tile masks its ends.
+//
+// MFMA operands: lane l supplies A[l % 16][k] and B[k][l % 16] with
+// k = l / 16, and register r of its accumulator is D[4 (l / 16) + r][l % 16].
+// The order of k inside a contraction is free as long as both operands agree,
+// so one 16-byte piece per lane (k = 16 b + 4 (l / 16) + s, s < 4) feeds four
+// MFMAs, s = 0..3.  Likewise a lane's four consecutive columns 4 (l % 16) + t
+// are its column l % 16 of four tiles t: rows are loaded and stored in
+// 16-byte pieces, 256 bytes per 16 lanes, with no transposition.
+#include "pfc_device.h"
+
+namespace pfc {
+namespace {
+
+constexpr float kEpsNorm = 1e-12f;
+constexpr int kRows = 64;        // batch rows of a forward tile (16 per wave)
+constexpr int kChunk = 64;       // slice of d (forward), classes (dX) or rows (dW) per LDS stage
+constexpr int kLd = kChunk + 4;  // LDS row stride: sixteen rows' 16-byte pieces on distinct banks
+constexpr int kDxRows = 32;      // batch rows of a dX workgroup
+constexpr int kDwCls = 16;       // classes of a dW workgroup
+
+// Four floats at any 4-byte aligned address (the caller's rows are only that).
+typedef float f32x4u_t __attribute__((ext_vector_type(4), aligned(4)));
+
+__device__ __forceinline__ f32x4_t load4(const float* p) {
+  return *reinterpret_cast<const f32x4u_t*>(p);
+}
+__device__ __forceinline__ void store4(float* p, f32x4_t v) {
+  *reinterpret_cast<f32x4u_t*>(p) = v;
+}
+__device__ __forceinline__ f32x4_t zero4() { return f32x4_t{0.0f, 0.0f, 0.0f, 0.0f}; }
+
+__device__ __forceinline__ f32x4_t mfma_16x16x4(float a, float b, f32x4_t c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// Sum over the sixteen lanes that share l / 16.
+__device__ __forceinline__ float sum16(float v) {
+#pragma unroll
+  for (int off = 1; off < 16; off <<= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+
+// ------------------------------------------------------------------ forward
+
+// cos[n][j] of a tile of 16 MT classes x 64 batch rows, d in 64-wide chunks
+// through two LDS stages (a chunk is loaded into registers while the previous
+// one is contracted).  Wave w owns rows 16 w .. + 15 and all the tile's
+// classes, so a row's (max, sum exp) pair of the tile needs lane moves only.
+// The row norms of both operands are summed from the pieces on their way to
+// LDS; the tiles of the first class tile (row tile) publish them for the
+// backward.  A negative that the PFC* filter drops is stored as -inf.
+//
+// Bound by the fp32 matrix rate and, on few tiles, by the chunk latency.  At
+// B = 250, |S| = 5,003, d = 512 (1.3 GFLOP) it takes 27 us; the
+// thread-per-dot kernel that it replaced took 2,671 us there.
+template <int MT>
+__global__ void __launch_bounds__(256) k_fwd32(
+    const float* __restrict__ X, const float* __restrict__ W, const int32_t* __restrict__ active,
+    const int32_t* __restrict__ n_active_p, const int32_t* __restrict__ yhat, int B, int d,
+    int64_t ld_cos, int64_t n_ctiles, Margin mg, float tau, float* __restrict__ inv_x,
+    float* __restrict__ inv_w, float* __restrict__ cos32, float2* __restrict__ stats,
+    float* __restrict__ tgt, uint32_t* __restrict__ arrivals) {
+  constexpr int CLS = 16 * MT;
+  __shared__ float As[2][CLS][kLd], Bs[2][kRows][kLd];
+  __shared__ float iwS[CLS], ixS[kRows];
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *arrivals = 0;
+  const int64_t K = *n_active_p;
+  const int64_t j0 = (int64_t)blockIdx.x * CLS;
+  // The first class tile publishes the batch norms even when S is empty.
+  if (j0 >= K && blockIdx.x > 0) return;
+  const int n0 = blockIdx.y * kRows;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l16 = lane & 15, g4 = 4 * (lane >> 4);
+
+  // Staging: thread t moves piece t % 16 of rows t / 16 + 16 u.
+  const int piece = 4 * (tid & 15), srow = tid >> 4;
+  const float *ap[MT], *bp[4];
+  float sa[MT], sb[4];
+#pragma unroll
+  for (int u = 0; u < MT; ++u) {
+    const int64_t j = j0 + srow + 16 * u;
+    ap[u] = j < K ? W + (int64_t)active[j] * d : nullptr;
+    sa[u] = 0.0f;
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int n = n0 + srow + 16 * u;
+    bp[u] = n < B ? X + (int64_t)n * d : nullptr;
+    sb[u] = 0.0f;
+  }
+  f32x4_t ar[MT], br[4];
+  auto load = [&](int k0) {
+    const bool in = k0 + piece < d;
+#pragma unroll
+    for (int u = 0; u < MT; ++u) ar[u] = in && ap[u] ? load4(ap[u] + k0 + piece) : zero4();
+#pragma unroll
+    for (int u = 0; u < 4; ++u) br[u] = in && bp[u] ? load4(bp[u] + k0 + piece) : zero4();
+  };
+  f32x4_t acc[MT];
+#pragma unroll
+  for (int m = 0; m < MT; ++m) acc[m] = zero4();
+  load(0);
+  for (int k0 = 0, st = 0; k0 < d; k0 += kChunk, st ^= 1) {
+#pragma unroll
+    for (int u = 0; u < MT; ++u) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sa[u] = fmaf(ar[u][e], ar[u][e], sa[u]);
+      *reinterpret_cast<f32x4_t*>(&As[st][srow + 16 * u][piece]) = ar[u];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sb[u] = fmaf(br[u][e], br[u][e], sb[u]);
+      *reinterpret_cast<f32x4_t*>(&Bs[st][srow + 16 * u][piece]) = br[u];
+    }
+    // A stage is rewritten two chunks later: every wave has then passed the
+    // barrier of the chunk between, after its reads of this one.
+    __syncthreads();
+    if (k0 + kChunk < d) load(k0 + kChunk);
+#pragma unroll
+    for (int kb = 0; kb < kChunk / 16; ++kb) {
+      const f32x4_t b = *reinterpret_cast<const f32x4_t*>(&Bs[st][16 * wave + l16][16 * kb + g4]);
+      f32x4_t a[MT];
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+        a[m] = *reinterpret_cast<const f32x4_t*>(&As[st][16 * m + l16][16 * kb + g4]);
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int m = 0; m < MT; ++m) acc[m] = mfma_16x16x4(a[m][s], b[s], acc[m]);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < MT; ++u) {
+    const float iv = 1.0f / fmaxf(sqrtf(sum16(sa[u])), kEpsNorm);
+    const int64_t j = j0 + srow + 16 * u;
+    if (piece == 0) {
+      iwS[srow + 16 * u] = iv;
+      if (blockIdx.y == 0 && j < K) inv_w[j] = iv;
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const float iv = 1.0f / fmaxf(sqrtf(sum16(sb[u])), kEpsNorm);
+    const int n = n0 + srow + 16 * u;
+    if (piece == 0) {
+      ixS[srow + 16 * u] = iv;
+      if (blockIdx.x == 0 && n < B) inv_x[n] = iv;
+    }
+  }
+  __syncthreads();
+
+  // Lane: batch row n, classes j0 + 16 m + 4 (lane / 16) + r.
+  const int n = n0 + 16 * wave + l16;
+  const bool row_ok = n < B;
+  const float ix = ixS[16 * wave + l16];
+  const int64_t y = row_ok ? (int64_t)yhat[n] : -1;
+  float f[MT][4];
+  float mx = -INFINITY;
+#pragma unroll
+  for (int m = 0; m < MT; ++m) {
+    const f32x4_t iw = *reinterpret_cast<const f32x4_t*>(&iwS[16 * m + g4]);
+    const int64_t j = j0 + 16 * m + g4;
+    f32x4_t c;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const bool target = j + r == y;
+      c[r] = acc[m][r] * ix * iw[r];
+      if (tau < 1.0f && !target && c[r] > tau) c[r] = -INFINITY;
+      f[m][r] = target ? target_logit(mg, c[r]) : mg.s * c[r];
+      if (j + r >= K) f[m][r] = -INFINITY;
+      else if (target) tgt[n] = f[m][r];
+      mx = fmaxf(mx, f[m][r]);
+    }
+    if (row_ok && j < K) store4(cos32 + (int64_t)n * ld_cos + j, c);
+  }
+  const float mref = mx == -INFINITY ? 0.0f : mx;
+  float sum = 0.0f;
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) sum += __expf(f[m][r] - mref);
+  float2 p = make_float2(mx, sum);
+#pragma unroll
+  for (int off = 16; off < 64; off <<= 1)
+    p = lse_merge(p, make_float2(__shfl_xor(p.x, off, 64), __shfl_xor(p.y, off, 64)));
+  if (row_ok && lane < 16) stats[(int64_t)n * n_ctiles + blockIdx.x] = p;
+}
+
+// ------------------------------------------------------------------ dX
+
+// Partial dX_hat[n][i] = sum_j g[n][j] / ||w_j|| W[S_j][i] of 32 batch rows,
+// all of d and a slice of the classes (in 64-class chunks).  The coefficients
+// of a chunk are computed once, into LDS; wave w owns NB blocks of 64 columns
+// and takes its W pieces straight from memory to registers, since no other
+// wave reads them.  blockDim = 64 x the waves that d needs (at most 4).
+//
+// At B = 250, |S| = 5,003, d = 512 it takes 32 us, at B = 64, |S| = 1,000,
+// d = 128 10 us; the loop that it replaced, a chain of |S| dependent steps per
+// output, took 1,585 and 266 us.
+template <int NB>
+__global__ void __launch_bounds__(256) k_dx32(
+    const float* __restrict__ W, const int32_t* __restrict__ active,
+    const int32_t* __restrict__ n_active_p, const int32_t* __restrict__ yhat,
+    const float* __restrict__ row_lse, const float* __restrict__ inv_w,
+    const float* __restrict__ cos32, int64_t ld_cos, int B, int d, Margin mg, int n_split,
+    float* __restrict__ part) {
+  __shared__ float G[2][kDxRows][kLd];
+  __shared__ int32_t ids[2][kChunk];
+  const int64_t K = *n_active_p;
+  const int n0 = blockIdx.y * kDxRows;
+  const int64_t n_chunks = ceil_div(K, (int64_t)kChunk);
+  const int64_t per = ceil_div(n_chunks, (int64_t)n_split);
+  const int64_t c_begin = blockIdx.x * per;
+  const int64_t c_end = c_begin + per < n_chunks ? c_begin + per : n_chunks;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l16 = lane & 15, g4 = 4 * (lane >> 4);
+
+  // Coefficients of chunk c into stage st: thread t owns piece t % 16 (four
+  // classes) of rows t / 16, + blockDim / 16, ...
+  auto produce = [&](int64_t c, int st) {
+    const int64_t j = c * kChunk + 4 * (tid & 15);
+    for (int r = tid >> 4; r < kDxRows; r += blockDim.x >> 4) {
+      const int n = n0 + r;
+      f32x4_t g = zero4();
+      if (n < B && j < K) {
+        const f32x4_t cv = load4(cos32 + (int64_t)n * ld_cos + j);
+        const float lse = row_lse[n];
+        const int64_t y = yhat[n];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (j + e < K) g[e] = grad_coef(mg, cv[e], j + e == y, lse) * inv_w[j + e];
+      }
+      *reinterpret_cast<f32x4_t*>(&G[st][r][4 * (tid & 15)]) = g;
+    }
+    if (tid < kChunk) {   // ids past |S| (coefficient 0) repeat the last one
+      const int64_t i = c * kChunk + tid;
+      ids[st][tid] = active[i < K ? i : K - 1];
+    }
+  };
+  f32x4_t acc[2][NB][4];
+#pragma unroll
+  for (int m = 0; m < 2; ++m)
+#pragma unroll
+    for (int q = 0; q < NB; ++q)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) acc[m][q][t] = zero4();
+  const int col0 = 64 * NB * wave + 4 * l16;
+  f32x4_t w[2][NB][4];   // W pieces of two 16-class blocks in turn
+  auto load_w = [&](int st, int kb, f32x4_t (&dst)[NB][4]) {
+    const int4 id = *reinterpret_cast<const int4*>(&ids[st][16 * kb + g4]);
+    const int row[4] = {id.x, id.y, id.z, id.w};
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int q = 0; q < NB; ++q)
+        dst[q][s] = col0 + 64 * q < d ? load4(W + (int64_t)row[s] * d + col0 + 64 * q) : zero4();
+  };
+  if (c_begin < c_end) produce(c_begin, 0);
+  int st = 0;
+  for (int64_t c = c_begin; c < c_end; ++c, st ^= 1) {
+    // After the barrier chunk c is ready, and the other stage is free.
+    __syncthreads();
+    load_w(st, 0, w[0]);
+    if (c + 1 < c_end) produce(c + 1, st ^ 1);
+#pragma unroll
+    for (int kb = 0; kb < kChunk / 16; ++kb) {
+      if (kb + 1 < kChunk / 16) load_w(st, kb + 1, w[(kb + 1) & 1]);
+      f32x4_t a[2];
+#pragma unroll
+      for (int m = 0; m < 2; ++m)
+        a[m] = *reinterpret_cast<const f32x4_t*>(&G[st][16 * m + l16][16 * kb + g4]);
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int q = 0; q < NB; ++q)
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+              acc[m][q][t] = mfma_16x16x4(a[m][s], w[kb & 1][q][s][t], acc[m][q][t]);
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < 2; ++m)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int n = n0 + 16 * m + g4 + r;
+      if (n >= B) continue;
+      float* out = part + ((int64_t)blockIdx.x * B + n) * d + col0;
+#pragma unroll
+      for (int q = 0; q < NB; ++q)
+        if (col0 + 64 * q < d)
+          store4(out + 64 * q, f32x4_t{acc[m][q][0][r], acc[m][q][1][r], acc[m][q][2][r],
+                                       acc[m][q][3][r]});
+    }
+}
+
+// The split partials of a row summed in split order, and the normalisation
+// backward dx = (v - x_hat (x_hat . v)) / ||x||, v = (s / B) * sum.  One
+// workgroup per row.
+__global__ void __launch_bounds__(256) k_dx_final32(const float* __restrict__ part, int n_split,
+                                                    const float* __restrict__ X,
+                                                    const float* __restrict__ inv_x, int B, int d,
+                                                    float sB, float* __restrict__ dX) {
+  constexpr int PER = 4;   // d <= 1024
+  __shared__ float red[4];
+  const int n = blockIdx.x, t = threadIdx.x;
+  const float ix = inv_x[n];
+  const int64_t stride = (int64_t)B * d;
+  float v[PER], xh[PER];
+  float dot = 0.0f;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int i = t + 256 * k;
+    v[k] = 0.0f;
+    xh[k] = 0.0f;
+    if (i >= d) continue;
+    const float* p = part + (int64_t)n * d + i;
+    float sum = 0.0f;
+    int s = 0;
+    for (; s + 8 <= n_split; s += 8) {
+      float q[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) q[u] = p[(s + u) * stride];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) sum += q[u];
+    }
+    for (; s < n_split; ++s) sum += p[s * stride];
+    v[k] = sB * sum;
+    xh[k] = X[(int64_t)n * d + i] * ix;
+    dot = fmaf(xh[k], v[k], dot);
+  }
+  dot = wave_sum(dot);
+  if ((t & 63) == 0) red[t >> 6] = dot;
+  __syncthreads();
+  dot = red[0] + red[1] + red[2] + red[3];
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int i = t + 256 * k;
+    if (i < d) dX[(int64_t)n * d + i] = ix * (v[k] - xh[k] * dot);
+  }
+}
+
+// ------------------------------------------------------------------ dW
+
+// Class gradients of 16 active classes x all of d over the whole batch (in
+// 64-row chunks), and the momentum update of their rows.  As in dX, the
+// coefficients (here transposed: class-major) go through LDS and the batch
+// rows straight to the registers of the wave that owns their columns.  The
+// accumulators end with four consecutive columns of a class per lane, so the
+// tangent projection, momentum and weight step read and write whole rows in
+// 16-byte pieces.  37 us at B = 250, |S| = 5,003, d = 512 (110 us as one
+// workgroup per class).
+template <int NB>
+__global__ void __launch_bounds__(256) k_dw32(
+    const float* __restrict__ X, float* __restrict__ W, float* __restrict__ W_master,
+    float* __restrict__ M, const int32_t* __restrict__ active,
+    const int32_t* __restrict__ n_active_p, const int32_t* __restrict__ yhat,
+    const float* __restrict__ row_lse, const float* __restrict__ inv_x,
+    const float* __restrict__ inv_w, const float* __restrict__ cos32, int64_t ld_cos, int B,
+    int d, Margin mg, float sB, float lr, float mu) {
+  __shared__ float G[2][kDwCls][kLd];
+  __shared__ float red[4][kDwCls];
+  const int64_t K = *n_active_p;
+  const int64_t j0 = (int64_t)blockIdx.x * kDwCls;
+  if (j0 >= K) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n_waves = blockDim.x >> 6;
+  const int l16 = lane & 15, g4 = 4 * (lane >> 4);
+
+  // Coefficients of rows nb .. nb + 63 into stage st: thread t owns four
+  // classes of rows t / 4, + blockDim / 4, ...
+  auto produce = [&](int nb, int st) {
+    const int q = 4 * (tid & 3);
+    for (int r = tid >> 2; r < kChunk; r += blockDim.x >> 2) {
+      const int n = nb + r;
+      f32x4_t g = zero4();
+      if (n < B && j0 + q < K) {
+        const f32x4_t cv = load4(cos32 + (int64_t)n * ld_cos + j0 + q);
+        const float lse = row_lse[n], ix = inv_x[n];
+        const int64_t y = yhat[n];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (j0 + q + e < K) g[e] = grad_coef(mg, cv[e], j0 + q + e == y, lse) * ix;
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) G[st][q + e][r] = g[e];
+    }
+  };
+  f32x4_t acc[NB][4];
+#pragma unroll
+  for (int q = 0; q < NB; ++q)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) acc[q][t] = zero4();
+  const int col0 = 64 * NB * wave + 4 * l16;
+  f32x4_t x[2][NB][4];   // batch pieces of two 16-row blocks in turn
+  auto load_x = [&](int nb, f32x4_t (&dst)[NB][4]) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      int n = nb + g4 + s;
+      n = n < B ? n : B - 1;   // coefficient 0
+#pragma unroll
+      for (int q = 0; q < NB; ++q)
+        dst[q][s] = col0 + 64 * q < d ? load4(X + (int64_t)n * d + col0 + 64 * q) : zero4();
+    }
+  };
+  produce(0, 0);
+  load_x(0, x[0]);
+  for (int nb = 0, st = 0; nb < B; nb += kChunk, st ^= 1) {
+    __syncthreads();   // the chunk is ready, the other stage free
+    if (nb + kChunk < B) produce(nb + kChunk, st ^ 1);
+#pragma unroll
+    for (int kb = 0; kb < kChunk / 16; ++kb) {
+      load_x(nb + 16 * (kb + 1), x[(kb + 1) & 1]);
+      const f32x4_t a = *reinterpret_cast<const f32x4_t*>(&G[st][l16][16 * kb + g4]);
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int q = 0; q < NB; ++q)
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+            acc[q][t] = mfma_16x16x4(a[s], x[kb & 1][q][s][t], acc[q][t]);
+    }
+  }
+
+  // Update: lane l owns columns col0 + 64 q .. + 3 of classes 4 (l / 16) + r.
+  int64_t base[4];
+  float iw[4];
+  f32x4_t wv[4][NB];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int64_t j = j0 + g4 + r;
+    base[r] = j < K ? (int64_t)active[j] * d + col0 : -1;
+    iw[r] = j < K ? inv_w[j] : 0.0f;
+    float dot = 0.0f;
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      wv[r][q] = base[r] >= 0 && col0 + 64 * q < d ? load4(W + base[r] + 64 * q) : zero4();
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        acc[q][t][r] *= sB;
+        dot = fmaf(wv[r][q][t] * iw[r], acc[q][t][r], dot);
+      }
+    }
+    dot = sum16(dot);
+    if (l16 == 0) red[wave][g4 + r] = dot;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    float dot = 0.0f;
+    for (int v = 0; v < n_waves; ++v) dot += red[v][g4 + r];
+    if (base[r] < 0) continue;
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      if (col0 + 64 * q >= d) continue;
+      const int64_t o = base[r] + 64 * q;
+      f32x4_t m = load4(M + o);
+      f32x4_t p = W_master ? load4(W_master + o) : wv[r][q];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const float gr = iw[r] * (acc[q][t][r] - wv[r][q][t] * iw[r] * dot);
+        m[t] = mu * m[t] + gr;
+        p[t] = p[t] - lr * m[t];
+      }
+      store4(M + o, m);
+      if (W_master) store4(W_master + o, p);
+      store4(W + o, p);
+    }
+  }
+}
+
+// Calls f with NB = the 64-column blocks per wave of a width d (waves = min(4,
+// ceil(d / 64)) share them evenly).
+template <typename F>
+void with_blocks(int d, F&& f) {
+  const int blocks = (int)ceil_div(d, 64);
+  const int waves = blocks < 4 ? blocks : 4;
+  switch ((int)ceil_div(blocks, waves)) {
+    case 1: f(std::integral_constant<int, 1>{}, 64 * waves); break;
+    case 2: f(std::integral_constant<int, 2>{}, 64 * waves); break;
+    case 3: f(std::integral_constant<int, 3>{}, 64 * waves); break;
+    default: f(std::integral_constant<int, 4>{}, 64 * waves); break;
+  }
+}
+
+}  // namespace
+
+// Splits of the dX contraction: about two workgroups of 32 rows per CU, each
+// with at least one 64-class chunk.
+int split_f32(int64_t B, int64_t cap) {
+  const int64_t n_rt = ceil_div(B, kDxRows), chunks = ceil_div(cap, kChunk);
+  const int64_t ns = 512 / n_rt < chunks ? 512 / n_rt : chunks;
+  return (int)(ns < 1 ? 1 : ns);
+}
+
+hipError_t launch_forward_f32(const StepArgs& a, const StepWs& w, hipStream_t stream) {
+  const int B = (int)a.B, d = (int)a.d;
+  const Margin mg{a.s, a.m, cosf(a.m), sinf(a.m), a.margin};
+  const unsigned n_rt = (unsigned)ceil_div(B, kRows);
+  // 64-class tiles re-read the batch half as often; 32-class ones where those
+  // would leave CUs idle (fewer than two workgroups each).
+  const bool wide = ceil_div(a.cap, 64) * n_rt >= 512;
+  const int64_t n_ct = ceil_div(a.cap, wide ? 64 : 32);
+  timing_start(2, stream);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)n_ct, n_rt), dim3(256), 0, stream,
+                       (const float*)a.X, (const float*)a.W, a.active, a.n_active,
+                       a.labels_mapped, B, d, w.ld_cos, n_ct, mg, a.tau, w.inv_x, w.inv_w,
+                       (float*)w.lbuf, w.stats, w.tgt, w.arrivals);
+  };
+  if (wide) go(k_fwd32<4>);
+  else go(k_fwd32<2>);
+  timing_stop(2, stream);
+  return launch_lse(a, w, n_ct, wide ? 64 : 32, false, stream);
+}
+
+hipError_t launch_backward_f32(const StepArgs& a, const StepWs& w, hipStream_t stream) {
+  const int B = (int)a.B, d = (int)a.d;
+  const Margin mg{a.s, a.m, cosf(a.m), sinf(a.m), a.margin};
+  const float sB = a.s / (float)a.B;
+  timing_start(4, stream);
+  with_blocks(d, [&](auto nb, int threads) {
+    hipLaunchKernelGGL(k_dx32<decltype(nb)::value>,
+                       dim3((unsigned)w.n_split, (unsigned)ceil_div(B, kDxRows)), dim3(threads),
+                       0, stream, (const float*)a.W, a.active, a.n_active, a.labels_mapped,
+                       a.row_lse, w.inv_w, (const float*)w.lbuf, w.ld_cos, B, d, mg, w.n_split,
+                       w.dx_part);
+  });
+  timing_stop(4, stream);
+  timing_start(5, stream);
+  hipLaunchKernelGGL(k_dx_final32, dim3((unsigned)B), dim3(256), 0, stream, w.dx_part, w.n_split,
+                     (const float*)a.X, w.inv_x, B, d, sB, a.dX);
+  timing_stop(5, stream);
+  timing_start(6, stream);
+  with_blocks(d, [&](auto nb, int threads) {
+    hipLaunchKernelGGL(k_dw32<decltype(nb)::value>, dim3((unsigned)ceil_div(a.cap, kDwCls)),
+                       dim3(threads), 0, stream, (const float*)a.X, (float*)a.W, a.W_master, a.M,
+                       a.active, a.n_active, a.labels_mapped, a.row_lse, w.inv_x, w.inv_w,
+                       (const float*)w.lbuf, w.ld_cos, B, d, mg, sB, a.lr, a.mu);
+  });
+  timing_stop(6, stream);
+  return hipGetLastError();
+}
+
+}  // namespace pfc

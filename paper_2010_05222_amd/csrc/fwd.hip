@@ -512,121 +512,79 @@ __global__ void __launch_bounds__(kFwdThreads, 2) k_fwd16(
   }
 }
 
-// Merge the per-tile (max, sum) pairs of a row: lse_n, and the row's loss
-// term.  One workgroup per row, one pass over the row's pairs: each thread
-// merges its pairs in tile order (base 2), the waves' pairs meet through
-// lane moves and LDS in a fixed order.
-__global__ void __launch_bounds__(256) k_lse16(const float2* __restrict__ stats, int64_t n_ctiles,
-                                               const int32_t* __restrict__ n_active_p,
-                                               const int32_t* __restrict__ yhat,
-                                               const float* __restrict__ tgt, int B,
-                                               float* __restrict__ row_lse,
-                                               float* __restrict__ loss_part) {
-  __shared__ float2 red[4];
-  const int n = blockIdx.x;
-  const int t = threadIdx.x, lane = t & 63;
-  const int64_t nct = ceil_div((int64_t)*n_active_p, (int64_t)kFwdBM);
+// Merge the per-tile (max, sum) pairs of each row (in base 2 or e): lse_n, the
+// row's loss term and, by the workgroup that arrives last, the batch mean of
+// the loss terms.  TPR threads per row, one pass over the row's pairs: each
+// thread merges its pairs in tile order, the waves' pairs meet through lane
+// moves and LDS in a fixed order, and the mean is summed in a fixed order, so
+// the result does not depend on which workgroup is last.  A kernel of its own
+// for the mean cost a launch (4.4 us, the length of a launch that does next to
+// nothing); several rows per workgroup keep the arrivals few.
+constexpr int kLseThreads = 1024;
+template <int TPR, bool BASE2>
+__global__ void __launch_bounds__(kLseThreads) k_lse(
+    const float2* __restrict__ stats, int64_t n_ctiles, int tile,
+    const int32_t* __restrict__ n_active_p, const int32_t* __restrict__ yhat,
+    const float* __restrict__ tgt, int B, float* __restrict__ row_lse,
+    float* __restrict__ loss_part, uint32_t* __restrict__ arrivals, float* __restrict__ loss) {
+  constexpr int WPR = TPR / 64;   // waves per row
+  __shared__ float2 red[kLseThreads / 64];
+  __shared__ double part[kLseThreads / 64];
+  __shared__ bool last;
+  const int n = blockIdx.x * (kLseThreads / TPR) + threadIdx.x / TPR;
+  const int t = threadIdx.x % TPR, lane = t & 63, wave = threadIdx.x >> 6;
+  const int64_t K = *n_active_p;
+  const int64_t nct = n < B ? ceil_div(K, (int64_t)tile) : 0;
   const float2* row = stats + (int64_t)n * n_ctiles;
+  auto merge = [](float2 p, float2 q) { return BASE2 ? lse_merge2(p, q) : lse_merge(p, q); };
   float2 acc = make_float2(-INFINITY, 0.0f);
   // Eight loads in flight per thread, merged in tile order.
-  for (int64_t c0 = t; c0 < nct; c0 += 256 * 8) {
+  for (int64_t c0 = t; c0 < nct; c0 += TPR * 8) {
     float2 v[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-      const int64_t c = c0 + 256 * k;
+      const int64_t c = c0 + TPR * k;
       v[k] = c < nct ? row[c] : make_float2(-INFINITY, 0.0f);
     }
 #pragma unroll
-    for (int k = 0; k < 8; ++k) acc = lse_merge2(acc, v[k]);
+    for (int k = 0; k < 8; ++k) acc = merge(acc, v[k]);
   }
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    float2 o;
-    o.x = __shfl_xor(acc.x, off, 64);
-    o.y = __shfl_xor(acc.y, off, 64);
-    acc = lse_merge2(acc, o);
+  for (int off = 32; off > 0; off >>= 1)
+    acc = merge(acc, make_float2(__shfl_xor(acc.x, off, 64), __shfl_xor(acc.y, off, 64)));
+  if constexpr (WPR > 1) {
+    if (lane == 0) red[wave] = acc;
+    __syncthreads();
+    acc = red[wave];
+    if (t == 0) {
+      static_assert(WPR == 4, "four waves per row");
+      acc = merge(merge(red[wave], red[wave + 1]), merge(red[wave + 2], red[wave + 3]));
+    }
   }
-  if (lane == 0) red[t >> 6] = acc;
-  __syncthreads();
-  if (t == 0) {
-    acc = lse_merge2(lse_merge2(red[0], red[1]), lse_merge2(red[2], red[3]));
+  if (t == 0 && n < B) {
     const float lse = acc.x == -INFINITY ? -INFINITY
-                                         : (acc.x + log2f(acc.y)) * 0.6931471805599453f;
+                      : BASE2           ? (acc.x + log2f(acc.y)) * 0.6931471805599453f
+                                        : acc.x + __logf(acc.y);
     row_lse[n] = lse;
     const int yh = yhat[n];
-    loss_part[n] = yh >= 0 && yh < *n_active_p ? lse - tgt[n] : 0.0f;   // past |S|: unowned
+    loss_part[n] = yh >= 0 && yh < K ? lse - tgt[n] : 0.0f;   // past |S|: unowned
   }
-}
-
-// fp32 path (small problems): one thread per (row, class) dot product.
-// With tau < 1, a negative whose cosine exceeds tau is stored as -inf (PFC*,
-// Eq. noise_filtering): its logit and its coefficient in the backward are 0.
-__global__ void __launch_bounds__(256) k_fwd32(const float* __restrict__ X,
-                                               const float* __restrict__ W,
-                                               const int32_t* __restrict__ active,
-                                               const int32_t* __restrict__ n_active_p,
-                                               const int32_t* __restrict__ yhat,
-                                               const float* __restrict__ inv_x,
-                                               const float* __restrict__ inv_w, int B, int d,
-                                               int64_t cap, int64_t ld_cos, float tau,
-                                               float* __restrict__ cos32) {
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int n = blockIdx.y;
-  if (j >= cap || j >= *n_active_p || n >= B) return;
-  const float* x = X + (int64_t)n * d;
-  const float* w = W + (int64_t)active[j] * d;
-  float acc = 0.0f;
-  for (int i = 0; i < d; ++i) acc = fmaf(x[i], w[i], acc);
-  const float c = acc * inv_x[n] * inv_w[j];
-  cos32[(int64_t)n * ld_cos + j] = (tau < 1.0f && j != yhat[n] && c > tau) ? -INFINITY : c;
-}
-
-__global__ void __launch_bounds__(256) k_lse32(const float* __restrict__ cos32, int64_t ld_cos,
-                                               const int32_t* __restrict__ n_active_p,
-                                               const int32_t* __restrict__ yhat, int B, Margin mg,
-                                               float* __restrict__ row_lse,
-                                               float* __restrict__ loss_part) {
-  const int lane = threadIdx.x & 63;
-  const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (n >= B) return;
-  const int K = *n_active_p;
-  const int yh = yhat[n];
-  float2 acc = make_float2(-INFINITY, 0.0f);
-  float ft = 0.0f;
-  for (int j = lane; j < K; j += 64) {
-    const float c = cos32[(int64_t)n * ld_cos + j];
-    const float f = j == yh ? target_logit(mg, c) : mg.s * c;
-    if (j == yh) ft = f;
-    acc = lse_merge(acc, make_float2(f, 1.0f));
-  }
+  __syncthreads();
+  if (threadIdx.x == 0)   // releases the workgroup's loss terms, acquires the others'
+    last = __hip_atomic_fetch_add(arrivals, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) ==
+           gridDim.x - 1;
+  __syncthreads();
+  if (!last) return;
+  double sum = 0.0;
+  for (int i = threadIdx.x; i < B; i += kLseThreads)
+    sum += (double)__hip_atomic_load(loss_part + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    float2 o;
-    o.x = __shfl_xor(acc.x, off, 64);
-    o.y = __shfl_xor(acc.y, off, 64);
-    acc = lse_merge(acc, o);
-    ft += __shfl_xor(ft, off, 64);
-  }
-  if (lane == 0) {
-    const float lse = acc.x + __logf(acc.y);
-    row_lse[n] = lse;
-    loss_part[n] = yh >= 0 && yh < K ? lse - ft : 0.0f;
-  }
-}
-
-// Deterministic batch mean of the row loss terms (one workgroup).
-__global__ void __launch_bounds__(1024) k_loss(const float* __restrict__ loss_part, int B,
-                                               float* __restrict__ loss) {
-  __shared__ double part[16];
-  double acc = 0.0;
-  for (int n = threadIdx.x; n < B; n += blockDim.x) acc += (double)loss_part[n];
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = acc;
+  for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+  if ((threadIdx.x & 63) == 0) part[wave] = sum;
   __syncthreads();
   if (threadIdx.x == 0) {
     double s = 0.0;
-    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) s += part[w];
+    for (int w = 0; w < kLseThreads / 64; ++w) s += part[w];
     *loss = (float)(s / (double)B);
   }
 }
@@ -660,41 +618,44 @@ void launch_fwd16(int d, unsigned grid, hipStream_t stream, const StepArgs& a, c
 
 }  // namespace
 
+hipError_t launch_lse(const StepArgs& a, const StepWs& w, int64_t n_ctiles, int tile, bool base2,
+                      hipStream_t stream) {
+  const int B = (int)a.B;
+  timing_start(3, stream);
+  auto go = [&](auto kernel, int rows) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)ceil_div(B, rows)), dim3(kLseThreads), 0, stream,
+                       w.stats, n_ctiles, tile, a.n_active, a.labels_mapped, w.tgt, B,
+                       a.row_lse_out, w.loss_part, w.arrivals, a.loss);
+  };
+  // A wave per row while one pass of eight loads per lane covers its pairs.
+  if (n_ctiles <= 512) {
+    if (base2) go(k_lse<64, true>, kLseThreads / 64);
+    else go(k_lse<64, false>, kLseThreads / 64);
+  } else {
+    if (base2) go(k_lse<256, true>, kLseThreads / 256);
+    else go(k_lse<256, false>, kLseThreads / 256);
+  }
+  timing_stop(3, stream);
+  return hipGetLastError();
+}
+
 hipError_t launch_forward(const StepArgs& a, const StepWs& w, hipStream_t stream) {
+  if (a.dtype == 0) return launch_forward_f32(a, w, stream);
   hipError_t e = launch_prep(a, w, stream);
   if (e != hipSuccess) return e;
   const int B = (int)a.B, d = (int)a.d;
   Margin mg{a.s, a.m, cosf(a.m), sinf(a.m), a.margin};
-  if (a.dtype == 0) {
-    dim3 grid((unsigned)ceil_div(a.cap, 256), (unsigned)B);
-    timing_start(2, stream);
-    hipLaunchKernelGGL(k_fwd32, grid, dim3(256), 0, stream, (const float*)a.X,
-                       (const float*)a.W, a.active, a.n_active, a.labels_mapped, w.inv_x,
-                       w.inv_w, B, d, a.cap, w.ld_cos, a.tau, (float*)w.lbuf);
-    timing_stop(2, stream);
-    timing_start(3, stream);
-    hipLaunchKernelGGL(k_lse32, dim3((unsigned)ceil_div(B, 4)), dim3(256), 0, stream,
-                       (const float*)w.lbuf, w.ld_cos, a.n_active, a.labels_mapped, B, mg,
-                       a.row_lse_out, w.loss_part);
-  } else {
-    const int n_rt = (int)ceil_div(B, kFwdBN);
-    const int64_t n_tiles = w.n_ctiles * n_rt;
-    const int64_t per_xcd = ceil_div(n_tiles, 8);
-    const unsigned grid = (unsigned)(8 * per_xcd);
-    timing_start(2, stream);
-    if (a.dtype == 1)
-      launch_fwd16<Bf16Tag>(d, grid, stream, a, w, B, n_rt, n_tiles, per_xcd, mg);
-    else
-      launch_fwd16<F16Tag>(d, grid, stream, a, w, B, n_rt, n_tiles, per_xcd, mg);
-    timing_stop(2, stream);
-    timing_start(3, stream);
-    hipLaunchKernelGGL(k_lse16, dim3((unsigned)B), dim3(256), 0, stream, w.stats,
-                       w.n_ctiles, a.n_active, a.labels_mapped, w.tgt, B, a.row_lse_out,
-                       w.loss_part);
-  }
-  hipLaunchKernelGGL(k_loss, dim3(1), dim3(1024), 0, stream, w.loss_part, B, a.loss);
-  timing_stop(3, stream);
-  return hipGetLastError();
+  const int n_rt = (int)ceil_div(B, kFwdBN);
+  const int64_t n_tiles = w.n_ctiles * n_rt;
+  const int64_t per_xcd = ceil_div(n_tiles, 8);
+  const unsigned grid = (unsigned)(8 * per_xcd);
+  timing_start(2, stream);
+  if (a.dtype == 1)
+    launch_fwd16<Bf16Tag>(d, grid, stream, a, w, B, n_rt, n_tiles, per_xcd, mg);
+  else
+    launch_fwd16<F16Tag>(d, grid, stream, a, w, B, n_rt, n_tiles, per_xcd, mg);
+  timing_stop(2, stream);
+  return launch_lse(a, w, w.n_ctiles, kFwdClassTile, true, stream);
 }
 
 }  // namespace pfc

@@ -65,6 +65,7 @@ struct StepWs {
                          // at the target and past |S|); fp32 path: fp32 cosines
   int64_t ld_cos;        // row stride of lbuf: cap rounded up to 256
   float2* stats;         // [B x n_ctiles] per class tile: (max, sum 2^(f log2 e - max)), base 2
+                         // (fp32 path: base e)
   int64_t n_ctiles;      // class tiles of the forward contraction
   float* tgt;            // [B] margined target logit
   float* tgtc;           // [B] unmargined target cosine
@@ -75,6 +76,7 @@ struct StepWs {
   float* dx_part;        // [n_split x B x d] split-K partial sums of dX_hat
   int n_split;
   float* loss_part;      // [B] per-row loss terms
+  uint32_t* arrivals;    // [1] workgroups that have written their rows' loss terms
   int32_t* act_pad;      // [n_act_pad] the active row ids, padded with the last one
                          // (read a whole 32-class chunk at a time by the dX kernel)
   int64_t n_act_pad;     // cap rounded up to 128
@@ -92,7 +94,7 @@ struct WsLayout {
   size_t off_bitmap, off_hist, off_state, off_digits, off_cand_key;
   size_t off_grp_sure, off_grp_tie, off_grp_out, off_grp_tie_off;
   size_t off_inv_x, off_xb, off_xblk, off_wmax, off_inv_w, off_cos, off_stats, off_tgt, off_tgtc,
-      off_gmax, off_gscale, off_dx, off_loss, off_act_pad, off_dw_gate;
+      off_gmax, off_gscale, off_dx, off_loss, off_act_pad, off_dw_gate, off_arrivals;
   int64_t ld_cos, n_ctiles, n_groups, ld_xt, ld_g, n_lgroups, n_act_pad;
   int n_split;
   int top_bits;
@@ -135,6 +137,16 @@ struct StepArgs {
 hipError_t launch_prep(const StepArgs& a, const StepWs& w, hipStream_t stream);
 hipError_t launch_forward(const StepArgs& a, const StepWs& w, hipStream_t stream);
 hipError_t launch_backward(const StepArgs& a, const StepWs& w, hipStream_t stream);
+// Row log-sum-exp and loss from the (max, sum) pairs of n_ctiles tiles of
+// `tile` classes (in base 2, else base e).
+hipError_t launch_lse(const StepArgs& a, const StepWs& w, int64_t n_ctiles, int tile, bool base2,
+                      hipStream_t stream);
+// The fp32 path (f32.hip).
+hipError_t launch_forward_f32(const StepArgs& a, const StepWs& w, hipStream_t stream);
+hipError_t launch_backward_f32(const StepArgs& a, const StepWs& w, hipStream_t stream);
+int split_f32(int64_t B, int64_t cap);   // class splits of its feature gradient
+// Narrowest class tile of the fp32 forward.
+constexpr int kFwdClassTile32 = 32;
 
 // Measurement hook (pfc_timing_begin / pfc_timing_end): launchers bracket a
 // kernel id's launches with these calls; both are no-ops unless armed.

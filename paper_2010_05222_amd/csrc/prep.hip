@@ -7,7 +7,8 @@
 // row / column scales.  On the 16-bit paths the class-row norms come out of
 // the forward contraction kernel, which streams every active row through
 // LDS anyway; this file holds the batch side (norms, the transposed bf16
-// copy used by the class-gradient contraction) and the fp32 path.
+// copy used by the class-gradient contraction).  The fp32 path's forward sums
+// both sides' norms itself.
 #include "pfc_device.h"
 
 namespace pfc {
@@ -33,7 +34,8 @@ __device__ __forceinline__ float sumsq8(const uint4& v) {
 // transposes through LDS; and the raw rows in 32-wide column blocks (block k
 // = [ld_xt][32]: entry (n, e) = X[n][32 k + e]), the forward's operand, whose
 // k-th chunk of a run of rows is then contiguous.  Rows n in [B, ld_xt) are
-// zero in both.  Also clears the running max of 1/||w_j||.
+// zero in both.  Also clears the running max of 1/||w_j|| and the arrival count
+// of the loss mean.
 // Workgroups past the first ld_xt / 32 write the padded copy of the active
 // row ids that the contraction kernels read a chunk or tile at a time, with
 // no wait on |S|: act_pad[j] = active[min(j, |S| - 1)] (0 if S is empty).
@@ -45,6 +47,7 @@ __global__ void __launch_bounds__(256) k_prep_x16(const uint16_t* __restrict__ X
                                                   uint16_t* __restrict__ xbT,
                                                   uint16_t* __restrict__ xblk,
                                                   float* __restrict__ inv_w_max,
+                                                  uint32_t* __restrict__ arrivals,
                                                   const int32_t* __restrict__ active,
                                                   const int32_t* __restrict__ n_active_p,
                                                   int32_t* __restrict__ act_pad, int64_t n_pad) {
@@ -63,7 +66,10 @@ __global__ void __launch_bounds__(256) k_prep_x16(const uint16_t* __restrict__ X
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n0 = blockIdx.x * kPrepRows;
-  if (blockIdx.x == 0 && threadIdx.x == 0) *inv_w_max = 0.0f;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    *inv_w_max = 0.0f;
+    *arrivals = 0;
+  }
   // Each wave's eight rows: all loads first (one memory round trip, not eight).
   const bool c_ok = lane < d / 8;   // d <= 512: one 16-byte piece per lane
   uint4 rows[kPrepRows / 4];
@@ -107,60 +113,19 @@ __global__ void __launch_bounds__(256) k_prep_x16(const uint16_t* __restrict__ X
   }
 }
 
-__global__ void __launch_bounds__(256) k_prep_x32(const float* __restrict__ X, int B, int d,
-                                                  float* __restrict__ inv_x) {
-  const int lane = threadIdx.x & 63;
-  const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (n >= B) return;
-  const float* row = X + (int64_t)n * d;
-  float ss = 0.0f;
-  for (int i = lane; i < d; i += 64) ss = fmaf(row[i], row[i], ss);
-  ss = wave_sum(ss);
-  if (lane == 0) inv_x[n] = 1.0f / fmaxf(sqrtf(ss), kEpsNorm);
-}
-
-__global__ void __launch_bounds__(256) k_norm_w32(const float* __restrict__ W, int d,
-                                                  const int32_t* __restrict__ active,
-                                                  const int32_t* __restrict__ n_active,
-                                                  int64_t cap, float* __restrict__ inv_w) {
-  const int lane = threadIdx.x & 63;
-  const int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (j >= cap || j >= *n_active) return;
-  const float* row = W + (int64_t)active[j] * d;
-  float ss = 0.0f;
-  for (int c = lane; c < d / 4; c += 64) {
-    const float4 v = *reinterpret_cast<const float4*>(row + 4 * c);
-    ss = fmaf(v.x, v.x, fmaf(v.y, v.y, fmaf(v.z, v.z, fmaf(v.w, v.w, ss))));
-  }
-  for (int i = (d / 4) * 4 + lane; i < d; i += 64) ss = fmaf(row[i], row[i], ss);
-  ss = wave_sum(ss);
-  if (lane == 0) inv_w[j] = 1.0f / fmaxf(sqrtf(ss), kEpsNorm);
-}
-
 }  // namespace
 
 hipError_t launch_prep(const StepArgs& a, const StepWs& w, hipStream_t stream) {
   const int B = (int)a.B, d = (int)a.d;
-  const unsigned wblocks = (unsigned)ceil_div(a.cap, 4);
+  const unsigned grid = (unsigned)(w.ld_xt / kPrepRows + ceil_div(w.n_act_pad, kPadPerBlock));
   timing_start(1, stream);
-  if (a.dtype == 0) {
-    hipLaunchKernelGGL(k_prep_x32, dim3((unsigned)ceil_div(B, 4)), dim3(256), 0, stream,
-                       (const float*)a.X, B, d, w.inv_x);
-    hipLaunchKernelGGL(k_norm_w32, dim3(wblocks), dim3(256), 0, stream, (const float*)a.W, d,
-                       a.active, a.n_active, a.cap, w.inv_w);
-  } else {
-    const unsigned grid = (unsigned)(w.ld_xt / kPrepRows + ceil_div(w.n_act_pad, kPadPerBlock));
-    if (a.dtype == 1)
-      hipLaunchKernelGGL(k_prep_x16<Bf16Tag>, dim3(grid), dim3(256), 0, stream,
-                         (const uint16_t*)a.X, B, d, w.ld_xt, w.inv_x, (uint16_t*)w.xbT,
-                         (uint16_t*)w.xblk, w.inv_w_max, a.active, a.n_active, w.act_pad,
-                         w.n_act_pad);
-    else
-      hipLaunchKernelGGL(k_prep_x16<F16Tag>, dim3(grid), dim3(256), 0, stream,
-                         (const uint16_t*)a.X, B, d, w.ld_xt, w.inv_x, (uint16_t*)w.xbT,
-                         (uint16_t*)w.xblk, w.inv_w_max, a.active, a.n_active, w.act_pad,
-                         w.n_act_pad);
-  }
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, stream, (const uint16_t*)a.X, B, d,
+                       w.ld_xt, w.inv_x, (uint16_t*)w.xbT, (uint16_t*)w.xblk, w.inv_w_max,
+                       w.arrivals, a.active, a.n_active, w.act_pad, w.n_act_pad);
+  };
+  if (a.dtype == 1) go(k_prep_x16<Bf16Tag>);
+  else go(k_prep_x16<F16Tag>);
   timing_stop(1, stream);
   return hipGetLastError();
 }

@@ -105,6 +105,38 @@ def test_f32_feature_widths(dev, d):
     _case(dev, 40, d, 1500, 0.2, "f32", "arcface", 0.5, seed=27, abs_scaled=(d == 8))
 
 
+@pytest.mark.parametrize("B,d,C,r,master,tau", [
+    (1, 8, 40, 0.5, False, None),          # one row, one 64-column block, a partial class tile
+    (16, 64, 330, 0.1, True, None),        # a full 16-row wave; |S| = 33
+    (65, 520, 640, 0.1, False, 0.4),       # one row past a 64-row tile; nine column blocks
+    (33, 1016, 650, 0.1, True, None),      # 32 + 1 rows of dX; sixteen column blocks, |S| = 65
+    (600, 200, 8200, 0.5, False, 0.4),     # enough tiles for the 64-class forward
+])
+def test_f32_tile_edges(dev, B, d, C, r, master, tau):
+    # The max-abs bar relative to max |ref|: the gradient scale s/B is 64 / B.
+    _case(dev, B, d, C, r, "f32", "arcface", 0.5, seed=61, master=master, tau=tau, conflicts=2,
+          abs_scaled=True)
+
+
+def test_f32_rows_need_no_16_byte_alignment(dev):
+    """fp32 tensors that start 4 bytes past a 16-byte boundary give the aligned
+    ones' results bit for bit."""
+    from _gpu_util import make_problem
+    outs = []
+    for off in (0, 1):
+        parts = make_problem(40, 136, 900, "f32", 62, master=True, device=dev)
+        Xd, Wd, Md, Pd = (torch.empty(t.numel() + 4, device=dev)[off:off + t.numel()]
+                          .view_as(t).copy_(t) for t in parts[:4])
+        assert Xd.data_ptr() % 16 == 4 * off
+        shard = _shard(40, 136, 900, 0.2, "f32", "arcface", 0.5, dev=dev)
+        shard.dX = torch.empty(40 * 136 + 4, device=dev)[off:off + 40 * 136].view(40, 136)
+        shard.step(Xd, parts[4], Wd, Md, 62, Pd)
+        torch.cuda.synchronize()
+        outs.append((shard.loss, shard.row_lse, shard.dX, Xd, Wd, Md, Pd))
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_single_class_shard(dev, dtype):
     # The smallest shard: one class, taken at r = 1.  Rows labelled with it
