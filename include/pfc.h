@@ -111,7 +111,7 @@ int pfc_sample(const int64_t* labels, int64_t B, int64_t C,
  * memory (code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc).  Same arguments, outputs and selection rule as
  * pfc_sample, minus ws / ws_bytes: the sampler's scratch is a file-scope
- * device array of the library, about 21 MiB on every device the library runs
+ * device array of the library, about 18 MiB on every device the library runs
  * on, held until the process ends.  Its address is looked up on the first
  * call on each device (that call must run with the device current).
  *

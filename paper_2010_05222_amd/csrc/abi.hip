@@ -13,12 +13,6 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 int64_t round_up(int64_t x, int64_t m) { return ceil_div(x, m) * m; }
 
-int ceil_log2(int64_t x) {
-  int b = 0;
-  while (((int64_t)1 << b) < x) ++b;
-  return b;
-}
-
 bool dtype_ok(int t) { return t == PFC_F32 || t == PFC_BF16 || t == PFC_F16; }
 
 bool finite_pos(double v) { return isfinite(v) && v > 0.0; }
@@ -68,16 +62,12 @@ WsLayout ws_layout(int64_t B, int64_t d, int64_t C, int64_t cap, int compute) {
     off = align256(off + bytes);
     return o;
   };
-  L.n_groups = ceil_div(C, kCompactClasses);
-  L.top_bits = ceil_log2(C) - 10;
-  L.top_bits = L.top_bits < 1 ? 1 : (L.top_bits > kTopBitsMax ? kTopBitsMax : L.top_bits);
-  L.off_bitmap = take((size_t)ceil_div(C, 32) * 4);
-  L.off_hist = take((size_t)(1 << kTopBitsMax) * 4);
+  L.n_groups = ceil_div(C, kGroupClasses);
   L.off_state = take(sizeof(SampleState));
-  L.off_digits = take((size_t)round_up(C, kCompactPer) * 2);   // read 16 at a time
+  L.off_masks = take((size_t)round_up(L.n_groups, 4) * kGroupThreads * 8);   // whole spans
   L.off_cand_key = take((size_t)C * 8);
   L.off_grp_sure = take((size_t)L.n_groups * 4);
-  L.off_grp_tie = take((size_t)L.n_groups * 4);
+  L.off_grp_cand = take((size_t)L.n_groups * 4);
   L.off_grp_out = take((size_t)L.n_groups * 4);
   L.off_grp_tie_off = take((size_t)L.n_groups * 4);
   L.sample_bytes = off;
@@ -123,13 +113,11 @@ WsLayout ws_layout(int64_t B, int64_t d, int64_t C, int64_t cap, int compute) {
 SampleWs sample_ws(void* ws, const WsLayout& L) {
   char* b = (char*)ws;
   SampleWs w;
-  w.bitmap = (uint32_t*)(b + L.off_bitmap);
-  w.hist = (uint32_t*)(b + L.off_hist);
   w.state = (SampleState*)(b + L.off_state);
-  w.digits = (uint16_t*)(b + L.off_digits);
+  w.masks = (uint64_t*)(b + L.off_masks);
   w.cand_key = (uint64_t*)(b + L.off_cand_key);
   w.grp_sure = (uint32_t*)(b + L.off_grp_sure);
-  w.grp_tie = (uint32_t*)(b + L.off_grp_tie);
+  w.grp_cand = (uint32_t*)(b + L.off_grp_cand);
   w.grp_out = (uint32_t*)(b + L.off_grp_out);
   w.grp_tie_off = (uint32_t*)(b + L.off_grp_tie_off);
   return w;
@@ -194,7 +182,7 @@ int pfc_sample(const int64_t* labels, int64_t B, int64_t C, int64_t class_offset
   if (!ws || ((uintptr_t)ws & 255) != 0) return PFC_ERR_WORKSPACE;
   if (ws_bytes < L.sample_bytes) return PFC_ERR_WORKSPACE;
   (void)hipGetLastError();
-  const hipError_t e = launch_sample(labels, B, C, class_offset, budget_of(r, C), seed, L.top_bits,
+  const hipError_t e = launch_sample(labels, B, C, class_offset, budget_of(r, C), seed,
                                      L.n_groups, sample_ws(ws, L), active, active_cap, n_active,
                                      labels_mapped, (hipStream_t)stream);
   return e == hipSuccess ? PFC_OK : PFC_ERR_HIP;

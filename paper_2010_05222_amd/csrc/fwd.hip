@@ -518,8 +518,9 @@ __global__ void __launch_bounds__(kFwdThreads, 2) k_fwd16(
 // thread merges its pairs in tile order, the waves' pairs meet through lane
 // moves and LDS in a fixed order, and the mean is summed in a fixed order, so
 // the result does not depend on which workgroup is last.  A kernel of its own
-// for the mean cost a launch (4.4 us, the length of a launch that does next to
-// nothing); several rows per workgroup keep the arrivals few.
+// for the mean took 4.4 us, as long as any launch that does next to nothing
+// (B = 128: 4.7 + 3.9 -> 7.1 us); several rows per workgroup keep the arrivals
+// few.
 constexpr int kLseThreads = 1024;
 template <int TPR, bool BASE2>
 __global__ void __launch_bounds__(kLseThreads) k_lse(
@@ -567,11 +568,17 @@ __global__ void __launch_bounds__(kLseThreads) k_lse(
                                         : acc.x + __logf(acc.y);
     row_lse[n] = lse;
     const int yh = yhat[n];
-    loss_part[n] = yh >= 0 && yh < K ? lse - tgt[n] : 0.0f;   // past |S|: unowned
+    // Written through to where every CU sees it, and waited for before the
+    // barrier, so the arrival needs no cache flush (with an acquire-release
+    // arrival of each workgroup the kernel took 12.1 instead of 10.1 us at 250
+    // workgroups).
+    __hip_atomic_store(loss_part + n, yh >= 0 && yh < K ? lse - tgt[n] : 0.0f,   // past |S|: unowned
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if (threadIdx.x == 0)   // releases the workgroup's loss terms, acquires the others'
-    last = __hip_atomic_fetch_add(arrivals, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) ==
+  if (threadIdx.x == 0)
+    last = __hip_atomic_fetch_add(arrivals, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
            gridDim.x - 1;
   __syncthreads();
   if (!last) return;

@@ -10,36 +10,37 @@ namespace pfc {
 
 // ----------------------------------------------------------------- sampler
 
-enum SampleMode : uint32_t { kSelectNone = 0, kSelectKeys = 1, kSelectAll = 2 };
-
-// Device-resident sampler state of one step (lives in the workspace).
+// Sampler state between the kernels of a shard with many groups (device
+// resident, in the workspace).
 struct SampleState {
-  uint32_t n_pos;       // |P|: distinct owned labels
-  uint32_t mode;        // SampleMode
-  uint32_t top_digit;   // value of the top key bits holding the threshold
-  int64_t n_neg;        // max(b - |P|, 0)
-  int64_t k_rem;        // keys equal to `thresh` still to take (class order)
   uint64_t thresh;      // n_neg-th smallest non-positive key
+  int64_t ties;         // non-positive keys equal to `thresh` to take (class order)
+  int64_t rank;         // of the threshold among the candidates; -1: outside their window
+  bool all_ties;        // `ties` is all of them
+  bool all_keys;        // the threshold was found over all keys
 };
 
-// Compaction works on groups of kCompactClasses consecutive classes.
-constexpr int kCompactThreads = 256;
-constexpr int kCompactPer = 16;   // classes per thread
-constexpr int kCompactClasses = kCompactPer * kCompactThreads;
-constexpr int kTopBitsMax = 12;
+// The classes go in groups of kGroupClasses consecutive ones, a workgroup each
+// when the keys are drawn.
+constexpr int kGroupThreads = 256;
+constexpr int kPerThread = 16;    // classes per thread
+constexpr int kGroupClasses = kPerThread * kGroupThreads;
+constexpr int kRunMax = 16;       // most groups per workgroup
+constexpr int kSpanRunMax = 8;    // most spans (of four groups) per workgroup of the output
+// Up to this many groups each workgroup of the output resolves the threshold
+// by itself, which saves a launch.
+constexpr int kMergeGroups = 512;
 
 struct SampleWs {
-  uint32_t* bitmap;      // ceil(C/32) words: bit c set iff class c is positive
-  uint32_t* hist;        // 2^kTopBitsMax bins
   SampleState* state;
-  uint16_t* digits;      // C top-bit digits of the keys (only in kSelectKeys mode)
-  uint64_t* cand_key;    // C: the full keys of compaction group g's non-positive classes
-                         // in the threshold's top bucket at [g * kCompactClasses, + count)
-  uint32_t* grp_sure;    // per compaction group: classes surely selected
-  uint32_t* grp_tie;     // per compaction group: its candidate count, then (once the
-                         // threshold is resolved) its non-positive keys == thresh
-  uint32_t* grp_out;     // per compaction group: output offset
-  uint32_t* grp_tie_off; // per compaction group: ties before the group
+  uint64_t* masks;       // per 16 classes: masks of the positives, of the classes surely in S
+                         // and of the candidates, 16 bits each
+  uint64_t* cand_key;    // C: the keys of group g's candidates, in class order, at
+                         // [g * kGroupClasses, + count)
+  uint32_t* grp_sure;    // per group: classes surely in S, and its positives << 16
+  uint32_t* grp_cand;    // per group: candidates
+  uint32_t* grp_out;     // per group: output offset
+  uint32_t* grp_tie_off; // per group: ties before the group
 };
 
 // ----------------------------------------------------------------- step
@@ -91,13 +92,12 @@ constexpr int kDwGates = 512;
 struct WsLayout {
   size_t bytes;
   size_t sample_bytes;   // prefix used by the sampler
-  size_t off_bitmap, off_hist, off_state, off_digits, off_cand_key;
-  size_t off_grp_sure, off_grp_tie, off_grp_out, off_grp_tie_off;
+  size_t off_state, off_masks, off_cand_key;
+  size_t off_grp_sure, off_grp_cand, off_grp_out, off_grp_tie_off;
   size_t off_inv_x, off_xb, off_xblk, off_wmax, off_inv_w, off_cos, off_stats, off_tgt, off_tgtc,
       off_gmax, off_gscale, off_dx, off_loss, off_act_pad, off_dw_gate, off_arrivals;
   int64_t ld_cos, n_ctiles, n_groups, ld_xt, ld_g, n_lgroups, n_act_pad;
   int n_split;
-  int top_bits;
 };
 
 // Activation budget b of a shard and the capacity max(b, min(B, C)) of S.
@@ -110,7 +110,7 @@ StepWs step_ws(void* ws, const WsLayout& L);
 
 hipError_t launch_sample(const int64_t* labels, int64_t B, int64_t C,
                          int64_t a, int64_t budget, uint64_t seed,
-                         int top_bits, int64_t n_groups, const SampleWs& w,
+                         int64_t n_groups, const SampleWs& w,
                          int32_t* active, int64_t cap, int32_t* n_active,
                          int32_t* labels_mapped, hipStream_t stream);
 

@@ -5,18 +5,29 @@
 // smallest 64-bit Philox keys, ties to the lower class id}, sorted ascending,
 // then labels_mapped = searchsorted(S, y - a).
 //
-// Kernel sequence (no host synchronisation; every kernel reads the
-// device-side mode and returns early when it has nothing to do):
-//   clear -> mark positives (bitmap, |P|) -> plan (mode, n_neg)
-//   -> keys + top-bit histogram (one Philox pass; only each key's top-bit
-//      digit is kept, 2 bytes per class)
-//   -> pick the top bucket holding the n_neg-th key -> collect that bucket
-//      (its keys recomputed in full)
-//   -> resolve the remaining key bits inside one workgroup (exact threshold)
-//   -> count / scan / write compaction in class order (wavefront ballots),
-//      which yields S already sorted -> remap by binary search.
-// A class whose digit differs from the threshold's is decided by the digit
-// alone; the few in the threshold's bucket compare their recomputed key.
+// The keys are uniform, so the threshold (the n_neg-th smallest key) is known
+// beforehand to within a few standard deviations, and one pass over the keys
+// settles every class outside that window:
+//   k_keys     positives of a group of classes (from the labels, in LDS), its
+//              keys, and per class: surely in S (a positive, or a key below
+//              the window), surely not (above), or a candidate, whose key is
+//              written out;
+//   k_resolve_write  the exact threshold among the candidates (by each
+//              workgroup for itself), each group's place in S, S in class
+//              order, and the labels' places in it.
+// A shard of at most four groups does both in one launch (k_sample_one), and one with
+// more than kMergeGroups groups finds the threshold once (k_resolve) before
+// k_write.  If the count below the window or up to its end turns out wrong
+// (3e-7 of all draws, 5e-5 of those with a budget of one), the threshold is
+// found over all keys, recomputed: slow, and the same result.  When the budget
+// is the whole shard nothing is drawn (k_take_all).  No host synchronisation,
+// and no state that has to be cleared first.
+//
+// This replaces ten launches (clear, mark, plan, key digits and histogram, top
+// digit, collect, refine, scan, write, remap), whose time was mostly that of
+// empty launches: 10 K classes 55 -> 13 us, 100 K 46 -> 17 us, 2M 49 -> 27 us.
+#include <math.h>
+
 #include "pfc_internal.h"
 
 namespace pfc {
@@ -29,659 +40,788 @@ constexpr uint64_t kPhiloxM1 = 0xCA5A826395121157ull;
 constexpr uint64_t kPhiloxW0 = 0x9E3779B97F4A7C15ull;
 constexpr uint64_t kPhiloxW1 = 0xBB67AE8584CAA73Bull;
 
-struct U64x4 {
-  uint64_t v[4];
-};
-
-__device__ __forceinline__ U64x4 philox4x64_10(uint64_t c0, uint64_t seed) {
-  uint64_t x0 = c0, x1 = 0, x2 = 0, x3 = 0;
-  uint64_t k0 = seed, k1 = 0;
+// N consecutive blocks from counter c0 on, their words in order.  The rounds are
+// a loop over all blocks at once (independent chains) and not unrolled: a
+// round of four blocks is about 1 KB of code, and on the small shards, where a
+// kernel runs once from a cold instruction cache, ten times that cost more
+// than the arithmetic.
+template <int N>
+__device__ __forceinline__ void philox4x64_10(uint64_t c0, uint64_t seed, uint64_t* out) {
+  uint64_t x[N][4];
 #pragma unroll
-  for (int r = 0; r < 10; ++r) {
-    if (r > 0) {
-      k0 += kPhiloxW0;
-      k1 += kPhiloxW1;
-    }
-    const uint64_t hi0 = __umul64hi(kPhiloxM0, x0);
-    const uint64_t lo0 = kPhiloxM0 * x0;
-    const uint64_t hi1 = __umul64hi(kPhiloxM1, x2);
-    const uint64_t lo1 = kPhiloxM1 * x2;
-    const uint64_t n0 = hi1 ^ x1 ^ k0;
-    const uint64_t n2 = hi0 ^ x3 ^ k1;
-    x0 = n0;
-    x1 = lo1;
-    x2 = n2;
-    x3 = lo0;
+  for (int i = 0; i < N; ++i) {
+    x[i][0] = c0 + i;
+    x[i][1] = x[i][2] = x[i][3] = 0;
   }
-  U64x4 out;
-  out.v[0] = x0;
-  out.v[1] = x1;
-  out.v[2] = x2;
-  out.v[3] = x3;
-  return out;
-}
-
-// Key of class c of the shard starting at global class a.  The word is
-// picked with selects: indexing the block's words by a run-time value would
-// place them in LDS, and that costs more than the generator here.
-__device__ __forceinline__ uint64_t class_key(uint64_t seed, int64_t a, int64_t c) {
-  const int64_t g = a + c;
-  const U64x4 w = philox4x64_10((uint64_t)(g >> 2), seed);
-  const int i = (int)(g & 3);
-  return i == 0 ? w.v[0] : i == 1 ? w.v[1] : i == 2 ? w.v[2] : w.v[3];
-}
-
-// Digits of the 16 classes c0 .. c0 + 15 (c0 a multiple of 16; the digit
-// array is padded to whole groups of 16): two 16-byte loads.
-__device__ __forceinline__ void load_digits16(const uint16_t* digits, int64_t c0, uint32_t (&w)[8]) {
-  const uint4 d0 = *reinterpret_cast<const uint4*>(digits + c0);
-  const uint4 d1 = *reinterpret_cast<const uint4*>(digits + c0 + 8);
-  w[0] = d0.x; w[1] = d0.y; w[2] = d0.z; w[3] = d0.w;
-  w[4] = d1.x; w[5] = d1.y; w[6] = d1.z; w[7] = d1.w;
-}
-__device__ __forceinline__ uint32_t digit_of(const uint32_t (&w)[8], int i) {
-  return (w[i >> 1] >> (16 * (i & 1))) & 0xFFFFu;
+  uint64_t k0 = seed, k1 = 0;
+#pragma unroll 1
+  for (int r = 0; r < 10; ++r) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const uint64_t hi0 = __umul64hi(kPhiloxM0, x[i][0]);
+      const uint64_t lo0 = kPhiloxM0 * x[i][0];
+      const uint64_t hi1 = __umul64hi(kPhiloxM1, x[i][2]);
+      const uint64_t lo1 = kPhiloxM1 * x[i][2];
+      x[i][0] = hi1 ^ x[i][1] ^ k0;
+      x[i][1] = lo1;
+      x[i][2] = hi0 ^ x[i][3] ^ k1;
+      x[i][3] = lo0;
+    }
+    k0 += kPhiloxW0;
+    k1 += kPhiloxW1;
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) out[4 * i + e] = x[i][e];
 }
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 
-__device__ __forceinline__ uint32_t popc_below(uint64_t mask) {
-  const uint64_t below = (1ull << lane_id()) - 1ull;
-  return (uint32_t)__popcll(mask & below);
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_add(uint32_t v) {
+  return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
 }
 
-// Exclusive prefix sum of `v` over the block (blockDim.x a multiple of 64,
-// at most 1024 threads); `total` receives the block sum.  Uses `smem` of
-// (blockDim.x / 64) entries.
-__device__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* smem, uint32_t* total) {
-  const int lane = lane_id();
-  const int wave = threadIdx.x >> 6;
-  const int nwaves = blockDim.x >> 6;
-  uint32_t incl = v;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t t = __shfl_up(incl, off, 64);
-    if (lane >= off) incl += t;
-  }
-  if (lane == 63) smem[wave] = incl;
-  __syncthreads();
-  uint32_t wave_off = 0, sum = 0;
-  for (int w = 0; w < nwaves; ++w) {
-    const uint32_t t = smem[w];
-    if (w < wave) wave_off += t;
-    sum += t;
-  }
-  __syncthreads();
-  *total = sum;
-  return wave_off + incl - v;
+// Inclusive prefix sum over the wave by lane moves: shifts by 1, 2, 4, 8 inside
+// each row of 16, then the last lanes of rows 0 and 2 into rows 1 and 3, and
+// lane 31 into the upper half.  (Through __shfl, each step is an LDS round trip.)
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
+  v = dpp_add<0x111, 0xF>(v);
+  v = dpp_add<0x112, 0xF>(v);
+  v = dpp_add<0x114, 0xF>(v);
+  v = dpp_add<0x118, 0xF>(v);
+  v = dpp_add<0x142, 0xA>(v);
+  return dpp_add<0x143, 0xC>(v);
 }
 
-// Same for 64-bit sums.
-__device__ uint64_t block_exclusive_scan64(uint64_t v, uint64_t* smem, uint64_t* total) {
-  const int lane = lane_id();
-  const int wave = threadIdx.x >> 6;
-  const int nwaves = blockDim.x >> 6;
-  uint64_t incl = v;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint64_t t = __shfl_up(incl, off, 64);
-    if (lane >= off) incl += t;
-  }
-  if (lane == 63) smem[wave] = incl;
+// Exclusive prefix sum of `v` over the workgroup of kWaves waves (at most 16);
+// `total` receives its sum.
+template <int kWaves>
+__device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t* smem, uint32_t* total) {
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint32_t incl = wave_scan(v);
+  if (lane_id() == 63) smem[wave] = incl;
   __syncthreads();
-  uint64_t wave_off = 0, sum = 0;
-  for (int w = 0; w < nwaves; ++w) {
-    const uint64_t t = smem[w];
-    if (w < wave) wave_off += t;
-    sum += t;
-  }
+  const uint32_t sums = wave_scan(lane_id() < kWaves ? smem[lane_id()] : 0u);
   __syncthreads();
-  *total = sum;
-  return wave_off + incl - v;
+  *total = (uint32_t)__builtin_amdgcn_readlane((int)sums, kWaves - 1);
+  const uint32_t before = wave ? (uint32_t)__builtin_amdgcn_readlane((int)sums, wave - 1) : 0u;
+  return before + incl - v;
 }
 
-// Find the bin holding the k-th (1-based) element of an LDS histogram of
-// `nbins` bins (nbins a multiple of blockDim.x).  Returns through shared
-// out[0] = bin, out[1] = count before the bin, out[2] = count of the bin
-// (the last bin and zero counts if the histogram holds fewer than k).
-__device__ void find_kth_bin(const uint32_t* hist, int nbins, int64_t k,
-                             uint64_t* scan_smem, int64_t* out) {
+// Find the bin holding the k-th (1-based) element of an LDS histogram of kBins
+// bins (two per thread of 1,024).  Returns through shared out[0] = bin, out[1] = count
+// before the bin, out[2] = count of the bin (the last bin and zero counts if
+// the histogram holds fewer than k).
+constexpr int kBins = 2048;
+__device__ __forceinline__ void find_kth_bin(const uint32_t* hist, int64_t k, uint32_t* smem,
+                                             int64_t* out) {
   if (threadIdx.x == 0) {   // ordered before the writes below by the scan's barriers
-    out[0] = nbins - 1;
+    out[0] = kBins - 1;
     out[1] = 0;
     out[2] = 0;
   }
-  const int per = nbins / blockDim.x;
-  const int b0 = threadIdx.x * per;
-  uint64_t local = 0;
-  for (int i = 0; i < per; ++i) local += hist[b0 + i];
-  uint64_t total;
-  uint64_t before = block_exclusive_scan64(local, scan_smem, &total);
-  if ((int64_t)before < k && k <= (int64_t)(before + local)) {
-    for (int i = 0; i < per; ++i) {
-      const uint64_t h = hist[b0 + i];
-      if ((int64_t)(before + h) >= k) {
-        out[0] = b0 + i;
-        out[1] = (int64_t)before;
-        out[2] = (int64_t)h;
-        break;
-      }
-      before += h;
-    }
+  const int b = 2 * threadIdx.x;
+  const uint2 h = *reinterpret_cast<const uint2*>(hist + b);
+  uint32_t total;
+  const int64_t before = block_scan<16>(h.x + h.y, smem, &total);
+  if (before < k && k <= before + h.x + h.y) {
+    const bool second = before + h.x < k;
+    out[0] = b + second;
+    out[1] = before + (second ? h.x : 0u);
+    out[2] = second ? h.y : h.x;
   }
   __syncthreads();
 }
 
-// ----------------------------------------------------------------- kernels
+// ------------------------------------------------------------ group of classes
 
-__global__ void k_sample_clear(uint32_t* bitmap, int64_t nwords, uint32_t* hist,
-                               SampleState* st) {
-  const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = tid; i < nwords; i += stride) bitmap[i] = 0u;
-  for (int64_t i = tid; i < (1 << kTopBitsMax); i += stride) hist[i] = 0u;
-  if (tid == 0) {
-    st->n_pos = 0;
-    st->mode = kSelectNone;
-    st->top_digit = 0;
-    st->n_neg = 0;
-    st->k_rem = 0;
-    st->thresh = 0;
-  }
+// Keys of the sixteen classes c0 .. c0 + 15 (c0 a multiple of 16) in the words
+// of their Philox blocks: key q is that of class c0 + q - o, o = (a + c0) % 4
+// (the shard may start inside a block; classes outside are neighbours').
+__device__ __forceinline__ void keys16(uint64_t seed, int64_t a, int64_t c0, uint64_t (&keys)[20]) {
+  const int64_t g = a + c0;
+  philox4x64_10<4>((uint64_t)(g >> 2), seed, keys);
+  if (g & 3) philox4x64_10<1>((uint64_t)(g >> 2) + 4, seed, keys + 16);
 }
 
-// Marks the positives and counts them once each.  The key histogram counts
-// non-positive classes only; the key pass adds every class, so each
-// positive's digit is taken off here (unsigned counts: the sum is exact once
-// both passes are done, whatever their order inside the histogram).
-__global__ void k_mark_positives(const int64_t* labels, int64_t B, int64_t C,
-                                 int64_t a, uint64_t seed, int top_bits, uint32_t* bitmap,
-                                 uint32_t* hist, SampleState* st) {
-  const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= B) return;
-  const int64_t y = labels[n];
-  if (y < a || y >= a + C) return;
-  const int64_t c = y - a;
-  const uint32_t bit = 1u << (c & 31);
-  const uint32_t old = atomicOr(&bitmap[c >> 5], bit);
-  if (!(old & bit)) {
-    atomicAdd(&st->n_pos, 1u);
-    atomicSub(&hist[(uint32_t)(class_key(seed, a, c) >> (64 - top_bits))], 1u);
-  }
-}
-
-__global__ void k_sample_plan(SampleState* st, int64_t budget, int64_t C) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  const int64_t n_pos = st->n_pos;
-  const int64_t n_neg = budget > n_pos ? budget - n_pos : 0;
-  const int64_t pool = C - n_pos;
-  st->n_neg = n_neg;
-  if (n_neg == 0) {
-    st->mode = kSelectNone;
-    st->thresh = 0;
-    st->k_rem = 0;
-  } else if (n_neg >= pool) {
-    st->mode = kSelectAll;
-    st->thresh = ~0ull;
-    st->k_rem = INT64_MAX;
-  } else {
-    st->mode = kSelectKeys;
-    st->k_rem = n_neg;
-  }
-}
-
-// Digits of the four classes of Philox block q into `digits` and the
-// workgroup's histogram.  With the shard starting on a block boundary the
-// four digits are one 8-byte store.
-__device__ __forceinline__ void keys_block(const U64x4& w, int64_t q, int64_t a, int64_t C,
-                                           int top_bits, uint16_t* digits, uint32_t* lhist) {
-  const int64_t c0 = 4 * q - a;
-  uint32_t dg[4];
+// f(i, key) for the classes i of `take`, c0 + i, in order.
+template <typename F>
+__device__ __forceinline__ void for_taken(uint32_t take, int o, const uint64_t (&keys)[20],
+                                          F&& f) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) dg[i] = (uint32_t)(w.v[i] >> (64 - top_bits));
-  if ((a & 3) == 0 && c0 + 3 < C) {
-    *reinterpret_cast<uint2*>(digits + c0) = make_uint2(dg[0] | (dg[1] << 16), dg[2] | (dg[3] << 16));
-#pragma unroll
-    for (int i = 0; i < 4; ++i) atomicAdd(&lhist[dg[i]], 1u);
-  } else {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int64_t c = c0 + i;
-      if (c < 0 || c >= C) continue;
-      digits[c] = (uint16_t)dg[i];
-      atomicAdd(&lhist[dg[i]], 1u);
-    }
+  for (int q = 0; q < 20; ++q) {
+    if (q >= 16 && o == 0) break;
+    if (q >= o && ((take >> (q - o)) & 1u)) f(q - o, keys[q]);
   }
 }
 
-// Grid-stride over the Philox blocks of the shard (global ids 4q .. 4q + 3),
-// two independent blocks per thread and iteration; each workgroup builds one
-// histogram of its share (every class; the positives were taken off before)
-// and flushes it once.  The loop reads nothing from memory.
-__global__ void __launch_bounds__(1024) k_keys_hist(uint64_t seed, int64_t a, int64_t C,
-                                                    int top_bits, uint16_t* digits,
-                                                    uint32_t* hist, const SampleState* st) {
-  if (st->mode != kSelectKeys) return;
-  __shared__ uint32_t lhist[1 << kTopBitsMax];
-  const int nbins = 1 << top_bits;
-  for (int i = threadIdx.x; i < nbins; i += blockDim.x) lhist[i] = 0u;
+__device__ __forceinline__ uint32_t live16(int64_t c0, int64_t C) {
+  return c0 >= C ? 0u : C - c0 >= kPerThread ? 0xFFFFu : (1u << (C - c0)) - 1u;
+}
+
+// The positives among the classes [c_lo, c_lo + n) (n a multiple of 32), as a
+// bitmap in LDS.  Ends with a barrier.
+__device__ __forceinline__ void mark_positives(const int64_t* labels, int64_t B, int64_t a,
+                                               int64_t c_lo, int n, uint32_t* bits) {
+  for (int i = threadIdx.x; i < n / 32; i += blockDim.x) bits[i] = 0u;
   __syncthreads();
-  const int64_t q_hi = (a + C - 1) >> 2;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  int64_t q = (a >> 2) + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  for (; q + stride <= q_hi; q += 2 * stride) {
-    const U64x4 w0 = philox4x64_10((uint64_t)q, seed);
-    const U64x4 w1 = philox4x64_10((uint64_t)(q + stride), seed);
-    keys_block(w0, q, a, C, top_bits, digits, lhist);
-    keys_block(w1, q + stride, a, C, top_bits, digits, lhist);
+  for (int64_t k = threadIdx.x; k < B; k += blockDim.x) {
+    // Unsigned: a label before the range wraps far past its end.
+    const uint64_t c = (uint64_t)labels[k] - (uint64_t)(a + c_lo);
+    if (c < (uint64_t)n) atomicOr(&bits[c >> 5], 1u << (c & 31));
   }
-  if (q <= q_hi) keys_block(philox4x64_10((uint64_t)q, seed), q, a, C, top_bits, digits, lhist);
   __syncthreads();
-  // Flush starting at a per-workgroup offset so that workgroups finishing
-  // together hit different bins.
-  const int rot = (int)((blockIdx.x * 97u) & (uint32_t)(nbins - 1));
-  for (int i = threadIdx.x; i < nbins; i += blockDim.x) {
-    const int b = (i + rot) & (nbins - 1);
-    const uint32_t h = lhist[b];
-    if (h) atomicAdd(&hist[b], h);
+}
+
+// A thread's sixteen classes: masks of the positives, of the classes surely in
+// S and of the candidates.
+struct Masks {
+  uint32_t pos, sure, in;
+};
+
+// Those of the classes from c0 on, and their keys; `bits` is the bitmap from
+// class c0 - 16 t on.
+__device__ __forceinline__ Masks draw16(const uint32_t* bits, int t, int64_t c0, int64_t C,
+                                        int64_t a, uint64_t seed, uint32_t lo, uint32_t hi,
+                                        uint64_t (&keys)[20]) {
+  const uint32_t live = live16(c0, C);
+  uint32_t below = 0, in = 0;
+  if (live) {
+    keys16(seed, a, c0, keys);
+    const int o = (int)((a + c0) & 3);
+    for_taken(live, o, keys, [&](int i, uint64_t key) {
+      const uint32_t top = (uint32_t)(key >> 32);
+      below |= (uint32_t)(top < lo) << i;
+      in |= (uint32_t)(top >= lo && top <= hi) << i;
+    });
+  }
+  const uint32_t pos = (bits[t >> 1] >> (16 * (t & 1))) & live;
+  return Masks{pos, below | pos, in & ~pos};
+}
+
+// One workgroup per run of groups.  The candidates' keys go to the group's own
+// part of cand_key in class order; masks keeps each thread's three masks and
+// (top 16 bits) its first candidate's place.  Bound by the generator (about
+// 300 instructions per four keys, a third of them multiplications at a quarter
+// of the rate) on a large shard, by its latency on a small one: groups of 4,096
+// classes spread it over four times the CUs that groups of 16,384 do (100 K
+// classes: 6.9 against 11.6 us).
+__global__ void __launch_bounds__(kGroupThreads) k_keys(
+    const int64_t* labels, int64_t B, int64_t C, int64_t a, uint64_t seed, uint32_t lo,
+    uint32_t hi, int64_t n_groups, int run, uint64_t* masks, uint64_t* cand_key,
+    uint32_t* grp_sure, uint32_t* grp_cand) {
+  __shared__ uint32_t bits[kGroupClasses / 32 * kRunMax];
+  __shared__ uint32_t smem[kGroupThreads / 64];
+  const int64_t g0 = (int64_t)blockIdx.x * run;
+  const int n = (int)(n_groups - g0 < run ? n_groups - g0 : run);
+  const int t = threadIdx.x;
+  mark_positives(labels, B, a, g0 * kGroupClasses, n * kGroupClasses, bits);
+#pragma unroll 1
+  for (int i = 0; i < n; ++i) {
+    const int64_t g = g0 + i;
+    const int64_t c0 = g * kGroupClasses + t * kPerThread;
+    uint64_t keys[20];
+    const Masks m = draw16(bits + kGroupClasses / 32 * i, t, c0, C, a, seed, lo, hi, keys);
+    // Surely selected classes and candidates (at most 4,096 each) in one scan.
+    uint32_t total, n_pos;
+    const uint32_t pre = block_scan<kGroupThreads / 64>(
+        (uint32_t)__popc(m.sure) | ((uint32_t)__popc(m.in) << 16), smem, &total) >> 16;
+    block_scan<kGroupThreads / 64>((uint32_t)__popc(m.pos), smem, &n_pos);
+    if (t == 0) {
+      grp_sure[g] = (total & 0xFFFFu) | (n_pos << 16);
+      grp_cand[g] = total >> 16;
+    }
+    masks[g * kGroupThreads + t] = (uint64_t)m.pos | ((uint64_t)m.sure << 16) |
+                                   ((uint64_t)m.in << 32) | ((uint64_t)pre << 48);
+    uint64_t* out = cand_key + g * kGroupClasses + pre;
+    for_taken(m.in, (int)((a + c0) & 3), keys, [&](int, uint64_t key) { *out++ = key; });
   }
 }
 
-// One workgroup of 1024 threads: the top bucket holding the n_neg-th key.
-__global__ void __launch_bounds__(1024) k_select_top(const uint32_t* hist, int top_bits,
-                                                     SampleState* st) {
-  if (st->mode != kSelectKeys) return;
-  __shared__ uint32_t lh[1 << kTopBitsMax];
-  __shared__ uint64_t scan_smem[16];
-  __shared__ int64_t found[3];
-  const int nbins = 1 << top_bits;
-  const int nb = nbins < (int)blockDim.x ? (int)blockDim.x : nbins;
-  for (int i = threadIdx.x; i < nb; i += blockDim.x) lh[i] = i < nbins ? hist[i] : 0u;
-  __syncthreads();
-  find_kth_bin(lh, nb, st->k_rem, scan_smem, found);
-  if (threadIdx.x == 0) {
-    st->top_digit = (uint32_t)found[0];
-    st->k_rem -= found[1];
-  }
-}
+// ------------------------------------------------------------------ threshold
+//
+// All kernels from here on have 1,024 threads.
 
-// One workgroup per compaction group (kCompactClasses classes, kCompactPer per
-// thread).  Counts the group's classes that the top-bit digit already selects
-// (positives, and non-positives below the threshold's bucket; every class when
-// all are taken, the positives when no negative is), and writes the full keys
-// of the group's non-positive classes in that bucket to the group's own part
-// of cand_key (offsets from one workgroup scan, no atomics).  The bucket's
-// classes are added to their groups' counts once the threshold is known
-// (k_refine).
-__global__ void __launch_bounds__(kCompactThreads) k_collect(
-    const uint16_t* digits, const uint32_t* bitmap, int64_t C, uint64_t seed, int64_t a,
-    const SampleState* st, uint64_t* cand_key, uint32_t* grp_sure, uint32_t* grp_tie) {
-  __shared__ uint32_t smem[kCompactThreads / 64];
-  const uint32_t mode = st->mode;
-  const uint32_t digit = st->top_digit;
-  const int64_t c0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * kCompactPer;
-  uint32_t take = 0, base_bits = 0;
-  if (c0 < C) {
-    // The digits are read whatever the mode (the array always holds whole
-    // groups of 16), so that these loads need not wait for the state's.
-    uint32_t w[8];
-    load_digits16(digits, c0, w);
-    const uint32_t pos = (bitmap[c0 >> 5] >> (c0 & 31)) & 0xFFFFu;
-    const uint32_t live = C - c0 >= kCompactPer ? 0xFFFFu : (1u << (C - c0)) - 1u;
-    uint32_t below = 0, equal = 0;
-#pragma unroll
-    for (int i = 0; i < kCompactPer; ++i) {
-      const uint32_t dg = digit_of(w, i);
-      below |= (uint32_t)(dg < digit) << i;
-      equal |= (uint32_t)(dg == digit) << i;
-    }
-    if (mode == kSelectAll) {
-      base_bits = live;
-    } else if (mode == kSelectNone) {
-      base_bits = pos & live;
-    } else {
-      base_bits = (below | pos) & live;
-      take = equal & ~pos & live;
-    }
-  }
-  // Both counts in one scan: selected classes in the low half, candidates in
-  // the high half (each at most kCompactClasses per group, so no carry).
-  uint32_t tot;
-  const uint32_t pre = block_exclusive_scan(
-      (uint32_t)__popc(base_bits) | ((uint32_t)__popc(take) << 16), smem, &tot);
-  if (threadIdx.x == 0) {
-    grp_sure[blockIdx.x] = tot & 0xFFFFu;
-    grp_tie[blockIdx.x] = tot >> 16;
-  }
-  uint64_t* out = cand_key + (int64_t)blockIdx.x * kCompactClasses + (pre >> 16);
-  while (take) {
-    const int i = __ffs(take) - 1;
-    take &= take - 1;
-    *out++ = class_key(seed, a, c0 + i);
-  }
-}
+constexpr int kThreads = 1024;
+constexpr int kSpan = kThreads * kPerThread;   // classes of a workgroup: four groups
+constexpr int kSpanGroups = kSpan / kGroupClasses;
+constexpr int kLastKeys = 512;    // keys ranked directly
+constexpr int kListMax = 8192;    // candidates held in LDS
 
-// The refinement's workgroup and the candidates it keeps in LDS (32 KB of
-// keys; more stay in memory).  It is small enough (40 KB of LDS, two waves
-// per SIMD) to share a CU with one workgroup of the step's big kernels, so a
-// sampler running beside a step does not wait for a whole kernel to drain.
-constexpr int kRefineThreads = 512;
-constexpr int kRefineLds = 4096;
+// A class is taken if its key is below `key`, or equal to it and (in class
+// order) among the first `ties` such; `all_ties`: every such key is.
+struct Threshold {
+  uint64_t key;
+  int64_t ties;
+  bool all_ties;
+  bool all_keys;    // found over all keys: the candidates do not decide
+  __device__ bool below(uint64_t k) const { return k < key || (all_ties && k == key); }
+  __device__ bool tie(uint64_t k) const { return !all_ties && k == key; }
+};
 
-// One workgroup: resolve the remaining 64 - top_bits bits of the threshold
-// among the collected candidates, 11 bits per round.  Thread t owns groups
-// t, t + kRefineThreads, ...; the candidates are first gathered in that
-// order into LDS when they fit.
-__global__ void __launch_bounds__(kRefineThreads) k_refine(const uint64_t* cand_key, int64_t n_groups,
-                                                 int top_bits, SampleState* st,
-                                                 uint32_t* grp_sure, uint32_t* grp_tie) {
-  if (st->mode != kSelectKeys) return;
-  constexpr int kBits = 11;
-  __shared__ uint32_t lh[1 << kBits];
-  __shared__ uint64_t lkeys[kRefineLds];
-  __shared__ uint64_t scan_smem[16];
-  __shared__ int64_t found[3];
-  __shared__ uint64_t sole;
-  uint64_t mine = 0;
-  for (int64_t g = threadIdx.x; g < n_groups; g += blockDim.x) mine += grp_tie[g];
-  uint64_t total;
-  const uint64_t base = block_exclusive_scan64(mine, scan_smem, &total);
-  const bool in_lds = total <= (uint64_t)kRefineLds;
-  if (in_lds) {
-    uint64_t p = base;
-    for (int64_t g = threadIdx.x; g < n_groups; g += blockDim.x) {
-      const uint32_t cnt = grp_tie[g];
-      for (uint32_t j = 0; j < cnt; ++j) lkeys[p + j] = cand_key[g * kCompactClasses + j];
-      p += cnt;
-    }
-  }
-  __syncthreads();
-  // Calls f on every candidate key once (across the workgroup).
-  auto for_each_key = [&](auto&& f) {
-    if (in_lds) {
-      for (uint64_t i = threadIdx.x; i < total; i += blockDim.x) f(lkeys[i]);
-    } else {
-      for (int64_t g = threadIdx.x; g < n_groups; g += blockDim.x) {
-        const uint32_t cnt = grp_tie[g];
-        for (uint32_t j = 0; j < cnt; ++j) f(cand_key[g * kCompactClasses + j]);
-      }
-    }
-  };
-  uint64_t prefix = st->top_digit;
-  int known = top_bits;
-  int64_t k = st->k_rem;
-  while (known < 64) {
-    const int bits = (64 - known) < kBits ? (64 - known) : kBits;
-    const int shift = 64 - known - bits;
-    for (int i = threadIdx.x; i < (1 << kBits); i += blockDim.x) lh[i] = 0u;
+struct ResolveLds {
+  __attribute__((aligned(8))) uint32_t hist[kBins];
+  uint64_t last[kLastKeys];
+  uint32_t scan[kThreads / 64];
+  int64_t found[3];
+  Threshold th;
+  uint32_t n_last;
+};
+
+// The k-th (1-based) smallest of the keys that each(f) calls f on, once each
+// across the workgroup; only those in [from, to] count.  The range is cut into
+// bins until the one that holds the k-th key can be ranked directly, or holds
+// one key value only.
+template <typename Each>
+__device__ __forceinline__ Threshold kth_key(Each&& each, int64_t k, uint64_t from, uint64_t to,
+                                             ResolveLds& L) {
+  const int t = threadIdx.x;
+#pragma unroll 1
+  for (;;) {
+    const int width = 64 - __clzll((long long)(to - from));   // to > from
+    const int shift = width > 11 ? width - 11 : 0;
+    *reinterpret_cast<uint2*>(L.hist + 2 * t) = make_uint2(0u, 0u);
+    if (t == 0) L.n_last = 0;
     __syncthreads();
-    for_each_key([&](uint64_t key) {
-      if ((key >> (64 - known)) == prefix)
-        atomicAdd(&lh[(key >> shift) & ((1u << bits) - 1u)], 1u);
+    each([&](uint64_t key) {
+      if (key >= from && key <= to) atomicAdd(&L.hist[(key - from) >> shift], 1u);
     });
     __syncthreads();
-    find_kth_bin(lh, 1 << kBits, k, scan_smem, found);
-    prefix = (prefix << bits) | (uint64_t)found[0];
-    k -= found[1];
-    known += bits;
-    if (found[2] == 1 && known < 64) {
-      // The bin holds a single key (k is then 1): that key is the threshold.
-      for_each_key([&](uint64_t key) {
-        if ((key >> (64 - known)) == prefix) sole = key;
+    find_kth_bin(L.hist, k, L.scan, L.found);
+    from += (uint64_t)L.found[0] << shift;
+    k -= L.found[1];
+    const int64_t n = L.found[2];
+    to = from + ((1ull << shift) - 1ull);
+    if (shift == 0) return Threshold{from, k, k == n, false};
+    if (n <= kLastKeys) {
+      each([&](uint64_t key) {
+        if (key < from || key > to) return;
+        const uint32_t i = atomicAdd(&L.n_last, 1u);
+        if (i < kLastKeys) L.last[i] = key;   // n of them: what the bin counted
       });
       __syncthreads();
-      prefix = sole;
-      known = 64;
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    st->thresh = prefix;
-    st->k_rem = k;
-  }
-  // The bucket's classes join their groups' counts: below the threshold they
-  // are selected, equal to it they are ties (taken in class order).  Each
-  // thread updates only the groups it owns.
-  uint64_t p = base;
-  for (int64_t g = threadIdx.x; g < n_groups; g += blockDim.x) {
-    const uint32_t cnt = grp_tie[g];
-    uint32_t below = 0, equal = 0;
-    for (uint32_t j = 0; j < cnt; ++j) {
-      const uint64_t key = in_lds ? lkeys[p + j] : cand_key[g * kCompactClasses + j];
-      below += key < prefix;
-      equal += key == prefix;
-    }
-    p += cnt;
-    if (cnt) {
-      grp_sure[g] += below;
-      grp_tie[g] = equal;
-    }
-  }
-}
-
-// Per class of one thread: bit i of `sure` / `tie` for class c0 + i
-// (i < kCompactPer).  The threshold's top-bit digit decides every class
-// outside its bucket; a class inside compares its recomputed key.
-__device__ __forceinline__ void class_flags(const uint16_t* digits, const uint32_t* bitmap,
-                                            int64_t C, uint64_t seed, int64_t a,
-                                            const SampleState* st, int64_t c0, uint32_t* sure,
-                                            uint32_t* tie) {
-  const uint32_t mode = st->mode;
-  const uint32_t top = st->top_digit;
-  const uint64_t thresh = st->thresh;
-  uint32_t s = 0, t = 0, need = 0;
-  if (c0 >= C) {
-    *sure = 0;
-    *tie = 0;
-    return;
-  }
-  // c0 is a multiple of 16: one bitmap word holds the classes' bits.  The
-  // digits are read whatever the mode, beside the state's loads.
-  uint32_t w[8];
-  load_digits16(digits, c0, w);
-  const uint32_t pos = (bitmap[c0 >> 5] >> (c0 & 31)) & 0xFFFFu;
-  const uint32_t live = C - c0 >= kCompactPer ? 0xFFFFu : (1u << (C - c0)) - 1u;
-  uint32_t below = 0, equal = 0;
-#pragma unroll
-  for (int i = 0; i < kCompactPer; ++i) {
-    const uint32_t dg = digit_of(w, i);
-    below |= (uint32_t)(dg < top) << i;
-    equal |= (uint32_t)(dg == top) << i;
-  }
-  if (mode == kSelectAll) {
-    s = live;
-  } else if (mode == kSelectKeys) {
-    s = (below | pos) & live;
-    need = equal & ~pos & live;
-  } else {
-    s = pos & live;
-  }
-  // Classes in the threshold's bucket (rare): one key generator in a loop.
-  if (need) {
-    do {
-      const int i = __ffs(need) - 1;
-      need &= need - 1;
-      const uint64_t key = class_key(seed, a, c0 + i);
-      if (key < thresh) s |= 1u << i;
-      else if (key == thresh) t |= 1u << i;
-    } while (need);
-  }
-  *sure = s;
-  *tie = t;
-}
-
-// One workgroup of 1024 threads: per-group tie offsets, selected counts and
-// output offsets; n_active.  The groups go in tiles of four per thread
-// (independent, coalesced loads), with running totals carried across tiles.
-__global__ void __launch_bounds__(1024) k_compact_scan(const uint32_t* grp_sure,
-                                                       const uint32_t* grp_tie,
-                                                       int64_t n_groups, const SampleState* st,
-                                                       int64_t cap, uint32_t* grp_out,
-                                                       uint32_t* grp_tie_off,
-                                                       int32_t* n_active) {
-  constexpr int PER = 4;
-  __shared__ uint64_t smem[16];
-  const int64_t k_rem = st->k_rem;
-  const int64_t tile = (int64_t)blockDim.x * PER;
-  uint64_t carry_tie = 0, carry_sel = 0;
-  for (int64_t base = 0; base < n_groups; base += tile) {
-    const int64_t g0 = base + (int64_t)threadIdx.x * PER;
-    uint32_t t[PER], sr[PER];
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int64_t g = g0 + i;
-      t[i] = g < n_groups ? grp_tie[g] : 0u;
-      sr[i] = g < n_groups ? grp_sure[g] : 0u;
-    }
-    // Ties before each group.
-    uint64_t tile_tie;
-    uint64_t tb = carry_tie +
-                  block_exclusive_scan64((uint64_t)t[0] + t[1] + t[2] + t[3], smem, &tile_tie);
-    // Selected count of each group: sure + the ties whose class-order rank is below k_rem.
-    uint32_t sel[PER];
-    uint64_t tie_off[PER];
-    uint64_t local_sel = 0;
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      int64_t take = k_rem - (int64_t)tb;
-      take = take < 0 ? 0 : (take > (int64_t)t[i] ? (int64_t)t[i] : take);
-      sel[i] = sr[i] + (uint32_t)take;
-      tie_off[i] = tb;
-      local_sel += sel[i];
-      tb += t[i];
-    }
-    uint64_t tile_sel;
-    uint64_t ob = carry_sel + block_exclusive_scan64(local_sel, smem, &tile_sel);
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int64_t g = g0 + i;
-      if (g < n_groups) {
-        grp_tie_off[g] = (uint32_t)tie_off[i];
-        grp_out[g] = (uint32_t)ob;
+      if (t < (int)n) {
+        const uint64_t key = L.last[t];
+        int64_t less = 0, equal = 0;
+#pragma unroll 1
+        for (int i = 0; i < (int)n; ++i) {
+          less += L.last[i] < key;
+          equal += L.last[i] == key;
+        }
+        if (less < k && k <= less + equal) L.th = Threshold{key, k - less, k == less + equal, false};
       }
-      ob += sel[i];
+      __syncthreads();
+      return L.th;
     }
-    carry_tie += tile_tie;
-    carry_sel += tile_sel;
+    __syncthreads();   // found is read before the next pass rewrites it
   }
-  // |S| <= cap by construction; the clamp keeps every later index in bounds.
-  if (threadIdx.x == 0) *n_active = (int32_t)(carry_sel < (uint64_t)cap ? carry_sel : cap);
 }
 
-__global__ void __launch_bounds__(kCompactThreads) k_compact_write(
-    const uint16_t* digits, const uint32_t* bitmap, int64_t C, uint64_t seed, int64_t a,
-    const SampleState* st, const uint32_t* grp_out, const uint32_t* grp_tie_off, int64_t cap,
-    int32_t* active) {
-  __shared__ uint32_t smem[kCompactThreads / 64];
-  const int64_t c0 = ((int64_t)blockIdx.x * kCompactThreads + threadIdx.x) * kCompactPer;
-  const int64_t tie_off = grp_tie_off[blockIdx.x];
-  const int64_t out_off = grp_out[blockIdx.x];
-  const int64_t k_rem = st->k_rem;
-  uint32_t s, t;
-  class_flags(digits, bitmap, C, seed, a, st, c0, &s, &t);
-  // Class-order ranks: thread t owns classes kCompactPer t .. + kCompactPer - 1,
-  // so a class's rank is the block's exclusive prefix of the per-thread
-  // counts plus the bits below it in the thread.
-  uint32_t ttot;
-  const uint32_t tpre = block_exclusive_scan((uint32_t)__popc(t), smem, &ttot);
-  const int64_t tie_base = tie_off + tpre;
-  uint32_t sel = s;
+// The threshold over all keys of the shard's non-positives, recomputed.
+__device__ __attribute__((noinline)) Threshold kth_of_all(const uint64_t* masks, int64_t C,
+                                                          int64_t a, uint64_t seed, int64_t n_neg,
+                                                          ResolveLds& L) {
+  Threshold th = kth_key(
+      [&](auto&& f) {
+        for (int64_t v = threadIdx.x; v * kPerThread < C; v += kThreads) {
+          uint64_t keys[20];
+          keys16(seed, a, v * kPerThread, keys);
+          for_taken(live16(v * kPerThread, C) & ~(uint32_t)(masks[v] & 0xFFFFu), (int)(a & 3),
+                    keys, [&](int, uint64_t key) { f(key); });
+        }
+      },
+      n_neg, 0, ~0ull, L);
+  th.all_keys = true;
+  return th;
+}
+
+// From the shard's |P|, its non-positives below the window and its candidates:
+// the rank of the threshold among the candidates, or -1 when the window missed
+// it.  (With n_neg = 0 nothing is below the window either, since one that
+// starts above 0 leaves n_neg > 0: rank 0, no candidate.)
+__device__ __forceinline__ int64_t candidate_rank(int64_t budget, int64_t pos, int64_t below,
+                                                  int64_t cand, int64_t* n_neg) {
+  *n_neg = budget > pos ? budget - pos : 0;
+  const int64_t k = *n_neg - below;
+  return k < 0 || k > cand ? -1 : k;
+}
+
+// Masks of a thread's classes in S and of its ties, with the threshold over
+// all keys.
+__device__ __attribute__((noinline)) uint2 settle_all(uint32_t pos, int64_t c0, int64_t C,
+                                                      int64_t a, uint64_t seed, Threshold th) {
+  const uint32_t take = live16(c0, C) & ~pos;
+  uint32_t sel = pos, tie = 0;
+  if (take) {
+    uint64_t keys[20];
+    keys16(seed, a, c0, keys);
+    for_taken(take, (int)((a + c0) & 3), keys, [&](int i, uint64_t key) {
+      sel |= (uint32_t)th.below(key) << i;
+      tie |= (uint32_t)th.tie(key) << i;
+    });
+  }
+  return make_uint2(sel, tie);
+}
+
+// The same from the thread's packed masks: of its candidates, whose keys start
+// at list, those that the threshold takes join the sure ones; no candidate
+// with k = 0, and all keys decide with k < 0.
+__device__ __forceinline__ uint2 settle(uint64_t m, const uint64_t* list, int64_t k,
+                                        const Threshold& th, int64_t c0, int64_t C, int64_t a,
+                                        uint64_t seed) {
+  if (k < 0) return settle_all((uint32_t)(m & 0xFFFFu), c0, C, a, seed, th);
+  uint32_t sel = (uint32_t)(m >> 16) & 0xFFFFu, tie = 0;
+  if (k > 0) {
+    const uint64_t* next = list + (m >> 48);
+    for (uint32_t rest = (uint32_t)(m >> 32) & 0xFFFFu; rest; rest &= rest - 1) {
+      const uint64_t key = *next++;
+      if (th.below(key)) sel |= rest & (0u - rest);
+      if (th.tie(key)) tie |= rest & (0u - rest);
+    }
+  }
+  return make_uint2(sel, tie);
+}
+
+// -------------------------------------------------------------------- output
+
+// A workgroup's span of classes in S, sixteen per thread from c0 on: `st.x` for
+// sure and, of `st.y`, the first that th.ties leaves after `tie_before`.  The
+// ids go to active[out ..), and where[t] keeps the thread's mask in the low
+// half, its first place relative to the span's in the high half.
+__device__ __forceinline__ void write_span(uint2 st, const Threshold& th, int64_t out,
+                                           int64_t tie_before, int64_t c0, int64_t cap,
+                                           int32_t* active, uint32_t* smem, uint32_t* where) {
+  uint32_t sel = st.x, total;
+  if (!th.all_ties && th.ties) {
+    int64_t before = tie_before + block_scan<16>((uint32_t)__popc(st.y), smem, &total);
+    for (uint32_t rest = st.y; rest; rest &= rest - 1)
+      if (before++ < th.ties) sel |= rest & (0u - rest);
+  }
+  const uint32_t pre = block_scan<16>((uint32_t)__popc(sel), smem, &total);
+  where[threadIdx.x] = sel | (pre << 16);
+  int64_t o = out + pre;
+  for (uint32_t rest = sel; rest; rest &= rest - 1, ++o)
+    if (o < cap) active[o] = (int32_t)(c0 + __ffs(rest) - 1);
+}
+
+// Places of the labels in n spans of classes from class c_lo on, which start at
+// out[0 .. n) in S; the first workgroup also marks the labels outside the
+// shard.  Every in-shard label is a positive, which S always holds; one that
+// it did not hold would be mapped to -1 (unowned), never to another class's
+// place or past |S|.
+__device__ __forceinline__ void map_labels(const int64_t* labels, int64_t B, int64_t C, int64_t a,
+                                           int64_t c_lo, int n, const uint32_t* out,
+                                           const uint32_t* where, int64_t cap,
+                                           int32_t* labels_mapped) {
+  for (int64_t k = threadIdx.x; k < B; k += kThreads) {
+    const uint64_t y = (uint64_t)labels[k] - (uint64_t)a;
+    if (y >= (uint64_t)C) {
+      if (c_lo == 0) labels_mapped[k] = -1;
+      continue;
+    }
+    const uint64_t c = y - (uint64_t)c_lo;
+    if (c >= (uint64_t)n * kSpan) continue;
+    const uint32_t p = where[c / kPerThread];
+    const int i = (int)(c % kPerThread);
+    const int64_t o = (int64_t)out[c / kSpan] + (p >> 16) + __popc(p & ((1u << i) - 1u));
+    labels_mapped[k] = ((p >> i) & 1u) && o < cap ? (int32_t)o : -1;
+  }
+}
+
+// Of `tie` ties, those taken when `before` precede them.
+__device__ __forceinline__ uint32_t taken(const Threshold& th, int64_t before, uint32_t tie) {
+  const int64_t left = th.ties - before;
+  return left <= 0 ? 0u : left < (int64_t)tie ? (uint32_t)left : tie;
+}
+
+// |S| <= cap by construction; the clamp keeps every later index in bounds.
+__device__ __forceinline__ int32_t clamp_count(uint64_t n, int64_t cap) {
+  return (int32_t)(n < (uint64_t)cap ? n : (uint64_t)cap);
+}
+
+// A shard of at most one span: everything in one workgroup.
+__global__ void __launch_bounds__(kThreads) k_sample_one(
+    const int64_t* labels, int64_t B, int64_t C, int64_t a, uint64_t seed, int64_t budget,
+    uint32_t lo, uint32_t hi, int64_t cap, uint64_t* masks, int32_t* active, int32_t* n_active,
+    int32_t* labels_mapped) {
+  __shared__ ResolveLds L;
+  __shared__ uint32_t bits[kSpan / 32], where[kThreads];
+  __shared__ uint64_t list[kSpan];
+  __shared__ uint32_t out;
+  const int t = threadIdx.x;
+  const int64_t c0 = t * kPerThread;
+  mark_positives(labels, B, a, 0, kSpan, bits);
+  uint64_t m;
+  uint32_t total, n_pos;
+  {
+    uint64_t keys[20];
+    const Masks d = draw16(bits, t, c0, C, a, seed, lo, hi, keys);
+    const uint32_t pre = block_scan<16>((uint32_t)__popc(d.sure) | ((uint32_t)__popc(d.in) << 16),
+                                        L.scan, &total) >> 16;
+    block_scan<16>((uint32_t)__popc(d.pos), L.scan, &n_pos);
+    uint64_t* next = list + pre;
+    for_taken(d.in, (int)(a & 3), keys, [&](int, uint64_t key) { *next++ = key; });
+    m = (uint64_t)d.pos | ((uint64_t)d.sure << 16) | ((uint64_t)d.in << 32) | ((uint64_t)pre << 48);
+  }
+  int64_t n_neg;
+  const int64_t k = candidate_rank(budget, n_pos, (int64_t)(total & 0xFFFFu) - n_pos, total >> 16,
+                                   &n_neg);
+  Threshold th{0, 0, false, false};
+  if (k > 0) {   // kth_key's first barrier completes the list
+    th = kth_key(
+        [&](auto&& f) {
+          for (uint32_t i = t; i < total >> 16; i += kThreads) f(list[i]);
+        },
+        k, (uint64_t)lo << 32, ((uint64_t)hi << 32) | 0xFFFFFFFFu, L);
+  } else if (k < 0) {
+    masks[t] = m;
+    __syncthreads();
+    th = kth_of_all(masks, C, a, seed, n_neg, L);
+  }
+  if (t == 0) {
+    out = 0;
+    *n_active = clamp_count((uint64_t)n_pos + (uint64_t)n_neg, cap);
+  }
+  write_span(settle(m, list, k, th, c0, C, a, seed), th, 0, 0, c0, cap, active, L.scan, where);
+  __syncthreads();
+  map_labels(labels, B, C, a, 0, 1, &out, where, cap, labels_mapped);
+}
+
+// Calls f(group, i, key) on candidate i of the groups, once across the
+// workgroup, 1 << lane_bits threads to a group so that they read its list in
+// one piece (few lanes per group read short pieces of many lists at a time, a
+// cache line each), eight groups' loads in flight per thread.  count(g) is the
+// group's number of candidates.
+template <typename Count, typename F>
+__device__ __forceinline__ void for_candidates(const uint64_t* cand_key, int64_t n_groups,
+                                               int lane_bits, Count&& count, F&& f) {
+  constexpr int U = 8;
+  const uint32_t lanes = 1u << lane_bits, sub = threadIdx.x & (lanes - 1);
+  const int64_t step = kThreads >> lane_bits;
+#pragma unroll 1
+  for (int64_t g0 = threadIdx.x >> lane_bits; g0 < n_groups; g0 += U * step) {
+    uint32_t n[U];
+    uint64_t v[U];
 #pragma unroll
-  for (int i = 0; i < kCompactPer; ++i)
-    if (((t >> i) & 1u) && tie_base + __popc(t & ((1u << i) - 1u)) < k_rem) sel |= 1u << i;
-  uint32_t stot;
-  const uint32_t spre = block_exclusive_scan((uint32_t)__popc(sel), smem, &stot);
-  const int64_t out_base = out_off + spre;
-  uint32_t rest = sel;
-  while (rest) {
-    const int i = __ffs(rest) - 1;
-    rest &= rest - 1;
-    const int64_t o = out_base + __popc(sel & ((1u << i) - 1u));
-    if (o < cap) active[o] = (int32_t)(c0 + i);
+    for (int u = 0; u < U; ++u) n[u] = g0 + u * step < n_groups ? count(g0 + u * step) : 0u;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      v[u] = sub < n[u] ? cand_key[(g0 + u * step) * kGroupClasses + sub] : 0;
+    bool more = false;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (sub < n[u]) f(g0 + u * step, sub, v[u]);
+      more |= sub + lanes < n[u];
+    }
+    if (more) {   // longer lists than expected
+#pragma unroll 1
+      for (int64_t g = g0; g < n_groups && g < g0 + U * step; g += step)
+        for (uint32_t i = sub + lanes; i < count(g); i += lanes)
+          f(g, i, cand_key[g * kGroupClasses + i]);
+    }
   }
 }
 
-// One wave per batch row.  S is written group by group, so a class of
-// compaction group g can only sit in [grp_out[g], grp_out[g + 1]) (clamped to
-// |S|).  The wave finds the first index f there whose id is >= the label
-// (searchsorted): [lo, hi) is the part not yet decided (ids before lo are
-// < the label, ids from hi on are >=); 64 probes per round shrink it to under
-// 64 entries (one round for a group's at most 4,096), and one read of those
-// plus index hi gives f and the id found there.
-__global__ void __launch_bounds__(256) k_remap(const int64_t* labels, int64_t B, int64_t C,
-                                               int64_t a, const int32_t* active,
-                                               const int32_t* n_active, const uint32_t* grp_out,
-                                               int64_t n_groups, int32_t* labels_mapped) {
-  const int64_t n = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = lane_id();
-  if (n >= B) return;   // wave-uniform
-  const int64_t y = labels[n];
-  if (y < a || y >= a + C) {
-    if (lane == 0) labels_mapped[n] = -1;
-    return;
+// At most kMergeGroups groups: each workgroup gathers all candidates into LDS
+// (1 << lane_bits threads per group), resolves the threshold, counts all
+// groups (1 << count_bits lanes of a wave each), and writes its own span.
+__global__ void __launch_bounds__(kThreads) k_resolve_write(
+    SampleWs w, const int64_t* labels, int64_t B, int64_t C, int64_t a, uint64_t seed,
+    int n_groups, int lane_bits, int count_bits, int64_t budget, uint32_t lo, uint32_t hi, int64_t cap,
+    int32_t* active, int32_t* n_active, int32_t* labels_mapped) {
+  __shared__ ResolveLds L;
+  __shared__ uint64_t list[kListMax];
+  __shared__ uint32_t where[kThreads];
+  __shared__ uint32_t start[kMergeGroups + 1];   // of each group's candidates in the list
+  __shared__ uint32_t cnt[2][kMergeGroups];
+  __shared__ uint32_t out, tie_before;
+  const int t = threadIdx.x;
+  const int64_t c0 = ((int64_t)blockIdx.x * kThreads + t) * kPerThread;
+  const int g_own = blockIdx.x * kSpanGroups;
+  const bool own = c0 < (int64_t)n_groups * kGroupClasses;
+  const uint64_t m = own ? w.masks[c0 / kPerThread] : 0;
+  const uint32_t sure = t < n_groups ? w.grp_sure[t] : 0u;
+  const uint32_t n_cand = t < n_groups ? w.grp_cand[t] : 0u;
+  uint32_t pos, below, cand;
+  block_scan<16>(sure >> 16, L.scan, &pos);
+  block_scan<16>((sure & 0xFFFFu) - (sure >> 16), L.scan, &below);
+  const uint32_t first = block_scan<16>(n_cand, L.scan, &cand);
+  if (t < n_groups) start[t] = first;
+  if (t == 0) start[n_groups] = cand;
+  __syncthreads();
+  int64_t n_neg;
+  const int64_t k = candidate_rank(budget, pos, below, cand, &n_neg);
+  const bool fits = cand <= (uint32_t)kListMax;
+  auto from_memory = [&](auto&& f) {
+    for_candidates(w.cand_key, n_groups, lane_bits,
+                   [&](int64_t g) { return start[g + 1] - start[g]; }, f);
+  };
+  Threshold th{0, 0, false, false};
+  if (k > 0) {
+    if (fits)
+      from_memory([&](int64_t g, uint32_t i, uint64_t key) { list[start[g] + i] = key; });
+    // kth_key's first barrier completes the list.
+    th = kth_key(
+        [&](auto&& f) {
+          if (fits) {
+            for (uint32_t i = t; i < cand; i += kThreads) f(list[i]);
+          } else {
+            from_memory([&](int64_t, uint32_t, uint64_t key) { f(key); });
+          }
+        },
+        k, (uint64_t)lo << 32, ((uint64_t)hi << 32) | 0xFFFFFFFFu, L);
+  } else if (k < 0) {
+    th = kth_of_all(w.masks, C, a, seed, n_neg, L);
   }
-  const int32_t c = (int32_t)(y - a);
-  const int64_t k = *n_active;
-  const int64_t g = c / kCompactClasses;
-  const int64_t g_lo = grp_out[g];
-  const int64_t g_hi = g + 1 < n_groups ? (int64_t)grp_out[g + 1] : k;
-  const int64_t end = g_hi < k ? g_hi : k;
-  int64_t lo = g_lo < end ? g_lo : end;
-  int64_t hi = end;
-  while (hi - lo > 63) {
-    const int64_t len = hi - lo;
-    const int64_t p = lo + (len * lane) / 64;   // strictly increasing in [lo, hi), p_0 = lo
-    const int nl = __popcll(__ballot(active[p] < c));   // sorted: true on lanes 0 .. nl - 1
-    const int64_t p_last = __shfl(p, nl > 0 ? nl - 1 : 0, 64);
-    const int64_t p_next = __shfl(p, nl < 64 ? nl : 63, 64);
-    if (nl == 0) {
-      hi = lo;
-    } else {
-      lo = p_last + 1;
-      if (nl < 64) hi = p_next;
+
+  const int lanes = 1 << count_bits, sub = t & (lanes - 1);
+  // Each group's classes in S and its ties, summed over its lanes.
+#pragma unroll 1
+  for (int g = t >> count_bits; g < n_groups; g += kThreads >> count_bits) {
+    uint32_t s = 0, e = 0;
+    if (k > 0) {
+      const uint64_t* src = fits ? list + start[g] : w.cand_key + (int64_t)g * kGroupClasses;
+      for (uint32_t i = sub; i < start[g + 1] - start[g]; i += lanes) {
+        s += th.below(src[i]);
+        e += th.tie(src[i]);
+      }
+    } else if (k < 0) {
+      for (int v = sub; v < kGroupThreads; v += lanes) {
+        const int64_t at = (int64_t)g * kGroupThreads + v;
+        const uint2 st = settle_all((uint32_t)(w.masks[at] & 0xFFFFu), at * kPerThread, C, a,
+                                    seed, th);
+        s += __popc(st.x);
+        e += __popc(st.y);
+      }
+    }
+    for (int off = 1; off < lanes; off <<= 1) {
+      s += __shfl_xor(s, off, 64);
+      e += __shfl_xor(e, off, 64);
+    }
+    if (sub == 0) {
+      cnt[0][g] = s;
+      cnt[1][g] = e;
     }
   }
-  const int64_t m = (hi < end ? hi + 1 : end) - lo;   // <= 64
-  const int32_t v = lane < m ? active[lo + lane] : INT32_MAX;
-  const int f = __popcll(__ballot(lane < m && v < c));
-  const int32_t vf = __shfl(v, f < 64 ? f : 63, 64);
-  // Every in-shard label is a positive, which the sampler always keeps; a
-  // label not found in S is nevertheless mapped to -1 (unowned), never to a
-  // position whose id is another class or lies past |S|.
-  if (lane == 0) labels_mapped[n] = (f < m && vf == c) ? (int32_t)(lo + f) : -1;
+  __syncthreads();
+  uint32_t s = t < n_groups ? cnt[0][t] + (k >= 0 ? sure & 0xFFFFu : 0u) : 0u;
+  uint32_t tb = 0, total;
+  if (!th.all_ties && th.ties) {
+    const uint32_t e = t < n_groups ? cnt[1][t] : 0u;
+    tb = block_scan<16>(e, L.scan, &total);
+    s += taken(th, tb, e);
+  }
+  const uint32_t ob = block_scan<16>(s, L.scan, &total);
+  if (t == g_own) {
+    out = ob;
+    tie_before = tb;
+  }
+  if (g_own == 0 && t == 0) *n_active = clamp_count(total, cap);
+  __syncthreads();
+  const uint64_t* keys = w.cand_key + c0 / kGroupClasses * kGroupClasses;
+  const uint2 st = own ? settle(m, keys, k, th, c0, C, a, seed) : make_uint2(0u, 0u);
+  write_span(st, th, out, tie_before, c0, cap, active, L.scan, where);
+  __syncthreads();
+  map_labels(labels, B, C, a, (int64_t)blockIdx.x * kSpan, 1, &out, where, cap, labels_mapped);
+}
+
+// More groups: the threshold, then the groups' counts (kept in grp_out and
+// grp_tie_off), turned into their offsets in tiles of one group per thread
+// with running totals.  One workgroup, 1 << lane_bits <= 64 lanes per group.
+__global__ void __launch_bounds__(kThreads) k_resolve(SampleWs w, int64_t n_groups, int lane_bits,
+                                                      int64_t C, int64_t a, uint64_t seed,
+                                                      int64_t budget, uint32_t lo, uint32_t hi,
+                                                      int64_t cap, int32_t* n_active) {
+  __shared__ ResolveLds L;
+  const int t = threadIdx.x;
+  const int lanes = 1 << lane_bits, sub = t & (lanes - 1);
+  uint32_t pos = 0, below = 0, cand = 0, sum;
+  for (int64_t g = t; g < n_groups; g += kThreads) {
+    const uint32_t s = w.grp_sure[g];
+    pos += s >> 16;
+    below += (s & 0xFFFFu) - (s >> 16);
+    cand += w.grp_cand[g];
+  }
+  block_scan<16>(pos, L.scan, &sum);
+  pos = sum;
+  block_scan<16>(below, L.scan, &sum);
+  below = sum;
+  block_scan<16>(cand, L.scan, &sum);
+  cand = sum;
+  int64_t n_neg;
+  const int64_t k = candidate_rank(budget, pos, below, cand, &n_neg);
+  Threshold th{0, 0, false, false};
+  if (k > 0) {
+    th = kth_key(
+        [&](auto&& f) {
+          for_candidates(w.cand_key, n_groups, lane_bits, [&](int64_t g) { return w.grp_cand[g]; },
+                         [&](int64_t, uint32_t, uint64_t key) { f(key); });
+        },
+        k, (uint64_t)lo << 32, ((uint64_t)hi << 32) | 0xFFFFFFFFu, L);
+  } else if (k < 0) {
+    th = kth_of_all(w.masks, C, a, seed, n_neg, L);
+  }
+#pragma unroll 1
+  for (int64_t g = t >> lane_bits; g < n_groups; g += kThreads >> lane_bits) {
+    uint32_t s = 0, e = 0;
+    if (k > 0) {
+      const uint32_t n = w.grp_cand[g];
+      for (uint32_t i = sub; i < n; i += lanes) {
+        const uint64_t key = w.cand_key[g * kGroupClasses + i];
+        s += th.below(key);
+        e += th.tie(key);
+      }
+    } else if (k < 0) {
+      for (int v = sub; v < kGroupThreads; v += lanes) {
+        const int64_t at = g * kGroupThreads + v;
+        const uint2 st = settle_all((uint32_t)(w.masks[at] & 0xFFFFu), at * kPerThread, C, a,
+                                    seed, th);
+        s += __popc(st.x);
+        e += __popc(st.y);
+      }
+    }
+    for (int off = 1; off < lanes; off <<= 1) {
+      s += __shfl_xor(s, off, 64);
+      e += __shfl_xor(e, off, 64);
+    }
+    if (sub == 0) {
+      w.grp_out[g] = s + (k >= 0 ? w.grp_sure[g] & 0xFFFFu : 0u);
+      w.grp_tie_off[g] = e;
+    }
+  }
+  __syncthreads();
+  uint64_t all_tie = 0, all_sel = 0;
+#pragma unroll 1
+  for (int64_t base = 0; base < n_groups; base += kThreads) {
+    const int64_t g = base + t;
+    const uint32_t s = g < n_groups ? w.grp_out[g] : 0u;
+    const uint32_t e = g < n_groups ? w.grp_tie_off[g] : 0u;
+    const uint64_t tb = all_tie + block_scan<16>(e, L.scan, &sum);
+    all_tie += sum;
+    const uint64_t ob =
+        all_sel + block_scan<16>(s + taken(th, (int64_t)tb, e), L.scan, &sum);
+    all_sel += sum;
+    if (g < n_groups) {
+      w.grp_out[g] = (uint32_t)ob;
+      w.grp_tie_off[g] = (uint32_t)tb;
+    }
+  }
+  if (t == 0) {
+    *w.state = SampleState{th.key, th.ties, k, th.all_ties, th.all_keys};
+    *n_active = clamp_count(all_sel, cap);
+  }
+}
+
+// One workgroup per run of spans.
+__global__ void __launch_bounds__(kThreads) k_write(
+    SampleWs w, const int64_t* labels, int64_t B, int64_t C, int64_t a, uint64_t seed,
+    int64_t n_groups, int run, int64_t cap, int32_t* active, int32_t* labels_mapped) {
+  __shared__ uint32_t smem[kThreads / 64];
+  __shared__ uint32_t where[kThreads * kSpanRunMax];
+  __shared__ uint32_t out[kSpanRunMax];
+  const int t = threadIdx.x;
+  const int64_t s0 = (int64_t)blockIdx.x * run;
+  const int64_t n_spans = ceil_div(n_groups, (int64_t)kSpanGroups);
+  const int n = (int)(n_spans - s0 < run ? n_spans - s0 : run);
+  const SampleState z = *w.state;
+  const Threshold th{z.thresh, z.ties, z.all_ties, z.all_keys};
+  if (t < n) out[t] = w.grp_out[(s0 + t) * kSpanGroups];
+#pragma unroll 1
+  for (int i = 0; i < n; ++i) {
+    const int64_t c0 = ((s0 + i) * kThreads + t) * kPerThread;
+    const int64_t g = c0 / kGroupClasses;
+    uint2 st = make_uint2(0u, 0u);
+    if (g < n_groups)
+      st = settle(w.masks[c0 / kPerThread], w.cand_key + g * kGroupClasses, z.rank, th, c0, C, a,
+                  seed);
+    write_span(st, th, w.grp_out[(s0 + i) * kSpanGroups], w.grp_tie_off[(s0 + i) * kSpanGroups],
+               c0, cap, active, smem, where + kThreads * i);
+  }
+  __syncthreads();
+  map_labels(labels, B, C, a, s0 * kSpan, n, out, where, cap, labels_mapped);
+}
+
+// A budget of the whole shard: S is every class, whatever the keys.
+__global__ void __launch_bounds__(256) k_take_all(const int64_t* labels, int64_t B, int64_t C,
+                                                  int64_t a, int32_t* active, int32_t* n_active,
+                                                  int32_t* labels_mapped) {
+  const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  if (tid == 0) *n_active = (int32_t)C;
+  for (int64_t i = tid; i < C; i += stride) active[i] = (int32_t)i;
+  for (int64_t i = tid; i < B; i += stride) {
+    const uint64_t y = (uint64_t)labels[i] - (uint64_t)a;
+    labels_mapped[i] = y < (uint64_t)C ? (int32_t)y : -1;
+  }
 }
 
 }  // namespace
 
+// The window of the keys' top 32 bits that holds the threshold.  The number of
+// keys below t is binomial with mean F = t C; the threshold lies where the
+// non-positives among them are b - |P|, that is where F is between b - |P|
+// (no positive below) and b (all of them), |P| <= min(B, C), give or take the
+// deviation of F: five of its standard deviations (at F = b, where it is no
+// smaller) and, for small budgets, four classes more.
+void sample_window(int64_t B, int64_t C, int64_t budget, uint32_t* lo, uint32_t* hi) {
+  const double b = (double)budget, c = (double)C, two32 = 4294967296.0;
+  const double slack = 5.0 * sqrt(b * (1.0 - b / c)) + 4.0;
+  const double from = (b - (double)(B < C ? B : C) - slack) / c * two32;
+  const double to = (b + slack) / c * two32;
+  *lo = from <= 0.0 ? 0u : (uint32_t)from;
+  *hi = to >= two32 - 1.0 ? 0xFFFFFFFFu : (uint32_t)ceil(to);
+}
+
 hipError_t launch_sample(const int64_t* labels, int64_t B, int64_t C, int64_t a,
-                         int64_t budget, uint64_t seed, int top_bits, int64_t n_groups,
-                         const SampleWs& w, int32_t* active, int64_t cap, int32_t* n_active,
-                         int32_t* labels_mapped, hipStream_t stream) {
+                         int64_t budget, uint64_t seed, int64_t n_groups, const SampleWs& w,
+                         int32_t* active, int64_t cap, int32_t* n_active, int32_t* labels_mapped,
+                         hipStream_t stream) {
   timing_start(0, stream);
-  const int64_t nwords = ceil_div(C, 32);
-  const int clear_blocks = (int)(ceil_div(nwords, 256) < 4096 ? ceil_div(nwords, 256) : 4096);
-  hipLaunchKernelGGL(k_sample_clear, dim3(clear_blocks > 0 ? clear_blocks : 1), dim3(256), 0,
-                     stream, w.bitmap, nwords, w.hist, w.state);
-  hipLaunchKernelGGL(k_mark_positives, dim3((unsigned)ceil_div(B, 256)), dim3(256), 0, stream,
-                     labels, B, C, a, seed, top_bits, w.bitmap, w.hist, w.state);
-  hipLaunchKernelGGL(k_sample_plan, dim3(1), dim3(64), 0, stream, w.state, budget, C);
-  const int64_t n_blocks_philox = ((a + C - 1) >> 2) - (a >> 2) + 1;
-  // One workgroup of 1024 threads per CU at most: each flushes a histogram.
-  const int64_t hist_wgs = ceil_div(n_blocks_philox, 1024);
-  hipLaunchKernelGGL(k_keys_hist, dim3((unsigned)(hist_wgs < 256 ? hist_wgs : 256)), dim3(1024), 0,
-                     stream, seed, a, C, top_bits, w.digits, w.hist, w.state);
-  hipLaunchKernelGGL(k_select_top, dim3(1), dim3(1024), 0, stream, w.hist, top_bits, w.state);
-  hipLaunchKernelGGL(k_collect, dim3((unsigned)n_groups), dim3(kCompactThreads), 0, stream,
-                     w.digits, w.bitmap, C, seed, a, w.state, w.cand_key, w.grp_sure, w.grp_tie);
-  hipLaunchKernelGGL(k_refine, dim3(1), dim3(kRefineThreads), 0, stream, w.cand_key, n_groups, top_bits,
-                     w.state, w.grp_sure, w.grp_tie);
-  hipLaunchKernelGGL(k_compact_scan, dim3(1), dim3(1024), 0, stream, w.grp_sure, w.grp_tie,
-                     n_groups, w.state, cap, w.grp_out, w.grp_tie_off, n_active);
-  hipLaunchKernelGGL(k_compact_write, dim3((unsigned)n_groups), dim3(kCompactThreads), 0, stream,
-                     w.digits, w.bitmap, C, seed, a, w.state, w.grp_out, w.grp_tie_off, cap,
-                     active);
-  hipLaunchKernelGGL(k_remap, dim3((unsigned)ceil_div(B, 4)), dim3(256), 0, stream, labels, B,
-                     C, a, active, n_active, w.grp_out, n_groups, labels_mapped);
+  if (budget >= C) {
+    const int64_t blocks = ceil_div(C > B ? C : B, 1024);
+    hipLaunchKernelGGL(k_take_all, dim3((unsigned)(blocks < 2048 ? blocks : 2048)), dim3(256), 0,
+                       stream, labels, B, C, a, active, n_active, labels_mapped);
+    timing_stop(0, stream);
+    return hipGetLastError();
+  }
+  uint32_t lo, hi;
+  sample_window(B, C, budget, &lo, &hi);
+  if (C <= kSpan) {
+    hipLaunchKernelGGL(k_sample_one, dim3(1), dim3(kThreads), 0, stream, labels, B, C, a, seed,
+                       budget, lo, hi, cap, w.masks, active, n_active, labels_mapped);
+    timing_stop(0, stream);
+    return hipGetLastError();
+  }
+  // Each workgroup reads all labels: on very large shards it takes a run of
+  // several groups, so that those reads stay below the generator's time.
+  const int n = (int)n_groups;
+  const int run = n / 2048 < 1 ? 1 : n / 2048 > kRunMax ? kRunMax : n / 2048;
+  hipLaunchKernelGGL(k_keys, dim3((unsigned)ceil_div(n, run)), dim3(kGroupThreads), 0, stream,
+                     labels, B, C, a, seed, lo, hi, n_groups, run, w.masks, w.cand_key, w.grp_sure,
+                     w.grp_cand);
+  // Threads that read a group's candidates: about as many as it has; at most a
+  // wave where their counts are summed by lane moves.
+  const double per_group = ((double)hi - (double)lo) / 4294967296.0 * kGroupClasses;
+  int lane_bits = 0;
+  while (lane_bits < 10 && (double)(1 << lane_bits) < per_group) ++lane_bits;
+  const int count_bits = lane_bits < 6 ? lane_bits : 6;
+  const int n_spans = (int)ceil_div(n, kSpanGroups);
+  if (n <= kMergeGroups) {
+    hipLaunchKernelGGL(k_resolve_write, dim3((unsigned)n_spans), dim3(kThreads), 0, stream, w,
+                       labels, B, C, a, seed, n, lane_bits, count_bits, budget, lo, hi, cap, active,
+                       n_active, labels_mapped);
+  } else {
+    const int span_run = n_spans / 512 < 1             ? 1
+                         : n_spans / 512 > kSpanRunMax ? kSpanRunMax
+                                                       : n_spans / 512;
+    hipLaunchKernelGGL(k_resolve, dim3(1), dim3(kThreads), 0, stream, w, n_groups, count_bits, C,
+                       a, seed, budget, lo, hi, cap, n_active);
+    hipLaunchKernelGGL(k_write, dim3((unsigned)ceil_div(n_spans, span_run)), dim3(kThreads), 0,
+                       stream, w, labels, B, C, a, seed, n_groups, span_run, cap, active,
+                       labels_mapped);
+  }
   timing_stop(0, stream);
   return hipGetLastError();
 }

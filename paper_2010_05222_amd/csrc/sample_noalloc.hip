@@ -1,6 +1,6 @@
 // pfc_sample_noalloc: pfc_sample for callers that cannot allocate device
-// memory.  The sampler's scratch (positive bitmap, key-digit histogram and
-// digits, threshold candidates and their keys, compaction counts) lives in a
+// memory.  The sampler's scratch (class masks, the candidates' keys, group
+// counts) lives in a
 // file-scope device array instead of a caller workspace.  Declaration and
 // contract in include/pfc.h.
 #include <math.h>
@@ -14,10 +14,9 @@ namespace pfc {
 namespace {
 
 // Largest sampler prefix of the workspace layout (ws_layout) for
-// C <= PFC_NOALLOC_MAX_CLASSES, rounded up: bitmap C/8 + histogram 16 KiB +
-// state + digits 2C + candidate keys 8C + four group arrays (20.3 MiB at
-// C = 2^21).
-constexpr size_t kScratchBytes = (size_t)21 << 20;
+// C <= PFC_NOALLOC_MAX_CLASSES, rounded up: state + masks C/2 + candidate keys
+// 8C + four group arrays (17.01 MiB at C = 2^21).
+constexpr size_t kScratchBytes = (size_t)18 << 20;
 
 // One copy per device; every call on a device shares it.
 __device__ __align__(256) unsigned char scratch[kScratchBytes];
@@ -60,7 +59,7 @@ extern "C" int pfc_sample_noalloc(const int64_t* labels, int64_t B, int64_t C,
   void* base = scratch_ptr(dev);
   if (!base) return PFC_ERR_HIP;
   (void)hipGetLastError();
-  const hipError_t e = launch_sample(labels, B, C, class_offset, budget_of(r, C), seed, L.top_bits,
+  const hipError_t e = launch_sample(labels, B, C, class_offset, budget_of(r, C), seed,
                                      L.n_groups, sample_ws(base, L), active, active_cap, n_active,
                                      labels_mapped, (hipStream_t)stream);
   return e == hipSuccess ? PFC_OK : PFC_ERR_HIP;

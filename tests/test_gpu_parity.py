@@ -247,6 +247,50 @@ def test_sampler_offsets_and_modes(dev, B, C, a, r, seed):
     assert np.array_equal(shard.labels_mapped.cpu().numpy(), mapped_ref)
 
 
+def _sampler_case(dev, labels, C, a, r, seed):
+    print(f"\nsampler B={len(labels)} C={C} a={a} r={r} seed={seed}", flush=True)
+    shard = _shard(len(labels), 128, C, r, "bf16", "arcface", 0.5, class_offset=a, dev=dev)
+    shard.sample(torch.from_numpy(labels.astype(np.int64)).to(dev), seed)
+    torch.cuda.synchronize()
+    active_ref, mapped_ref, info = O.sample_active(labels, C, a, r, seed)
+    K = int(shard.n_active.item())
+    assert K == len(active_ref) == max(O.budget(r, C), info["n_pos"])
+    assert np.array_equal(shard.active[:K].cpu().numpy(), active_ref)
+    assert np.array_equal(shard.labels_mapped.cpu().numpy(), mapped_ref)
+    return info
+
+
+@pytest.mark.parametrize("C,a,r", [
+    (4096, 0, 0.5), (4097, 1, 0.5),                  # one group, one class past it
+    (1 << 20, 0, 0.1), ((1 << 20) + 1, 3, 0.1),      # one group per workgroup, two
+    (1 << 21, 0, 0.01), ((1 << 21) + 1, 2, 0.01),    # threshold found per workgroup, once
+    (3000, 0, 2999 / 3000),                          # all but one
+])
+@pytest.mark.parametrize("B", [1, 8192])
+def test_sampler_group_edges(dev, B, C, a, r):
+    rng = np.random.default_rng(63)
+    labels = rng.integers(a, a + C, size=B)
+    labels[1::3] = np.iinfo(np.int64).min + 1   # no class of any shard
+    _sampler_case(dev, labels, C, a, r, 64)
+
+
+@pytest.mark.parametrize("C,b,seed", [
+    (1000, 1, 4572), (9001, 1, 60), (1100003, 1, 2488), (2200003, 1, 4342),
+    (100, 99, 10856), (2200003, 2200002, 413),
+])
+def test_sampler_threshold_outside_window(dev, C, b, seed):
+    """Seeds whose threshold lies outside the window in which the sampler
+    expects it (five standard deviations and four classes around the budget):
+    it is then found over all keys."""
+    from oracle import philox
+    labels = np.array([C + 5])                       # unowned: b negatives
+    slack = 5.0 * np.sqrt(b * (1 - b / C)) + 4.0
+    key = np.partition(philox.class_keys(seed, np.arange(C)), b - 1)[b - 1]
+    at = float(key) / 2.0 ** 64 * C
+    assert at < b - 1 - slack or at > b + slack
+    _sampler_case(dev, labels, C, 0, b / C, seed)
+
+
 def test_sampler_refinement_beyond_lds(dev):
     """A shard of 20M classes: the threshold's top-digit bucket holds more
     candidates than the refinement keeps in LDS (4,096), so it works on them
