@@ -77,17 +77,7 @@ WsLayout ws_layout(int64_t B, int64_t d, int64_t C, int64_t cap, int compute) {
   L.ld_xt = round_up(B, 32);
   L.ld_g = round_up(B, 128);
   L.n_lgroups = L.ld_cos / kLogitGroup;
-  if (compute == PFC_F32) {
-    L.n_split = split_f32(B, cap);
-  } else {
-    // Split-K of the feature-gradient contraction: ~256 workgroups of
-    // 128 batch rows, one per CU.
-    const int64_t n_rt = ceil_div(B, 128);
-    const int64_t chunks = ceil_div(cap, 32);
-    int64_t ns = ceil_div(256, n_rt);
-    ns = ns > chunks ? chunks : ns;
-    L.n_split = (int)(ns < 1 ? 1 : ns);
-  }
+  L.n_split = compute == PFC_F32 ? split_f32(B, cap) : split_16(B, d, cap);
   const size_t cos_elt = compute == PFC_F32 ? 4 : 2;
   L.off_inv_x = take((size_t)B * 4);
   L.off_xb = take(compute == PFC_F32 ? 0 : (size_t)L.ld_xt * d * 2);

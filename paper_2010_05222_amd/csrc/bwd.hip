@@ -23,6 +23,8 @@
 //   epilogue has complete rows: target terms, tangent projection, momentum,
 //   weight step and the scatter into the persistent W / momentum rows (unique
 //   rows, no atomics).  It runs after the dX kernels, which read the old W.
+#include <math.h>
+
 #include <atomic>
 
 #include "pfc_gemm.h"
@@ -85,11 +87,6 @@ PFC_STAGE3(dw_r, int16_t, wR0, wR1, wR2)
 PFC_STAGE3(dw_q, float, wQ0, wQ1, wQ2)
 PFC_STAGE3(dw_g, uint16_t, wG0, wG1, wG2)
 #undef PFC_STAGE3
-
-template <typename Tag>
-__device__ __forceinline__ float load16(const void* p, int64_t idx) {
-  return to_float<Tag>(((const uint16_t*)p)[idx]);
-}
 
 // Target term of a row, (p_t - 1) * slope_t, from its unmargined target cosine.
 __device__ __forceinline__ float target_coef(const Margin& mg, float c, float lse) {
@@ -446,64 +443,94 @@ __global__ void __launch_bounds__(256) k_scales(const float* __restrict__ gmax,
   *reinterpret_cast<float4*>(gscale + i) = make_float4(v[0], v[1], v[2], v[3]);
 }
 
-// Sum the split partials of a row in split order, add the row's target term
+// Sum the split partials of a row, add the row's target term
 // g_t * W[S_t] / ||w_t||, and apply the normalisation backward:
 // dx = (dX_hat - x_hat (x_hat . dX_hat)) / ||x||, dX_hat = (s/B) * sum.  A
 // mapped label outside [0, |S|) counts as unowned: no target term, and no
 // row of W or of the id list is read for it.
-template <typename Tag>
-__global__ void __launch_bounds__(256) k_dx_final(
-    const float* __restrict__ dx_part, int n_split, const void* __restrict__ X,
-    const void* __restrict__ W, const int32_t* __restrict__ active,
+//
+// One workgroup per batch row: d / 4 threads of four entries each sum one of
+// its runs of consecutive splits (independent loads, eight in flight), and the
+// runs' sums are added in order.  Bound by the partials' bytes on a large
+// batch (B = 1024, 32 splits, d = 512, 67 MB: 13.9 us, 15.7 with one run), by the
+// loads' latency on a small one, which the runs divide.  Few splits (a large
+// batch) take fewer threads: B = 4096, 8 splits: 15.0 us, 18.5 with 512.
+template <typename Tag, int D, int THREADS>
+__global__ void __launch_bounds__(THREADS) k_dx_final(
+    const float* __restrict__ dx_part, int n_split, const uint16_t* __restrict__ X,
+    const uint16_t* __restrict__ W, const int32_t* __restrict__ active,
     const int32_t* __restrict__ n_active_p,
     const int32_t* __restrict__ yhat, const float* __restrict__ row_lse,
     const float* __restrict__ inv_x, const float* __restrict__ inv_w,
-    const float* __restrict__ tgtc, int B, int d, Margin mg, float sB, float* __restrict__ dX) {
-  // One workgroup per batch row, thread t owns entries t and t + 256 (d <= 512):
-  // the split partials are independent loads, summed in split order.
-  __shared__ float red[4];
+    const float* __restrict__ tgtc, int B, Margin mg, float sB, float* __restrict__ dX) {
+  constexpr int TPR = D / 4;                     // threads of a run
+  constexpr int RUNS = THREADS / TPR;
+  constexpr int NW = TPR > 64 ? TPR / 64 : 1;    // waves that hold the row
+  __shared__ f32x4_t sums[RUNS][TPR];
+  __shared__ float red[NW];
   const int n = blockIdx.x;
-  const int t = threadIdx.x, lane = t & 63;
+  const int t = threadIdx.x % TPR, run = threadIdx.x / TPR;
+  const int per = (n_split + RUNS - 1) / RUNS;
+  const int s1 = per * (run + 1) < n_split ? per * (run + 1) : n_split;
+  const float* p = dx_part + (int64_t)n * D + 4 * t;
+  const int64_t stride = (int64_t)B * D;
+  f32x4_t sum = {0.0f, 0.0f, 0.0f, 0.0f};
+  for (int s = per * run; s < s1; s += 8) {
+    f32x4_t q[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      q[u] = s + u < s1 ? *reinterpret_cast<const f32x4_t*>(p + (s + u) * stride)
+                        : f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int u = 0; u < 8; ++u) sum += q[u];
+  }
+  sums[run][t] = sum;
+  // The first run's threads go on with the row.
+  const bool mine = run == 0;
   const float ix = inv_x[n];
-  const int K = *n_active_p;
-  const int yt = yhat[n] < K ? yhat[n] : -1;
+  f32x4_t v = {0.0f, 0.0f, 0.0f, 0.0f}, xh = v;
   float gt = 0.0f;
-  int64_t wbase = 0;
-  if (yt >= 0) {
-    gt = target_coef(mg, tgtc[n], row_lse[n]) * inv_w[yt];
-    wbase = (int64_t)active[yt] * d;
-  }
-  float v[2] = {0.0f, 0.0f}, xh[2] = {0.0f, 0.0f};
-  float dot = 0.0f;
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const int i = t + 256 * k;
-    if (i >= d) continue;
-    const float* p = dx_part + (int64_t)n * d + i;
-    const int64_t stride = (int64_t)B * d;
-    float sum = 0.0f;
-    int s = 0;
-    for (; s + 8 <= n_split; s += 8) {
-      float q[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) q[u] = p[(int64_t)(s + u) * stride];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) sum += q[u];
+  uint2 w4 = make_uint2(0, 0), x4 = make_uint2(0, 0);
+  if (mine) {
+    const int yt = yhat[n];
+    if (yt >= 0 && yt < *n_active_p) {
+      gt = target_coef(mg, tgtc[n], row_lse[n]) * inv_w[yt];
+      w4 = *reinterpret_cast<const uint2*>(W + (int64_t)active[yt] * D + 4 * t);
     }
-    for (; s < n_split; ++s) sum += p[(int64_t)s * stride];
-    if (yt >= 0) sum = fmaf(gt, load16<Tag>(W, wbase + i), sum);
-    v[k] = sB * sum;
-    xh[k] = load16<Tag>(X, (int64_t)n * d + i) * ix;
-    dot = fmaf(xh[k], v[k], dot);
+    x4 = *reinterpret_cast<const uint2*>(X + (int64_t)n * D + 4 * t);
   }
-  dot = wave_sum(dot);
-  if (lane == 0) red[t >> 6] = dot;
   __syncthreads();
-  dot = red[0] + red[1] + red[2] + red[3];
+  float dot = 0.0f;
+  if (mine) {
+    const uint32_t wq[2] = {w4.x, w4.y}, xq[2] = {x4.x, x4.y};
 #pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const int i = t + 256 * k;
-    if (i < d) dX[(int64_t)n * d + i] = ix * (v[k] - xh[k] * dot);
+    for (int u = 1; u < RUNS; ++u) sum += sums[u][t];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int sh = 16 * (e & 1);
+      v[e] = sB * fmaf(gt, to_float<Tag>((uint16_t)(wq[e >> 1] >> sh)), sum[e]);
+      xh[e] = to_float<Tag>((uint16_t)(xq[e >> 1] >> sh)) * ix;
+      dot = fmaf(xh[e], v[e], dot);
+    }
+    if constexpr (TPR < 64) {   // the row's half of its wave
+#pragma unroll
+      for (int off = TPR / 2; off > 0; off >>= 1) dot += __shfl_xor(dot, off, 64);
+    } else {
+      dot = wave_sum(dot);
+      if ((t & 63) == 0) red[t >> 6] = dot;
+    }
+  }
+  if constexpr (NW > 1) {
+    __syncthreads();
+    dot = 0.0f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) dot += red[w];
+  }
+  if (mine) {
+    f32x4_t o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = ix * (v[e] - xh[e] * dot);
+    *reinterpret_cast<f32x4u_t*>(dX + (int64_t)n * D + 4 * t) = o;
   }
 }
 
@@ -1074,6 +1101,28 @@ __global__ void __launch_bounds__(512) k_dw16(
   });
 }
 
+}  // namespace
+
+// Class splits of the feature gradient: workgroups of 128 batch rows, one per
+// CU, in one round (`kDxWgs` of them; one more would be a second round, as
+// ceil(256 / n_rt) gave at B = 777: 90 us for 45).  On few classes fewer
+// splits: a split costs its partial sums, written and read again (8 B d bytes
+// at the copy rate, 4.7 MB/us), and saves its share of the 1.2 us that a
+// chunk of 32 classes takes, so their sum is least at
+// sqrt(1.2 chunks 4.7e6 / (8 B d)).
+// At B = 128, |S| = 10,000, d = 512 that is 59 splits instead of 256: the sum
+// of the partials takes 5.7 instead of 26.8 us, dX 21.6 instead of 21.0.
+int split_16(int64_t B, int64_t d, int64_t cap) {
+  constexpr int64_t kDxWgs = 256;
+  const int64_t most = kDxWgs / ceil_div(B, kDxRows);   // B <= 8192: at least 4
+  const double chunks = (double)ceil_div(cap, kBwKC);
+  const int64_t best = (int64_t)ceil(sqrt(1.2 * 4.7e6 / 8.0 * chunks / ((double)B * (double)d)));
+  const int64_t ns = best < most ? best : most;
+  return (int)(ns < (int64_t)chunks ? ns : (int64_t)chunks);
+}
+
+namespace {
+
 // Compute units of the current device (0 if the query fails).
 int device_cu_count() {
   int dev = 0, n = 0;
@@ -1106,9 +1155,13 @@ void launch_bwd16(const StepArgs& a, const StepWs& w, const Margin& mg, float sB
                      n_tiles, per_xcd, w.dx_part);
   timing_stop(4, stream);
   timing_start(5, stream);
-  hipLaunchKernelGGL(k_dx_final<Tag>, dim3((unsigned)B), dim3(256), 0, stream,
-                     w.dx_part, w.n_split, a.X, a.W, a.active, a.n_active, a.labels_mapped,
-                     a.row_lse, w.inv_x, w.inv_w, w.tgtc, B, (int)a.d, mg, sB, a.dX);
+  auto final = [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)B), dim3(threads), 0, stream, w.dx_part, w.n_split,
+                       (const uint16_t*)a.X, (const uint16_t*)a.W, a.active, a.n_active,
+                       a.labels_mapped, a.row_lse, w.inv_x, w.inv_w, w.tgtc, B, mg, sB, a.dX);
+  };
+  if (w.n_split <= 8) final(k_dx_final<Tag, 128 * WI, 128>, 128);
+  else final(k_dx_final<Tag, 128 * WI, 512>, 512);
   timing_stop(5, stream);
   timing_start(6, stream);
   if (a.W_master)

@@ -26,9 +26,6 @@ constexpr int kLd = kChunk + 4;  // LDS row stride: sixteen rows' 16-byte pieces
 constexpr int kDxRows = 32;      // batch rows of a dX workgroup
 constexpr int kDwCls = 16;       // classes of a dW workgroup
 
-// Four floats at any 4-byte aligned address (the caller's rows are only that).
-typedef float f32x4u_t __attribute__((ext_vector_type(4), aligned(4)));
-
 __device__ __forceinline__ f32x4_t load4(const float* p) {
   return *reinterpret_cast<const f32x4u_t*>(p);
 }

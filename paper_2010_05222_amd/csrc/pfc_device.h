@@ -13,6 +13,8 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
+// Four floats at any 4-byte aligned address (a caller's fp32 rows are only that).
+typedef float f32x4u_t __attribute__((ext_vector_type(4), aligned(4)));
 
 // Storage tags of the 16-bit operand types.
 struct Bf16Tag {};

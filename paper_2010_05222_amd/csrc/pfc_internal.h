@@ -144,7 +144,9 @@ hipError_t launch_lse(const StepArgs& a, const StepWs& w, int64_t n_ctiles, int 
 // The fp32 path (f32.hip).
 hipError_t launch_forward_f32(const StepArgs& a, const StepWs& w, hipStream_t stream);
 hipError_t launch_backward_f32(const StepArgs& a, const StepWs& w, hipStream_t stream);
-int split_f32(int64_t B, int64_t cap);   // class splits of its feature gradient
+// Class splits of the feature gradient.
+int split_f32(int64_t B, int64_t cap);
+int split_16(int64_t B, int64_t d, int64_t cap);
 // Narrowest class tile of the fp32 forward.
 constexpr int kFwdClassTile32 = 32;
 

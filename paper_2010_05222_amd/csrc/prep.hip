@@ -40,9 +40,14 @@ __device__ __forceinline__ float sumsq8(const uint4& v) {
 // row ids that the contraction kernels read a chunk or tile at a time, with
 // no wait on |S|: act_pad[j] = active[min(j, |S| - 1)] (0 if S is empty).
 constexpr int kPrepRows = 32;
-constexpr int kPadPerBlock = 4 * 256;   // act_pad entries per workgroup
+// 1,024 threads, two rows per wave, so that few row blocks still have their
+// loads and the transposition spread over many waves (d = 512: 4.9 us at
+// B = 128, 6.8 at 1024; 8.5 and 11.4 with 256 threads).
+constexpr int kPrepThreads = 1024;
+constexpr int kPrepWaves = kPrepThreads / 64;
+constexpr int kPadPerBlock = 4 * kPrepThreads;   // act_pad entries per workgroup
 template <typename Tag>
-__global__ void __launch_bounds__(256) k_prep_x16(const uint16_t* __restrict__ X, int B, int d,
+__global__ void __launch_bounds__(kPrepThreads) k_prep_x16(const uint16_t* __restrict__ X, int B, int d,
                                                   int64_t ld_xt, float* __restrict__ inv_x,
                                                   uint16_t* __restrict__ xbT,
                                                   uint16_t* __restrict__ xblk,
@@ -70,18 +75,18 @@ __global__ void __launch_bounds__(256) k_prep_x16(const uint16_t* __restrict__ X
     *inv_w_max = 0.0f;
     *arrivals = 0;
   }
-  // Each wave's eight rows: all loads first (one memory round trip, not eight).
+  // Each wave's rows: all loads first (one memory round trip).
   const bool c_ok = lane < d / 8;   // d <= 512: one 16-byte piece per lane
-  uint4 rows[kPrepRows / 4];
+  uint4 rows[kPrepRows / kPrepWaves];
 #pragma unroll
-  for (int k = 0; k < kPrepRows / 4; ++k) {
-    const int n = n0 + wave + 4 * k;
+  for (int k = 0; k < kPrepRows / kPrepWaves; ++k) {
+    const int n = n0 + wave + kPrepWaves * k;
     rows[k] = make_uint4(0, 0, 0, 0);
     if (n < B && c_ok) rows[k] = *reinterpret_cast<const uint4*>(X + (int64_t)n * d + 8 * lane);
   }
 #pragma unroll
-  for (int k = 0; k < kPrepRows / 4; ++k) {
-    const int r = wave + 4 * k;
+  for (int k = 0; k < kPrepRows / kPrepWaves; ++k) {
+    const int r = wave + kPrepWaves * k;
     const int n = n0 + r;
     const uint4 v = rows[k];
     const float ss = wave_sum(sumsq8<Tag>(v));
@@ -102,7 +107,7 @@ __global__ void __launch_bounds__(256) k_prep_x16(const uint16_t* __restrict__ X
   // Column i of the tile (32 rows) -> block blockIdx.x of xbT, row i: four
   // 16-byte pieces (the block is contiguous: [d][32]).
   uint16_t* blk = xbT + (int64_t)blockIdx.x * d * kPrepRows;
-  for (int q = threadIdx.x; q < d * 4; q += 256) {
+  for (int q = threadIdx.x; q < d * 4; q += kPrepThreads) {
     const int i = q >> 2, r0 = (q & 3) * 8;
     uint16_t o[8];
 #pragma unroll
@@ -120,7 +125,7 @@ hipError_t launch_prep(const StepArgs& a, const StepWs& w, hipStream_t stream) {
   const unsigned grid = (unsigned)(w.ld_xt / kPrepRows + ceil_div(w.n_act_pad, kPadPerBlock));
   timing_start(1, stream);
   auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, stream, (const uint16_t*)a.X, B, d,
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kPrepThreads), 0, stream, (const uint16_t*)a.X, B, d,
                        w.ld_xt, w.inv_x, (uint16_t*)w.xbT, (uint16_t*)w.xblk, w.inv_w_max,
                        w.arrivals, a.active, a.n_active, w.act_pad, w.n_act_pad);
   };

@@ -327,6 +327,24 @@ def test_many_rows_per_class(dev):
     _case(dev, 2400, 128, 3000, 0.1, "bf16", "arcface", 0.5, seed=13, labels=labels)
 
 
+@pytest.mark.parametrize("d,dtype", [(128, "bf16"), (256, "f16"), (512, "bf16")])
+@pytest.mark.parametrize("B,C,r", [
+    (5, 90, 0.4),        # two 32-class chunks: two splits, one run of them
+    (385, 6000, 0.3),    # four row blocks of 128, one of a single row; 57 chunks
+    (129, 40000, 0.5),   # more chunks than splits
+])
+def test_feature_gradient_splits(dev, B, C, r, d, dtype):
+    # Splits of the class range and the runs that sum them.  The max-abs bar
+    # relative to max |ref|: the gradient scale is 64 / B.  At d = 128 logits
+    # spread by 64 / sqrt(128) = 5.7, and of 20,000 classes a few have all 129
+    # softmax numerators below 2^-14 of their group's maximum, where the fp16
+    # store's steps of 2^-24 are no longer 2^-11 of them (a class gradient row
+    # off by 4 %): 3,600 classes there.
+    if d == 128 and C == 40000:
+        C, r = 12000, 0.3
+    _case(dev, B, d, C, r, dtype, "arcface", 0.5, seed=65, random_m=False, abs_scaled=True)
+
+
 # PFC* conflict filter (Sec. 3.3.4, Eq. noise_filtering): some rows sit near
 # the centre of another row's class, so their cosine to that (active)
 # negative is ~0.9 > tau and the logit leaves the row's denominator.
