@@ -547,9 +547,16 @@ __global__ void __launch_bounds__(THREADS) k_dx_final(
 // chunk c + 1 produced, chunk c contracted.  The second k-step of chunk c is
 // contracted at the start of the next chunk, from fragments read in this
 // one, so that the matrix pipe is busy while the next fragments arrive.
-template <typename Tag, int WI, bool MASTER>
+//
+// That is a tile of CLS = 128 classes, and a tile of 64 classes is the same with
+// half the classes per wave; one of 32 gives each wave an eighth of d (a
+// quarter at D = 128, which two waves then share the work of, with the same
+// results).  Where a tile has fewer pieces to load or coefficients to produce
+// than the waves have slots, several waves load and write the same bytes, so
+// that all waves' load counts stay alike.
+template <typename Tag, int WI, bool MASTER, int CLS>
 __global__ void __launch_bounds__(512) k_dw16(
-    const uint16_t* __restrict__ xbT, int64_t ld_xt, const void* __restrict__ X,
+    const uint16_t* __restrict__ xbT, const void* __restrict__ X,
     uint16_t* __restrict__ W, float* __restrict__ W_master, float* __restrict__ M,
     const int32_t* __restrict__ active, const int32_t* __restrict__ n_active_p,
     const int32_t* __restrict__ yhat, const float* __restrict__ row_lse,
@@ -559,10 +566,13 @@ __global__ void __launch_bounds__(512) k_dw16(
     float mu, int32_t* __restrict__ gate, int n_gate, int epoch) {
   constexpr int D = 128 * WI;
   constexpr int NW = 8;
-  constexpr int DW = D / 4;             // d entries of a wave
-  constexpr int CW = kDwCls / 2;        // classes of a wave
+  constexpr int WD = CLS == 32 && D > 128 ? 8 : 4;   // waves that share d
+  constexpr int DW = D / WD;            // d entries of a wave
+  constexpr int CW = CLS == 128 ? 64 : 32;   // classes of a wave
   constexpr int MB = DW / 32;           // 32-entry d blocks of a wave
   constexpr int NB = CW / 32;           // 32-class blocks of a wave
+  constexpr int PIECES = CLS / 8;       // 16-byte pieces of a logit-store row
+  constexpr int RROWS = 64 / PIECES;    // rows of one load
   constexpr int XDMA = D / 16 / NW;     // X^T loads (16 d rows each) per wave per chunk
   constexpr int RDMA = 8 / NW;          // logit-store loads (4 rows each) per wave
   constexpr int QL = 8 / NW;            // row-scale pieces (4 rows each) per wave
@@ -571,7 +581,7 @@ __global__ void __launch_bounds__(512) k_dw16(
   constexpr int NF = MB + NB;           // fragment reads per k-step
   static_assert(PER_ITER + 2 * (RDMA + 1) < 64, "vmcnt range");
   const int K = *n_active_p;
-  const int64_t j0 = (int64_t)blockIdx.x * kDwCls;
+  const int64_t j0 = (int64_t)blockIdx.x * CLS;
   if (j0 >= K) return;
   // Start gates (n_gate > 0 on a long grid, one workgroup per CU): workgroup
   // 2 i + 1 of the first wave starts once workgroup 2 i has finished its
@@ -593,10 +603,10 @@ __global__ void __launch_bounds__(512) k_dw16(
     }
     __syncthreads();
   }
-
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wd = wave & 3, wc = wave >> 2;   // the wave's d quarter and class half
+  // The wave's part of d and of the classes.
+  const int wd = wave & (WD - 1), wc = CLS == 128 ? wave >> 2 : wave / WD % (CLS / CW);
   const int half = lane >> 5, l32 = lane & 31;
   const int n_chunks = (int)ceil_div(B, kBwKC);
   const int c_stop = (int)ceil_div(n_chunks, 3) * 3;
@@ -610,10 +620,14 @@ __global__ void __launch_bounds__(512) k_dw16(
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
     const int64_t j = j0 + 64 * u + lane;
-    act_l[u] = j < K ? active[j] : 0;
-    iw_l[u] = j < K ? inv_w[j] : 0.0f;
+    const bool in = 64 * u + lane < CLS && j < K;
+    act_l[u] = in ? active[j] : 0;
+    iw_l[u] = in ? inv_w[j] : 0.0f;
   }
 
+  // Swizzle of a logit-store row's pieces: the rows of a transposing read on
+  // distinct banks.
+  auto swz = [](int r) { return 2 * (r & (PIECES < 8 ? 1 : 3)); };
   // Producer slots: a 16-lane group owns 16 classes x 8 batch rows of a chunk;
   // lane gi of the group owns class 16 cb + gi.
   const int grp = lane >> 4, gi = lane & 15;
@@ -622,27 +636,28 @@ __global__ void __launch_bounds__(512) k_dw16(
 #pragma unroll
   for (int u = 0; u < GROUPS; ++u) {
     const int s = 4 * wave + grp + 16 * u;
-    const int cb = s >> 2;
+    const int cb = CLS == 128 ? s >> 2 : (s >> 2) % (CLS / 16);
     pcls[u] = 16 * cb + gi;
     prg[u] = s & 3;
     // Lane 4 e + q of the group points at row 8 rg + e, classes 16 cb + 4 q .. + 3
-    // (16-byte piece 2 cb + q / 2, stored at piece ^ 2 (row & 3)), half q & 1.
+    // (16-byte piece 2 cb + q / 2, stored at piece ^ swz(row)), half q & 1.
     const int e = gi >> 2, q = gi & 3;
     const int r = 8 * prg[u] + e;
-    ptr_off[u] = (uint32_t)(r * kDwCls * 2 + 16 * ((2 * cb + (q >> 1)) ^ (2 * (r & 3))) + 8 * (q & 1));
+    ptr_off[u] = (uint32_t)(r * CLS * 2 + 16 * ((2 * cb + (q >> 1)) ^ swz(r)) + 8 * (q & 1));
   }
 
-  // Raw logit-store values: load v of this wave covers rows 4 b .. 4 b + 3
-  // (b = wave RDMA + v); lane l fills piece l % 16 of row 4 b + l / 16 with
-  // source piece (l % 16) ^ 2 (row & 3).
+  // Raw logit-store values: load v of this wave covers rows RROWS b .. + RROWS - 1
+  // (b = wave RDMA + v, modulo the tile's 32 / RROWS); lane l fills piece
+  // l % PIECES of row RROWS b + l / PIECES with source piece (l % PIECES) ^ swz(row).
   auto dma_raw_piece = [&](auto st, int c, int v) __attribute__((always_inline)) {
     constexpr int S = decltype(st)::value;
     const int cc = c < n_chunks ? c : n_chunks - 1;
-    const int blk = wave * RDMA + v;
-    const int r = 4 * blk + (lane >> 4);
+    constexpr int BLKS = kBwKC / RROWS;
+    const int blk = BLKS == NW * RDMA ? wave * RDMA + v : (wave * RDMA + v) % BLKS;
+    const int r = RROWS * blk + lane / PIECES;
     int n = cc * kBwKC + r;
     n = n < B ? n : B - 1;
-    const int piece = (lane & 15) ^ (2 * (r & 3));
+    const int piece = lane % PIECES ^ swz(r);
     dma16(lbuf + (int64_t)n * ld_cos + j0 + 8 * piece, dw_r<S>() + 512 * blk);
   };
   // Row scales of the chunk: QL 16-byte pieces (4 rows each) per wave; rows < ld_g always.
@@ -686,7 +701,7 @@ __global__ void __launch_bounds__(512) k_dw16(
     for (int u = 0; u < GROUPS; ++u) {
       const uint32_t ra = lds_addr(dw_r<S>()) + ptr_off[u];
       ds_read_tr_b64<0>(in.qlo[u], ra);
-      ds_read_tr_b64<4 * kDwCls * 2>(in.qhi[u], ra);
+      ds_read_tr_b64<4 * CLS * 2>(in.qhi[u], ra);
       const uint32_t qa = lds_addr(dw_q<S>()) + 32 * prg[u];
       ds_read_128<0>(in.sq[u][0], qa);
       ds_read_128<16>(in.sq[u][1], qa);
@@ -766,10 +781,9 @@ __global__ void __launch_bounds__(512) k_dw16(
   // while the matrix pipe works through the MFMAs already issued.
   constexpr int NMF = MB * NB;
   constexpr int W_AT = NMF >= 16 ? 3 : NMF / 4;      // wait for the chunk's fragment and producer reads
-  constexpr int G0_AT = NMF / 2 - 1;                 // coefficient group 0 written
-  constexpr int G1_AT = NMF - 2 > G0_AT ? NMF - 2 : G0_AT + 1;  // group 1 written
+  constexpr int G0_AT = NMF / 2 - 1 > W_AT ? NMF / 2 - 1 : W_AT;   // coefficients written
   constexpr int NITEM = RDMA + 1 + XDMA + NF;        // loads and reads spread over the second k-step
-  static_assert(G1_AT < NMF, "slots");
+  static_assert(GROUPS == 1, "one producer slot per thread");
   for (int c = 0; c < c_stop; c += 3) {
     static_for<0, 3>([&](auto uu) {
       constexpr int u = decltype(uu)::value;
@@ -808,8 +822,6 @@ __global__ void __launch_bounds__(512) k_dw16(
           pin_group(pin, 0);
         }
         if constexpr (i == G0_AT) produce_group(SN{}, pin, 0, gmask);
-        if constexpr (GROUPS > 1 && i == G0_AT + 1) pin_group(pin, 1);
-        if constexpr (GROUPS > 1 && i == G1_AT) produce_group(SN{}, pin, 1, gmask);
       });
       // First k-step of this chunk, with the loads of later chunks and this
       // chunk's second k-step reads spread over its slots.
@@ -848,7 +860,7 @@ __global__ void __launch_bounds__(512) k_dw16(
   if (gated && !(blockIdx.x & 1) && threadIdx.x == 0)
     __hip_atomic_store(gate + blockIdx.x / 2, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
-  // ---- update: the tile goes through LDS in four passes of 32 classes so
+  // ---- update: the tile goes through LDS in passes of 32 classes so
   // that each wave then owns whole rows: W, momentum and master rows are read
   // and written in full contiguous segments.  Pass p holds the classes
   // 32 p + r (r < 32); entry d of row r sits in stage array d / 256 at
@@ -861,7 +873,7 @@ __global__ void __launch_bounds__(512) k_dw16(
   float* const tlo = reinterpret_cast<float*>(wX0);
   float* const thi = reinterpret_cast<float*>(wX1);
   const bool lane_on = LPH == 64 || lane < LPH;
-  const int kt = (int)(K - j0);               // classes of the tile that exist (>= 1)
+  const int kt = (int)(K - j0);               // classes from the tile's first on that exist (>= 1)
   int* const hits = reinterpret_cast<int*>(wG0);   // NW lists of kHitCap entries
   int* const hit_n = reinterpret_cast<int*>(wQ0);  // their lengths
   static_assert(NW * kHitCap * 4 <= kDwCls * kBwKC * 2, "hit lists fit a coefficient stage");
@@ -911,18 +923,19 @@ __global__ void __launch_bounds__(512) k_dw16(
 #pragma unroll
     for (int k = 0; k < RPW; ++k) load_row(bt, p, k);
   };
-  // Pass p's classes are block p % 2 of the waves of class half p / 2.
+  constexpr int PASSES = CLS / 32;
+  // Pass p's classes are block p % NB of the waves of class part p / NB.
   auto park = [&](auto pp) __attribute__((always_inline)) {
     constexpr int p = decltype(pp)::value;
-    if (wc != p / 2) return;
+    if (wc != p / NB) return;
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const int d0 = DW * wd + 32 * mb + 8 * g + 4 * half;
         *reinterpret_cast<float4*>((d0 >= 256 ? thi : tlo) + l32 * kTLd + (d0 & 255)) =
-            make_float4(acc[mb][p % 2][4 * g], acc[mb][p % 2][4 * g + 1],
-                        acc[mb][p % 2][4 * g + 2], acc[mb][p % 2][4 * g + 3]);
+            make_float4(acc[mb][p % NB][4 * g], acc[mb][p % NB][4 * g + 1],
+                        acc[mb][p % NB][4 * g + 2], acc[mb][p % NB][4 * g + 3]);
       }
   };
   // Target term of batch row nn added to staged row r (this wave's own row).
@@ -949,7 +962,7 @@ __global__ void __launch_bounds__(512) k_dw16(
   // Row update, with a = the staged row (dL/dw_hat = sB a), w_hat = w / ||w||:
   // g_w = (sB a - w_hat (w_hat . sB a)) / ||w|| = ga a - gb w,
   // ga = sB / ||w||, gb = ga (w . a) / ||w||^2; then momentum and the step.
-  // With PN < 4 each row's registers are refilled, right after the row is
+  // With PN < PASSES each row's registers are refilled, right after the row is
   // written, with the same row of pass PN: the next pass's loads spread over
   // this pass's arithmetic and stores instead of queueing behind them.
   auto update_rows = [&](Rows& bt, auto pn_c) __attribute__((always_inline)) {
@@ -975,7 +988,7 @@ __global__ void __launch_bounds__(512) k_dw16(
 #pragma unroll
     for (int k = 0; k < RPW; ++k) dots[k] = wave_total(dots[k]);
     const int nv = bt.nv;
-    if constexpr (PN < 4) set_rows(bt, PN);
+    if constexpr (PN < PASSES) set_rows(bt, PN);
 #pragma unroll
     for (int k = 0; k < RPW; ++k) {
       const int r = RPW * wave + k;
@@ -1026,7 +1039,7 @@ __global__ void __launch_bounds__(512) k_dw16(
           *reinterpret_cast<uint2*>(reinterpret_cast<char*>(W + rb) + 2 * o) = ov;
         }
       }
-      if constexpr (PN < 4) load_row(bt, PN, k);
+      if constexpr (PN < PASSES) load_row(bt, PN, k);
     }
   };
 
@@ -1047,7 +1060,7 @@ __global__ void __launch_bounds__(512) k_dw16(
     for (int nbase = q0; nbase < q1; nbase += 64) {
       const int n = nbase + lane;
       const int yv = n < q1 ? yhat[n] : -1;
-      const bool hit = yv >= j0 && yv < j0 + kDwCls;
+      const bool hit = yv >= j0 && yv < j0 + CLS;
       const uint64_t mask = __ballot(hit);
       const int pos = cnt + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
                                                       __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
@@ -1066,7 +1079,7 @@ __global__ void __launch_bounds__(512) k_dw16(
     hn[w] = __builtin_amdgcn_readfirstlane(hit_n[w]);
     hit_scan |= hn[w] > kHitCap;
   }
-  static_for<0, 4>([&](auto pp) {
+  static_for<0, PASSES>([&](auto pp) {
     constexpr int p = decltype(pp)::value;
     if constexpr (p > 0) {
       wait_lgkm0();
@@ -1139,8 +1152,18 @@ void launch_bwd16(const StepArgs& a, const StepWs& w, const Margin& mg, float sB
   // launch writes a number of its own to the gates it opens.
   static std::atomic<int> launches{0};
   const int n_cu = device_cu_count();
-  const int64_t dw_grid = ceil_div(a.cap, kDwCls);
-  const int n_gate = (n_cu > 0 && dw_grid >= 4LL * n_cu) ? (n_cu / 2 < kDwGates ? n_cu / 2 : kDwGates) : 0;
+  // A workgroup fills its CU.  A shard whose 128-class tiles leave half of the
+  // CUs idle goes in tiles of 64 or 32 classes (d = 512, us with 128 -> now:
+  // |S| = 8,192, B = 128 28 -> 17, B = 1024 52 -> 34, B = 4096 140 -> 102; |S| =
+  // 16,384 34 -> 26, 56 -> 46, 149 -> 134).  The last round of a longer grid
+  // does not: cut that way in the same kernel it made the full tiles 2 % slower,
+  // in a launch of its own it cost what it saved (|S| = 100,000 with a master
+  // 311 -> 304 us, |S| = 45,000, d = 256 66 -> 68).
+  const int64_t tiles = ceil_div(a.cap, kDwCls);
+  const int n_slots = n_cu > 0 ? n_cu : 256;
+  const int cls = tiles * 4 <= n_slots ? 32 : tiles * 2 <= n_slots ? 64 : kDwCls;
+  const int n_gate =
+      (n_cu > 0 && tiles >= 4LL * n_cu) ? (n_cu / 2 < kDwGates ? n_cu / 2 : kDwGates) : 0;
   const int epoch = 1 + (launches.fetch_add(1, std::memory_order_relaxed) & 0x3FFFFFFF);
   const int n_rt = (int)ceil_div(B, kDxRows);
   const int64_t n_tiles = (int64_t)n_rt * w.n_split;
@@ -1164,18 +1187,21 @@ void launch_bwd16(const StepArgs& a, const StepWs& w, const Margin& mg, float sB
   else final(k_dx_final<Tag, 128 * WI, 512>, 512);
   timing_stop(5, stream);
   timing_start(6, stream);
-  if (a.W_master)
-    hipLaunchKernelGGL((k_dw16<Tag, WI, true>), dim3((unsigned)dw_grid), dim3(512),
-                       0, stream, (const uint16_t*)w.xbT, w.ld_xt, a.X, (uint16_t*)a.W, a.W_master,
-                       a.M, a.active, a.n_active, a.labels_mapped, a.row_lse, w.inv_x, w.inv_w,
-                       w.tgtc, (const uint16_t*)w.lbuf, w.ld_cos, w.gscale, w.ld_g, B, mg, sB, a.lr,
-                       a.mu, w.dw_gate, n_gate, epoch);
-  else
-    hipLaunchKernelGGL((k_dw16<Tag, WI, false>), dim3((unsigned)dw_grid), dim3(512),
-                       0, stream, (const uint16_t*)w.xbT, w.ld_xt, a.X, (uint16_t*)a.W, a.W_master,
-                       a.M, a.active, a.n_active, a.labels_mapped, a.row_lse, w.inv_x, w.inv_w,
-                       w.tgtc, (const uint16_t*)w.lbuf, w.ld_cos, w.gscale, w.ld_g, B, mg, sB, a.lr,
-                       a.mu, w.dw_gate, n_gate, epoch);
+  auto update = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)ceil_div(a.cap, cls)), dim3(512), 0, stream,
+                       (const uint16_t*)w.xbT, a.X, (uint16_t*)a.W, a.W_master, a.M, a.active,
+                       a.n_active, a.labels_mapped, a.row_lse, w.inv_x, w.inv_w, w.tgtc,
+                       (const uint16_t*)w.lbuf, w.ld_cos, w.gscale, w.ld_g, B, mg, sB, a.lr, a.mu,
+                       w.dw_gate, n_gate, epoch);
+  };
+  auto update_in = [&](auto c) {
+    constexpr int CLS = decltype(c)::value;
+    if (a.W_master) update(k_dw16<Tag, WI, true, CLS>);
+    else update(k_dw16<Tag, WI, false, CLS>);
+  };
+  if (cls == 32) update_in(std::integral_constant<int, 32>{});
+  else if (cls == 64) update_in(std::integral_constant<int, 64>{});
+  else update_in(std::integral_constant<int, 128>{});
   timing_stop(6, stream);
 }
 

@@ -345,6 +345,44 @@ def test_feature_gradient_splits(dev, B, C, r, d, dtype):
     _case(dev, B, d, C, r, dtype, "arcface", 0.5, seed=65, random_m=False, abs_scaled=True)
 
 
+@pytest.mark.parametrize("d,dtype,master", [(128, "bf16", True), (256, "f16", False),
+                                            (512, "bf16", True), (512, "f16", False)])
+def test_class_tiles_agree(dev, d, dtype, master):
+    """The class-gradient tiles of 128, 64 and 32 classes give a class the same
+    momentum row bit for bit.  A shard of 256 full tiles and a last round of few
+    classes, against shards of some of its classes (whole 128-class groups),
+    whose tiles are others, given its row log-sum-exp."""
+    from _gpu_util import make_problem
+    B, n_cu = 70, torch.cuda.get_device_properties(dev).multi_processor_count
+    C = 128 * n_cu + 66 * 128 + 33              # a round of 128-class tiles, then 64
+    Xd, Wd, Md, Pd, Ld = make_problem(B, d, C, dtype, 66, master=master, device=dev)
+    Ld[3:9] = Ld[2]                             # rows of one class
+
+    def run(lo, hi, lse):
+        print(f"\nclass tiles: d={d} {dtype} classes [{lo}, {hi})", flush=True)
+        W, M = Wd[lo:hi].clone(), Md[lo:hi].clone()
+        P = Pd[lo:hi].clone() if master else None
+        shard = _shard(B, d, hi - lo, 1.0, dtype, "arcface", 0.5, class_offset=lo, dev=dev)
+        shard.sample(Ld, 0)
+        shard.forward(Xd, W)
+        shard.backward(Xd, W, M, P, row_lse=shard.row_lse if lse is None else lse)
+        torch.cuda.synchronize()
+        return shard.row_lse.clone(), W, M, P
+
+    lse, W, M, P = run(0, C, None)
+    full = 128 * n_cu
+    for lo, hi in [(0, 128), (full - 128, C), (0, 128 * (n_cu // 4)), (256, 256 + 128 * 129),
+                   (full, C), (0, 128 * (n_cu // 2)), (0, full), (128, full + 256)]:
+        _, w, m, p = run(lo, hi, lse)
+        assert torch.equal(m, M[lo:hi])
+        assert p is None or torch.equal(p, P[lo:hi])
+        # The same fp32 step, rounded to the storage type once, or (where the
+        # compiler fuses the step's last operation with the conversion to fp16)
+        # without the fp32 rounding before: at most one unit in the last place.
+        ulp = 2.0 ** -10 if dtype == "f16" else 0.0
+        assert torch.all((w.float() - W[lo:hi].float()).abs() <= ulp * W[lo:hi].float().abs())
+
+
 # PFC* conflict filter (Sec. 3.3.4, Eq. noise_filtering): some rows sit near
 # the centre of another row's class, so their cosine to that (active)
 # negative is ~0.9 > tau and the logit leaves the row's denominator.
