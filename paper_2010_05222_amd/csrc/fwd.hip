@@ -512,6 +512,180 @@ __global__ void __launch_bounds__(kFwdThreads, 2) k_fwd16(
   }
 }
 
+// The same for short grids: 128 active classes x 64 batch rows, with no
+// pipeline.  A wave owns 32 of the classes and all 64 rows; its class rows go
+// straight to registers, all of d at once (16 bytes of row lane % 32 per
+// k-step), the batch rows to LDS, and one wait covers both, so the kernel is
+// one memory round trip, the MFMAs and the epilogue, where the pipelined tile
+// waits sixteen times (d = 512) for a 32-wide chunk and computes 256 rows
+// whatever the batch.  At |S| = 10,000, B = 128: 13.8 us, 20.0 pipelined.
+// 16-byte piece c of LDS row r sits at position c ^ (r & 15): sixteen
+// consecutive rows of a fragment read on distinct banks.
+constexpr int kNarrowRows = 64;
+template <typename Tag, int D>
+__global__ void __launch_bounds__(kFwdThreads, 2) k_fwd16n(
+    const uint16_t* __restrict__ X, const uint16_t* __restrict__ W,
+    const int32_t* __restrict__ act_pad, const int32_t* __restrict__ n_active_p,
+    const int32_t* __restrict__ yhat, const float* __restrict__ inv_x,
+    float* __restrict__ inv_w, float* __restrict__ inv_w_max, int B, int64_t ld_cos,
+    int64_t n_ctiles, int n_rt, int64_t n_tiles, int64_t per_xcd, Margin mg, float tau,
+    uint16_t* __restrict__ lbuf, float2* __restrict__ stats, float* __restrict__ tgt,
+    float* __restrict__ tgtc, float* __restrict__ gmax, int64_t ld_g) {
+  constexpr int NK = D / 16;                       // k-steps
+  constexpr int PIECES = D / 8;                    // 16-byte pieces of a row
+  constexpr int LOADS = kNarrowRows * PIECES / kFwdThreads;   // direct-to-LDS loads per wave
+  __shared__ __attribute__((aligned(1024))) uint16_t xs[kNarrowRows * D];
+  __shared__ __attribute__((aligned(16))) float iws[kFwdBM];
+  __shared__ float redm[4][kNarrowRows], reds[4][kNarrowRows];
+  const int64_t t = (int64_t)(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  if (t >= n_tiles) return;
+  const int64_t ct = t / n_rt;
+  const int rt = (int)(t % n_rt);
+  const int64_t j0 = ct * kFwdBM;
+  const int n0 = rt * kNarrowRows;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int half = lane >> 5, l32 = lane & 31;
+
+  const int64_t id = act_pad[j0 + 32 * wave + l32];   // valid past |S| too
+#pragma unroll
+  for (int u = 0; u < LOADS; ++u) {
+    const int blk = LOADS * wave + u;   // 1 KB of LDS
+    const int r = 64 * blk / PIECES + lane / PIECES;
+    const int n = n0 + r < B ? n0 + r : B - 1;
+    dma16(X + (int64_t)n * D + 8 * (lane % PIECES ^ (r & 15)), xs + 512 * blk);
+  }
+  const int K = *n_active_p;
+  if (j0 >= K) {   // drain the wave's loads into LDS, leave
+    wait_vmcnt<0>();
+    return;
+  }
+  const uint16_t* wrow = W + id * D + 8 * half;
+  uint4 a[NK];
+#pragma unroll
+  for (int s = 0; s < NK; ++s) a[s] = *reinterpret_cast<const uint4*>(wrow + 16 * s);
+  float ixr[2];
+  int yraw[2];
+#pragma unroll
+  for (int nb = 0; nb < 2; ++nb) {
+    const int n = n0 + 32 * nb + l32;
+    ixr[nb] = inv_x[n < B ? n : B - 1];
+    yraw[nb] = n < B ? yhat[n] : -1;
+  }
+  wait_vmcnt<0>();
+  __syncthreads();
+
+  f32x16_t acc[2];
+#pragma unroll
+  for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[nb][r] = 0.0f;
+  float ss = 0.0f;
+#pragma unroll
+  for (int s = 0; s < NK; ++s) {
+    const int pos = ((2 * s + half) ^ (l32 & 15)) * 8;
+    ss = sumsq2(a[s].x, ss, Tag{});
+    ss = sumsq2(a[s].y, ss, Tag{});
+    ss = sumsq2(a[s].z, ss, Tag{});
+    ss = sumsq2(a[s].w, ss, Tag{});
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) {
+      const uint4 b = *reinterpret_cast<const uint4*>(xs + (32 * nb + l32) * D + pos);
+      acc[nb] = mfma_32x32x16(a[s], b, acc[nb], Tag{});
+    }
+  }
+  // Inverse norms of the wave's 32 classes; the first row tile publishes them
+  // and their running maximum.
+  {
+    const float inv = 1.0f / fmaxf(sqrtf(ss + __shfl_xor(ss, 32, 64)), kEpsNormW);
+    const int64_t j = j0 + 32 * wave + l32;
+    if (half == 0) iws[32 * wave + l32] = inv;
+    if (rt == 0) {
+      if (half == 0) inv_w[j] = j < K ? inv : 0.0f;
+      const float m = wave_max(j < K ? inv : 0.0f);
+      if (lane == 0) atomicMax(reinterpret_cast<int*>(inv_w_max), __float_as_int(m));
+    }
+  }
+  __syncthreads();   // norms written; every fragment read of xs is done
+  // As in fwd_epilogue_rows, the row maximum and sum over the waves.
+  const float s2 = mg.s * kLog2e;
+  const bool filt = tau < 1.0f;
+  float ft2[2];
+#pragma unroll
+  for (int nb = 0; nb < 2; ++nb) {
+    const int n = n0 + 32 * nb + l32;
+    const int yh = yraw[nb] < K ? yraw[nb] : -1;   // past |S|: unowned
+    const int64_t jb = j0 + 32 * wave + 4 * half;
+    const int64_t tpos = yh - jb;
+    float mx = -INFINITY;
+    ft2[nb] = -INFINITY;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const f32x4_t iw = *reinterpret_cast<const f32x4_t*>(iws + 32 * wave + 8 * g + 4 * half);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float c = acc[nb][4 * g + e] * ixr[nb] * iw[e];
+        float f2 = c * s2;
+        if (jb + 8 * g + e >= K) f2 = -INFINITY;
+        if (filt && c > tau) f2 = -INFINITY;
+        if (yh >= 0 && tpos == 8 * g + e) {
+          f2 = -INFINITY;   // its margined logit takes part in the maximum and the sum only
+          const float ft = target_logit(mg, c);
+          tgt[n] = ft;
+          tgtc[n] = c;
+          ft2[nb] = ft * kLog2e;
+        }
+        acc[nb][4 * g + e] = f2;
+        mx = fmaxf(mx, f2);
+      }
+    }
+    mx = fmaxf(mx, ft2[nb]);
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    if (half == 0) redm[wave][32 * nb + l32] = mx;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int nb = 0; nb < 2; ++nb) {
+    const int r = 32 * nb + l32;
+    const float mx = fmaxf(fmaxf(redm[0][r], redm[1][r]), fmaxf(redm[2][r], redm[3][r]));
+    const float mref = mx == -INFINITY ? 0.0f : mx;
+    float sm = 0.0f;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      float ev[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        ev[e] = __builtin_amdgcn_exp2f(acc[nb][4 * g + e] - mref);
+        sm += ev[e];
+      }
+      uint2 packed;
+      packed.x = pack_f16x2(ev[0], ev[1]);
+      packed.y = pack_f16x2(ev[2], ev[3]);
+      *reinterpret_cast<uint2*>(xs + r * kFwdBM + 8 * ((4 * wave + g) ^ (r & 15)) + 4 * half) =
+          packed;
+    }
+    sm += __builtin_amdgcn_exp2f(ft2[nb] - mref);
+    sm += __shfl_xor(sm, 32, 64);
+    if (half == 0) reds[wave][r] = sm;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kNarrowRows / 16; ++u) {
+    const int r = 16 * wave + 4 * u + (lane >> 4), b = lane & 15;
+    const u32x4_t v = *reinterpret_cast<const u32x4_t*>(xs + r * kFwdBM + 8 * (b ^ (r & 15)));
+    if (n0 + r < B)
+      __builtin_nontemporal_store(
+          v, reinterpret_cast<u32x4_t*>(lbuf + (int64_t)(n0 + r) * ld_cos + j0 + 8 * b));
+  }
+  if (tid < kNarrowRows && n0 + tid < B) {
+    const int r = tid, n = n0 + r;
+    const float mx = fmaxf(fmaxf(redm[0][r], redm[1][r]), fmaxf(redm[2][r], redm[3][r]));
+    gmax[ct * ld_g + n] = mx == -INFINITY ? 0.0f : mx;
+    stats[(int64_t)n * n_ctiles + ct] =
+        make_float2(mx, (reds[0][r] + reds[1][r]) + (reds[2][r] + reds[3][r]));
+  }
+}
+
 // Merge the per-tile (max, sum) pairs of each row (in base 2 or e): lse_n, the
 // row's loss term and, by the workgroup that arrives last, the batch mean of
 // the loss terms.  TPR threads per row, one pass over the row's pairs: each
@@ -652,15 +826,37 @@ hipError_t launch_forward(const StepArgs& a, const StepWs& w, hipStream_t stream
   if (e != hipSuccess) return e;
   const int B = (int)a.B, d = (int)a.d;
   Margin mg{a.s, a.m, cosf(a.m), sinf(a.m), a.margin};
-  const int n_rt = (int)ceil_div(B, kFwdBN);
+  // Narrow tiles while all of them run at once, two per CU (512 on 256 CUs):
+  // beyond, their second round costs more than the pipelined tile (d = 512, us
+  // pipelined / narrow: |S| = 10,000, B = 128 20.0 / 13.8; 8,192, 512 21.1 /
+  // 19.6; 32,768, 128 25.5 / 23.9, and with 1,024 tiles 65,536, 128 39.2 / 41.3;
+  // 8,192, 1024 22.5 / 32.2).
+  const bool narrow = w.n_ctiles * ceil_div(B, kNarrowRows) <= 512;
+  const int n_rt = (int)ceil_div(B, narrow ? kNarrowRows : kFwdBN);
   const int64_t n_tiles = w.n_ctiles * n_rt;
   const int64_t per_xcd = ceil_div(n_tiles, 8);
   const unsigned grid = (unsigned)(8 * per_xcd);
   timing_start(2, stream);
-  if (a.dtype == 1)
+  if (narrow) {
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(grid), dim3(kFwdThreads), 0, stream, (const uint16_t*)a.X,
+                         (const uint16_t*)a.W, w.act_pad, a.n_active, a.labels_mapped, w.inv_x,
+                         w.inv_w, w.inv_w_max, B, w.ld_cos, w.n_ctiles, n_rt, n_tiles, per_xcd, mg,
+                         a.tau, (uint16_t*)w.lbuf, w.stats, w.tgt, w.tgtc, w.gmax, w.ld_g);
+    };
+    auto go_d = [&](auto tag) {
+      using Tag = decltype(tag);
+      if (d == 128) go(k_fwd16n<Tag, 128>);
+      else if (d == 256) go(k_fwd16n<Tag, 256>);
+      else go(k_fwd16n<Tag, 512>);
+    };
+    if (a.dtype == 1) go_d(Bf16Tag{});
+    else go_d(F16Tag{});
+  } else if (a.dtype == 1) {
     launch_fwd16<Bf16Tag>(d, grid, stream, a, w, B, n_rt, n_tiles, per_xcd, mg);
-  else
+  } else {
     launch_fwd16<F16Tag>(d, grid, stream, a, w, B, n_rt, n_tiles, per_xcd, mg);
+  }
   timing_stop(2, stream);
   return launch_lse(a, w, w.n_ctiles, kFwdClassTile, true, stream);
 }

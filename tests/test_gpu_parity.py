@@ -349,12 +349,13 @@ def test_feature_gradient_splits(dev, B, C, r, d, dtype):
                                             (512, "bf16", True), (512, "f16", False)])
 def test_class_tiles_agree(dev, d, dtype, master):
     """The class-gradient tiles of 128, 64 and 32 classes give a class the same
-    momentum row bit for bit.  A shard of 256 full tiles and a last round of few
-    classes, against shards of some of its classes (whole 128-class groups),
-    whose tiles are others, given its row log-sum-exp."""
+    momentum row bit for bit.  A shard of more than a round of 128-class tiles, against
+    shards of some of its classes (whole 128-class groups), whose tiles are
+    others, given its row log-sum-exp."""
     from _gpu_util import make_problem
-    B, n_cu = 70, torch.cuda.get_device_properties(dev).multi_processor_count
-    C = 128 * n_cu + 66 * 128 + 33              # a round of 128-class tiles, then 64
+    # One row tile of 64 (so that every shard's forward is the narrow one).
+    B, n_cu = 60, torch.cuda.get_device_properties(dev).multi_processor_count
+    C = 128 * n_cu + 66 * 128 + 33
     Xd, Wd, Md, Pd, Ld = make_problem(B, d, C, dtype, 66, master=master, device=dev)
     Ld[3:9] = Ld[2]                             # rows of one class
 
@@ -381,6 +382,19 @@ def test_class_tiles_agree(dev, d, dtype, master):
         # without the fp32 rounding before: at most one unit in the last place.
         ulp = 2.0 ** -10 if dtype == "f16" else 0.0
         assert torch.all((w.float() - W[lo:hi].float()).abs() <= ulp * W[lo:hi].float().abs())
+
+
+@pytest.mark.parametrize("B,d,K,dtype,tau", [
+    (512, 256, 8192, "f16", 0.4),     # 512 narrow forward tiles (64 rows), the most they are used for
+    (513, 256, 8192, "f16", 0.4),     # one row tile more: the 256-row kernel
+    (64, 512, 65409, "bf16", None),   # 512 class tiles, one class in the last: narrow
+    (65, 512, 32769, "bf16", 0.4),    # 257 class tiles of two row tiles each: the 256-row kernel
+])
+def test_forward_tile_widths(dev, B, d, K, dtype, tau):
+    """Both forward kernels around the line between them: ragged tiles, the
+    PFC* filter, rows whose label is outside the shard."""
+    _case(dev, B, d, K, 1.0, dtype, "arcface", 0.5, seed=67, class_offset=100,
+          label_span=(0, K + 200), tau=tau, conflicts=4, random_m=False)
 
 
 # PFC* conflict filter (Sec. 3.3.4, Eq. noise_filtering): some rows sit near
