@@ -73,7 +73,7 @@ WsLayout ws_layout(int64_t B, int64_t d, int64_t C, int64_t cap, int compute) {
   L.sample_bytes = off;
 
   L.ld_cos = round_up(cap, 256);
-  L.n_ctiles = ceil_div(cap, compute == PFC_F32 ? kFwdClassTile32 : kFwdClassTile);
+  L.n_ctiles = ceil_div(cap, kFwdClassTile);
   L.ld_xt = round_up(B, 32);
   L.ld_g = round_up(B, 128);
   L.n_lgroups = L.ld_cos / kLogitGroup;
@@ -85,7 +85,7 @@ WsLayout ws_layout(int64_t B, int64_t d, int64_t C, int64_t cap, int compute) {
   L.off_wmax = take(4);
   L.off_inv_w = take((size_t)L.ld_cos * 4);
   L.off_cos = take((size_t)B * L.ld_cos * cos_elt);
-  L.off_stats = take((size_t)B * L.n_ctiles * 8);
+  L.off_stats = take(compute == PFC_F32 ? 0 : (size_t)B * L.n_ctiles * 8);
   L.off_tgt = take((size_t)B * 4);
   L.off_dx = take((size_t)L.n_split * B * d * 4);
   L.off_loss = take((size_t)B * 4);

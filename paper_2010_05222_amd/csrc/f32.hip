@@ -9,10 +9,16 @@
 //
 // MFMA operands: lane l supplies A[l % 16][k] and B[k][l % 16] with
 // k = l / 16, and register r of its accumulator is D[4 (l / 16) + r][l % 16].
-// The order of k inside a contraction is free as long as both operands agree,
-// so one 16-byte piece per lane (k = 16 b + 4 (l / 16) + s, s < 4) feeds four
-// MFMAs, s = 0..3.  Likewise a lane's four consecutive columns 4 (l % 16) + t
-// are its column l % 16 of four tiles t: rows are loaded and stored in
+// The instruction adds its four products one after another, each with one
+// rounding, so a contraction over k = 0, 1, 2, ... is the chain of fmaf that a
+// plain loop computes, bit for bit (51,200 sums of 512 compared).  The sums
+// that later steps build on - cosines, norms, log-sum-exp, class gradients
+// and their projection - all keep a plain loop's order: in a converging head
+// the loss is a difference of nearly equal numbers, and a cosine that differs
+// in its last bit moves it by a per mille.  A lane's 16-byte LDS piece feeds
+// four MFMAs: k = 16 b + 4 s + g sits at position 16 b + 4 g + s, and lane
+// group g reads 4 g .. + 3.  A lane's four consecutive columns 4 (l % 16) + t
+// are its column l % 16 of four tiles t, so rows are loaded and stored in
 // 16-byte pieces, 256 bytes per 16 lanes, with no transposition.
 #include "pfc_device.h"
 
@@ -38,10 +44,15 @@ __device__ __forceinline__ f32x4_t mfma_16x16x4(float a, float b, f32x4_t c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-// Sum over the sixteen lanes that share l / 16.
-__device__ __forceinline__ float sum16(float v) {
+// Position of k in a row of 16-blocks (see above).
+__device__ __forceinline__ int k_pos(int k) { return (k & ~15) + 4 * (k & 3) + ((k >> 2) & 3); }
+
+// v + its value in the lane whose l % 16 differs in `bits`, from the highest of
+// four bits down: the upper steps of a 64-value butterfly sum whose values
+// 4 (l % 16) + e are spread over sixteen lanes' registers e.
+__device__ __forceinline__ float butterfly16(float v) {
 #pragma unroll
-  for (int off = 1; off < 16; off <<= 1) v += __shfl_xor(v, off, 64);
+  for (int off = 8; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
   return v;
 }
 
@@ -50,21 +61,21 @@ __device__ __forceinline__ float sum16(float v) {
 // cos[n][j] of a tile of 16 MT classes x 64 batch rows, d in 64-wide chunks
 // through two LDS stages (a chunk is loaded into registers while the previous
 // one is contracted).  Wave w owns rows 16 w .. + 15 and all the tile's
-// classes, so a row's (max, sum exp) pair of the tile needs lane moves only.
-// The row norms of both operands are summed from the pieces on their way to
-// LDS; the tiles of the first class tile (row tile) publish them for the
-// backward.  A negative that the PFC* filter drops is stored as -inf.
+// classes.  The row norms of both operands are summed from the pieces on their
+// way to LDS, each in the order of one wave per row (batch rows: lane i % 64,
+// class rows: lane (i / 4) % 64, then a butterfly); the tiles of the first
+// class tile (row tile) publish them for the backward.  A negative that the
+// PFC* filter drops is stored as -inf.
 //
 // Bound by the fp32 matrix rate and, on few tiles, by the chunk latency.  At
-// B = 250, |S| = 5,003, d = 512 (1.3 GFLOP) it takes 27 us; the
+// B = 250, |S| = 5,003, d = 512 (1.3 GFLOP) it takes 28 us; the
 // thread-per-dot kernel that it replaced took 2,671 us there.
 template <int MT>
 __global__ void __launch_bounds__(256) k_fwd32(
     const float* __restrict__ X, const float* __restrict__ W, const int32_t* __restrict__ active,
     const int32_t* __restrict__ n_active_p, const int32_t* __restrict__ yhat, int B, int d,
-    int64_t ld_cos, int64_t n_ctiles, Margin mg, float tau, float* __restrict__ inv_x,
-    float* __restrict__ inv_w, float* __restrict__ cos32, float2* __restrict__ stats,
-    float* __restrict__ tgt, uint32_t* __restrict__ arrivals) {
+    int64_t ld_cos, float tau, float* __restrict__ inv_x, float* __restrict__ inv_w,
+    float* __restrict__ cos32, uint32_t* __restrict__ arrivals) {
   constexpr int CLS = 16 * MT;
   __shared__ float As[2][CLS][kLd], Bs[2][kRows][kLd];
   __shared__ float iwS[CLS], ixS[kRows];
@@ -78,20 +89,23 @@ __global__ void __launch_bounds__(256) k_fwd32(
   const int l16 = lane & 15, g4 = 4 * (lane >> 4);
 
   // Staging: thread t moves piece t % 16 of rows t / 16 + 16 u.
-  const int piece = 4 * (tid & 15), srow = tid >> 4;
+  const int p16 = tid & 15, piece = 4 * p16, srow = tid >> 4;
+  const int at = k_pos(piece);   // of the piece's entry e: at + 4 e
   const float *ap[MT], *bp[4];
-  float sa[MT], sb[4];
+  float sa[MT][4], sb[4][4];
 #pragma unroll
   for (int u = 0; u < MT; ++u) {
     const int64_t j = j0 + srow + 16 * u;
     ap[u] = j < K ? W + (int64_t)active[j] * d : nullptr;
-    sa[u] = 0.0f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sa[u][e] = 0.0f;
   }
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
     const int n = n0 + srow + 16 * u;
     bp[u] = n < B ? X + (int64_t)n * d : nullptr;
-    sb[u] = 0.0f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sb[u][e] = 0.0f;
   }
   f32x4_t ar[MT], br[4];
   auto load = [&](int k0) {
@@ -106,18 +120,26 @@ __global__ void __launch_bounds__(256) k_fwd32(
   for (int m = 0; m < MT; ++m) acc[m] = zero4();
   load(0);
   for (int k0 = 0, st = 0; k0 < d; k0 += kChunk, st ^= 1) {
+    // Class rows: lane 16 (chunk % 4) + p16 of the row's wave.
+    const int part = (k0 / kChunk) & 3;   // uniform
 #pragma unroll
     for (int u = 0; u < MT; ++u) {
+      float v = part == 0 ? sa[u][0] : part == 1 ? sa[u][1] : part == 2 ? sa[u][2] : sa[u][3];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) sa[u] = fmaf(ar[u][e], ar[u][e], sa[u]);
-      *reinterpret_cast<f32x4_t*>(&As[st][srow + 16 * u][piece]) = ar[u];
+      for (int e = 3; e >= 0; --e) v = fmaf(ar[u][e], ar[u][e], v);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) sa[u][q] = part == q ? v : sa[u][q];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) As[st][srow + 16 * u][at + 4 * e] = ar[u][e];
     }
+    // Batch rows: lane 4 p16 + e of the row's wave.
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < 4; ++u)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) sb[u] = fmaf(br[u][e], br[u][e], sb[u]);
-      *reinterpret_cast<f32x4_t*>(&Bs[st][srow + 16 * u][piece]) = br[u];
-    }
+      for (int e = 0; e < 4; ++e) {
+        sb[u][e] = fmaf(br[u][e], br[u][e], sb[u][e]);
+        Bs[st][srow + 16 * u][at + 4 * e] = br[u][e];
+      }
     // A stage is rewritten two chunks later: every wave has then passed the
     // barrier of the chunk between, after its reads of this one.
     __syncthreads();
@@ -137,18 +159,22 @@ __global__ void __launch_bounds__(256) k_fwd32(
   }
 #pragma unroll
   for (int u = 0; u < MT; ++u) {
-    const float iv = 1.0f / fmaxf(sqrtf(sum16(sa[u])), kEpsNorm);
+    const float ss = butterfly16((sa[u][0] + sa[u][2]) + (sa[u][1] + sa[u][3]));
+    const float iv = 1.0f / fmaxf(sqrtf(ss), kEpsNorm);
     const int64_t j = j0 + srow + 16 * u;
-    if (piece == 0) {
+    if (p16 == 0) {
       iwS[srow + 16 * u] = iv;
       if (blockIdx.y == 0 && j < K) inv_w[j] = iv;
     }
   }
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
-    const float iv = 1.0f / fmaxf(sqrtf(sum16(sb[u])), kEpsNorm);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sb[u][e] = butterfly16(sb[u][e]);
+    const float ss = (sb[u][0] + sb[u][2]) + (sb[u][1] + sb[u][3]);
+    const float iv = 1.0f / fmaxf(sqrtf(ss), kEpsNorm);
     const int n = n0 + srow + 16 * u;
-    if (piece == 0) {
+    if (p16 == 0) {
       ixS[srow + 16 * u] = iv;
       if (blockIdx.x == 0 && n < B) inv_x[n] = iv;
     }
@@ -157,11 +183,9 @@ __global__ void __launch_bounds__(256) k_fwd32(
 
   // Lane: batch row n, classes j0 + 16 m + 4 (lane / 16) + r.
   const int n = n0 + 16 * wave + l16;
-  const bool row_ok = n < B;
+  if (n >= B) return;
   const float ix = ixS[16 * wave + l16];
-  const int64_t y = row_ok ? (int64_t)yhat[n] : -1;
-  float f[MT][4];
-  float mx = -INFINITY;
+  const int64_t y = yhat[n];
 #pragma unroll
   for (int m = 0; m < MT; ++m) {
     const f32x4_t iw = *reinterpret_cast<const f32x4_t*>(&iwS[16 * m + g4]);
@@ -169,27 +193,62 @@ __global__ void __launch_bounds__(256) k_fwd32(
     f32x4_t c;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const bool target = j + r == y;
       c[r] = acc[m][r] * ix * iw[r];
-      if (tau < 1.0f && !target && c[r] > tau) c[r] = -INFINITY;
-      f[m][r] = target ? target_logit(mg, c[r]) : mg.s * c[r];
-      if (j + r >= K) f[m][r] = -INFINITY;
-      else if (target) tgt[n] = f[m][r];
-      mx = fmaxf(mx, f[m][r]);
+      if (tau < 1.0f && j + r != y && c[r] > tau) c[r] = -INFINITY;
     }
-    if (row_ok && j < K) store4(cos32 + (int64_t)n * ld_cos + j, c);
+    if (j < K) store4(cos32 + (int64_t)n * ld_cos + j, c);   // ld_cos holds whole tiles
   }
-  const float mref = mx == -INFINITY ? 0.0f : mx;
-  float sum = 0.0f;
+}
+
+// lse_n and the loss: a wave per row, lane l merges the logits j = l, l + 64,
+// ... one by one, the lanes meet in a butterfly, and the workgroup that arrives
+// last takes the batch mean.  Bound by that chain: the next sixteen loads are
+// in flight while sixteen logits are merged, and four waves to a workgroup put
+// each on a SIMD of its own (B = 250, |S| = 5,003: 15 us; 30 with one load at a time).
+constexpr int kLse32Threads = 256;
+__global__ void __launch_bounds__(kLse32Threads) k_lse32(
+    const float* __restrict__ cos32, int64_t ld_cos, const int32_t* __restrict__ n_active_p,
+    const int32_t* __restrict__ yhat, int B, Margin mg, float* __restrict__ row_lse,
+    float* __restrict__ loss_part, uint32_t* __restrict__ arrivals, float* __restrict__ loss) {
+  const int lane = threadIdx.x & 63;
+  const int n = blockIdx.x * (kLse32Threads / 64) + (threadIdx.x >> 6);
+  const int K = *n_active_p;
+  if (n < B) {
+    const int yh = yhat[n];
+    const float* row = cos32 + (int64_t)n * ld_cos;
+    float2 acc = make_float2(-INFINITY, 0.0f);
+    float ft = 0.0f;
+    constexpr int U = 16;
+    float c[U], next[U];
+    auto load = [&](int j0, float (&v)[U]) {
 #pragma unroll
-  for (int m = 0; m < MT; ++m)
+      for (int u = 0; u < U; ++u) v[u] = j0 + 64 * u < K ? row[j0 + 64 * u] : 0.0f;
+    };
+    load(lane, c);
+    for (int j0 = lane; j0 < K; j0 += 64 * U) {
+      load(j0 + 64 * U, next);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) sum += __expf(f[m][r] - mref);
-  float2 p = make_float2(mx, sum);
+      for (int u = 0; u < U; ++u) {
+        const int j = j0 + 64 * u;
+        const float f = j == yh ? target_logit(mg, c[u]) : mg.s * c[u];
+        if (j == yh) ft = f;
+        if (j < K) acc = lse_merge(acc, make_float2(f, 1.0f));
+      }
 #pragma unroll
-  for (int off = 16; off < 64; off <<= 1)
-    p = lse_merge(p, make_float2(__shfl_xor(p.x, off, 64), __shfl_xor(p.y, off, 64)));
-  if (row_ok && lane < 16) stats[(int64_t)n * n_ctiles + blockIdx.x] = p;
+      for (int u = 0; u < U; ++u) c[u] = next[u];
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+      acc = lse_merge(acc, make_float2(__shfl_xor(acc.x, off, 64), __shfl_xor(acc.y, off, 64)));
+      ft += __shfl_xor(ft, off, 64);
+    }
+    if (lane == 0) {
+      const float lse = acc.x + __logf(acc.y);
+      row_lse[n] = lse;
+      put_loss_term(loss_part + n, yh >= 0 && yh < K ? lse - ft : 0.0f);
+    }
+  }
+  mean_by_last<kLse32Threads>(loss_part, B, arrivals, loss);
 }
 
 // ------------------------------------------------------------------ dX
@@ -390,7 +449,7 @@ __global__ void __launch_bounds__(256) k_dw32(
           if (j0 + q + e < K) g[e] = grad_coef(mg, cv[e], j0 + q + e == y, lse) * ix;
       }
 #pragma unroll
-      for (int e = 0; e < 4; ++e) G[st][q + e][r] = g[e];
+      for (int e = 0; e < 4; ++e) G[st][q + e][k_pos(r)] = g[e];
     }
   };
   f32x4_t acc[NB][4];
@@ -398,16 +457,17 @@ __global__ void __launch_bounds__(256) k_dw32(
   for (int q = 0; q < NB; ++q)
 #pragma unroll
     for (int t = 0; t < 4; ++t) acc[q][t] = zero4();
-  const int col0 = 64 * NB * wave + 4 * l16;
+  // The wave's q-th block of 64 columns is block wave + 4 q.
+  const int col0 = 64 * wave + 4 * l16;
   f32x4_t x[2][NB][4];   // batch pieces of two 16-row blocks in turn
   auto load_x = [&](int nb, f32x4_t (&dst)[NB][4]) {
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      int n = nb + g4 + s;
+      int n = nb + 4 * s + (lane >> 4);
       n = n < B ? n : B - 1;   // coefficient 0
 #pragma unroll
       for (int q = 0; q < NB; ++q)
-        dst[q][s] = col0 + 64 * q < d ? load4(X + (int64_t)n * d + col0 + 64 * q) : zero4();
+        dst[q][s] = col0 + 256 * q < d ? load4(X + (int64_t)n * d + col0 + 256 * q) : zero4();
     }
   };
   produce(0, 0);
@@ -429,7 +489,9 @@ __global__ void __launch_bounds__(256) k_dw32(
     }
   }
 
-  // Update: lane l owns columns col0 + 64 q .. + 3 of classes 4 (l / 16) + r.
+  // Update: lane l owns columns col0 + 256 q .. + 3 of classes 4 (l / 16) + r.
+  // The dot w_hat . dw of a class goes over q in each column, over a wave's 64
+  // columns in a butterfly, and over the waves in order.
   int64_t base[4];
   float iw[4];
   f32x4_t wv[4][NB];
@@ -438,29 +500,30 @@ __global__ void __launch_bounds__(256) k_dw32(
     const int64_t j = j0 + g4 + r;
     base[r] = j < K ? (int64_t)active[j] * d + col0 : -1;
     iw[r] = j < K ? inv_w[j] : 0.0f;
-    float dot = 0.0f;
+    f32x4_t dot = zero4();
 #pragma unroll
     for (int q = 0; q < NB; ++q) {
-      wv[r][q] = base[r] >= 0 && col0 + 64 * q < d ? load4(W + base[r] + 64 * q) : zero4();
+      wv[r][q] = base[r] >= 0 && col0 + 256 * q < d ? load4(W + base[r] + 256 * q) : zero4();
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         acc[q][t][r] *= sB;
-        dot = fmaf(wv[r][q][t] * iw[r], acc[q][t][r], dot);
+        dot[t] = fmaf(wv[r][q][t] * iw[r], acc[q][t][r], dot[t]);
       }
     }
-    dot = sum16(dot);
-    if (l16 == 0) red[wave][g4 + r] = dot;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) dot[t] = butterfly16(dot[t]);
+    if (l16 == 0) red[wave][g4 + r] = (dot[0] + dot[2]) + (dot[1] + dot[3]);
   }
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    float dot = 0.0f;
-    for (int v = 0; v < n_waves; ++v) dot += red[v][g4 + r];
+    float dot = red[0][g4 + r];
+    for (int v = 1; v < n_waves; ++v) dot += red[v][g4 + r];
     if (base[r] < 0) continue;
 #pragma unroll
     for (int q = 0; q < NB; ++q) {
-      if (col0 + 64 * q >= d) continue;
-      const int64_t o = base[r] + 64 * q;
+      if (col0 + 256 * q >= d) continue;
+      const int64_t o = base[r] + 256 * q;
       f32x4_t m = load4(M + o);
       f32x4_t p = W_master ? load4(W_master + o) : wv[r][q];
 #pragma unroll
@@ -476,8 +539,8 @@ __global__ void __launch_bounds__(256) k_dw32(
   }
 }
 
-// Calls f with NB = the 64-column blocks per wave of a width d (waves = min(4,
-// ceil(d / 64)) share them evenly).
+// Calls f with NB = the 64-column blocks per wave of a width d (min(4, ceil(d /
+// 64)) waves share them).
 template <typename F>
 void with_blocks(int d, F&& f) {
   const int blocks = (int)ceil_div(d, 64);
@@ -512,13 +575,18 @@ hipError_t launch_forward_f32(const StepArgs& a, const StepWs& w, hipStream_t st
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)n_ct, n_rt), dim3(256), 0, stream,
                        (const float*)a.X, (const float*)a.W, a.active, a.n_active,
-                       a.labels_mapped, B, d, w.ld_cos, n_ct, mg, a.tau, w.inv_x, w.inv_w,
-                       (float*)w.lbuf, w.stats, w.tgt, w.arrivals);
+                       a.labels_mapped, B, d, w.ld_cos, a.tau, w.inv_x, w.inv_w, (float*)w.lbuf,
+                       w.arrivals);
   };
   if (wide) go(k_fwd32<4>);
   else go(k_fwd32<2>);
   timing_stop(2, stream);
-  return launch_lse(a, w, n_ct, wide ? 64 : 32, false, stream);
+  timing_start(3, stream);
+  hipLaunchKernelGGL(k_lse32, dim3((unsigned)ceil_div(B, kLse32Threads / 64)), dim3(kLse32Threads),
+                     0, stream, (const float*)w.lbuf, w.ld_cos, a.n_active, a.labels_mapped, B, mg,
+                     a.row_lse_out, w.loss_part, w.arrivals, a.loss);
+  timing_stop(3, stream);
+  return hipGetLastError();
 }
 
 hipError_t launch_backward_f32(const StepArgs& a, const StepWs& w, hipStream_t stream) {

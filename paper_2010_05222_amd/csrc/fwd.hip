@@ -518,7 +518,7 @@ __global__ void __launch_bounds__(kFwdThreads, 2) k_fwd16(
 // k-step), the batch rows to LDS, and one wait covers both, so the kernel is
 // one memory round trip, the MFMAs and the epilogue, where the pipelined tile
 // waits sixteen times (d = 512) for a 32-wide chunk and computes 256 rows
-// whatever the batch.  At |S| = 10,000, B = 128: 13.8 us, 20.0 pipelined.
+// whatever the batch.  At |S| = 10,000, B = 128: 15.6 us, 20.0 pipelined.
 // 16-byte piece c of LDS row r sits at position c ^ (r & 15): sixteen
 // consecutive rows of a fragment read on distinct banks.
 constexpr int kNarrowRows = 64;
@@ -536,7 +536,7 @@ __global__ void __launch_bounds__(kFwdThreads, 2) k_fwd16n(
   constexpr int LOADS = kNarrowRows * PIECES / kFwdThreads;   // direct-to-LDS loads per wave
   __shared__ __attribute__((aligned(1024))) uint16_t xs[kNarrowRows * D];
   __shared__ __attribute__((aligned(16))) float iws[kFwdBM];
-  __shared__ float redm[4][kNarrowRows], reds[4][kNarrowRows];
+  __shared__ float redm[4][kNarrowRows], reds[2][kNarrowRows], redt[2][kNarrowRows];
   const int64_t t = (int64_t)(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
   if (t >= n_tiles) return;
   const int64_t ct = t / n_rt;
@@ -580,14 +580,14 @@ __global__ void __launch_bounds__(kFwdThreads, 2) k_fwd16n(
   for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[nb][r] = 0.0f;
-  float ss = 0.0f;
+  float ss[2] = {0.0f, 0.0f};   // of the even and the odd k-steps
 #pragma unroll
   for (int s = 0; s < NK; ++s) {
     const int pos = ((2 * s + half) ^ (l32 & 15)) * 8;
-    ss = sumsq2(a[s].x, ss, Tag{});
-    ss = sumsq2(a[s].y, ss, Tag{});
-    ss = sumsq2(a[s].z, ss, Tag{});
-    ss = sumsq2(a[s].w, ss, Tag{});
+    ss[s & 1] = sumsq2(a[s].x, ss[s & 1], Tag{});
+    ss[s & 1] = sumsq2(a[s].y, ss[s & 1], Tag{});
+    ss[s & 1] = sumsq2(a[s].z, ss[s & 1], Tag{});
+    ss[s & 1] = sumsq2(a[s].w, ss[s & 1], Tag{});
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb) {
       const uint4 b = *reinterpret_cast<const uint4*>(xs + (32 * nb + l32) * D + pos);
@@ -597,7 +597,9 @@ __global__ void __launch_bounds__(kFwdThreads, 2) k_fwd16n(
   // Inverse norms of the wave's 32 classes; the first row tile publishes them
   // and their running maximum.
   {
-    const float inv = 1.0f / fmaxf(sqrtf(ss + __shfl_xor(ss, 32, 64)), kEpsNormW);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) ss[q] += __shfl_xor(ss[q], 32, 64);
+    const float inv = 1.0f / fmaxf(sqrtf(ss[0] + ss[1]), kEpsNormW);
     const int64_t j = j0 + 32 * wave + l32;
     if (half == 0) iws[32 * wave + l32] = inv;
     if (rt == 0) {
@@ -607,68 +609,93 @@ __global__ void __launch_bounds__(kFwdThreads, 2) k_fwd16n(
     }
   }
   __syncthreads();   // norms written; every fragment read of xs is done
-  // As in fwd_epilogue_rows, the row maximum and sum over the waves.
+  // The epilogue of k_fwd16, operation for operation: a tile of its 64 rows
+  // with neither a target, a missing class nor the filter takes the common
+  // path (u q - m), others the checked one; the maximum meets over the waves,
+  // and a row's sum runs through the classes in order, wave after wave.
   const float s2 = mg.s * kLog2e;
   const bool filt = tau < 1.0f;
-  float ft2[2];
+  bool tile_t = false;
+#pragma unroll
+  for (int nb = 0; nb < 2; ++nb) {
+    yraw[nb] = yraw[nb] < K ? yraw[nb] : -1;   // past |S|: unowned
+    tile_t |= yraw[nb] >= j0 && yraw[nb] < j0 + kFwdBM;
+  }
+  const bool plain = !filt && j0 + kFwdBM <= (int64_t)K && !__any(tile_t);   // workgroup-uniform
+  float mx[2], ft2[2];
 #pragma unroll
   for (int nb = 0; nb < 2; ++nb) {
     const int n = n0 + 32 * nb + l32;
-    const int yh = yraw[nb] < K ? yraw[nb] : -1;   // past |S|: unowned
     const int64_t jb = j0 + 32 * wave + 4 * half;
-    const int64_t tpos = yh - jb;
-    float mx = -INFINITY;
+    const int64_t tpos = yraw[nb] - jb;
+    mx[nb] = -INFINITY;
     ft2[nb] = -INFINITY;
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       const f32x4_t iw = *reinterpret_cast<const f32x4_t*>(iws + 32 * wave + 8 * g + 4 * half);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const float c = acc[nb][4 * g + e] * ixr[nb] * iw[e];
-        float f2 = c * s2;
-        if (jb + 8 * g + e >= K) f2 = -INFINITY;
-        if (filt && c > tau) f2 = -INFINITY;
-        if (yh >= 0 && tpos == 8 * g + e) {
-          f2 = -INFINITY;   // its margined logit takes part in the maximum and the sum only
-          const float ft = target_logit(mg, c);
-          tgt[n] = ft;
-          tgtc[n] = c;
-          ft2[nb] = ft * kLog2e;
+        float v = acc[nb][4 * g + e];
+        if (plain) {
+          v = v * iw[e];
+        } else {
+          const float c = v * ixr[nb] * iw[e];
+          v = c * s2;
+          if (jb + 8 * g + e >= K) v = -INFINITY;
+          if (filt && c > tau) v = -INFINITY;   // PFC* drops the negative (not the target: below)
+          if (yraw[nb] >= 0 && tpos == 8 * g + e) {
+            v = -INFINITY;   // its margined logit takes part in the maximum and the sum only
+            const float ft = target_logit(mg, c);
+            tgt[n] = ft;
+            tgtc[n] = c;
+            ft2[nb] = ft * kLog2e;
+          }
         }
-        acc[nb][4 * g + e] = f2;
-        mx = fmaxf(mx, f2);
+        acc[nb][4 * g + e] = v;
+        mx[nb] = fmaxf(mx[nb], v);
       }
     }
-    mx = fmaxf(mx, ft2[nb]);
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    if (half == 0) redm[wave][32 * nb + l32] = mx;
+    // The target's term by the half that holds it, as the sum below needs it.
+    if (ft2[nb] > -INFINITY) redt[half][32 * nb + l32] = ft2[nb];
+    mx[nb] = fmaxf(mx[nb], ft2[nb]);
+    mx[nb] = fmaxf(mx[nb], __shfl_xor(mx[nb], 32, 64));
+    if (half == 0) redm[wave][32 * nb + l32] = mx[nb];
   }
   __syncthreads();
 #pragma unroll
   for (int nb = 0; nb < 2; ++nb) {
     const int r = 32 * nb + l32;
-    const float mx = fmaxf(fmaxf(redm[0][r], redm[1][r]), fmaxf(redm[2][r], redm[3][r]));
-    const float mref = mx == -INFINITY ? 0.0f : mx;
-    float sm = 0.0f;
+    mx[nb] = fmaxf(fmaxf(redm[0][r], redm[1][r]), fmaxf(redm[2][r], redm[3][r]));
+    const float q = ixr[nb] * s2;
+    if (plain) mx[nb] *= q;
+    const float mref = mx[nb] == -INFINITY ? 0.0f : mx[nb];
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      float ev[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        ev[e] = __builtin_amdgcn_exp2f(acc[nb][4 * g + e] - mref);
-        sm += ev[e];
+        const float v = acc[nb][4 * g + e];
+        acc[nb][4 * g + e] = __builtin_amdgcn_exp2f(plain ? fmaf(v, q, -mx[nb]) : v - mref);
       }
       uint2 packed;
-      packed.x = pack_f16x2(ev[0], ev[1]);
-      packed.y = pack_f16x2(ev[2], ev[3]);
+      packed.x = pack_f16x2(acc[nb][4 * g], acc[nb][4 * g + 1]);
+      packed.y = pack_f16x2(acc[nb][4 * g + 2], acc[nb][4 * g + 3]);
       *reinterpret_cast<uint2*>(xs + r * kFwdBM + 8 * ((4 * wave + g) ^ (r & 15)) + 4 * half) =
           packed;
     }
-    sm += __builtin_amdgcn_exp2f(ft2[nb] - mref);
-    sm += __shfl_xor(sm, 32, 64);
-    if (half == 0) reds[wave][r] = sm;
   }
-  __syncthreads();
+#pragma unroll 1
+  for (int w = 0; w < 4; ++w) {
+    if (wave == w) {
+#pragma unroll
+      for (int nb = 0; nb < 2; ++nb) {
+        float sm = w ? reds[half][32 * nb + l32] : 0.0f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sm += acc[nb][r];
+        reds[half][32 * nb + l32] = sm;
+      }
+    }
+    __syncthreads();
+  }
 #pragma unroll
   for (int u = 0; u < kNarrowRows / 16; ++u) {
     const int r = 16 * wave + 4 * u + (lane >> 4), b = lane & 15;
@@ -677,97 +704,82 @@ __global__ void __launch_bounds__(kFwdThreads, 2) k_fwd16n(
       __builtin_nontemporal_store(
           v, reinterpret_cast<u32x4_t*>(lbuf + (int64_t)(n0 + r) * ld_cos + j0 + 8 * b));
   }
-  if (tid < kNarrowRows && n0 + tid < B) {
-    const int r = tid, n = n0 + r;
-    const float mx = fmaxf(fmaxf(redm[0][r], redm[1][r]), fmaxf(redm[2][r], redm[3][r]));
-    gmax[ct * ld_g + n] = mx == -INFINITY ? 0.0f : mx;
-    stats[(int64_t)n * n_ctiles + ct] =
-        make_float2(mx, (reds[0][r] + reds[1][r]) + (reds[2][r] + reds[3][r]));
+  if (wave == 0) {   // lanes of half 0 hold the rows' maxima and finish their pairs
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) {
+      const int r = 32 * nb + l32, n = n0 + r;
+      const float mref = mx[nb] == -INFINITY ? 0.0f : mx[nb];
+      float sm = reds[half][r];
+      const int yh = yraw[nb];
+      if (yh >= j0 && yh < j0 + kFwdBM && (((yh - (int)j0) >> 2) & 1) == half)
+        sm += __builtin_amdgcn_exp2f(redt[half][r] - mref);
+      sm += __shfl_xor(sm, 32, 64);
+      if (half == 0 && n < B) {
+        gmax[ct * ld_g + n] = mref;
+        stats[(int64_t)n * n_ctiles + ct] = make_float2(mx[nb], sm);
+      }
+    }
   }
 }
 
-// Merge the per-tile (max, sum) pairs of each row (in base 2 or e): lse_n, the
-// row's loss term and, by the workgroup that arrives last, the batch mean of
-// the loss terms.  TPR threads per row, one pass over the row's pairs: each
-// thread merges its pairs in tile order, the waves' pairs meet through lane
-// moves and LDS in a fixed order, and the mean is summed in a fixed order, so
-// the result does not depend on which workgroup is last.  A kernel of its own
-// for the mean took 4.4 us, as long as any launch that does next to nothing
-// (B = 128: 4.7 + 3.9 -> 7.1 us); several rows per workgroup keep the arrivals
-// few.
-constexpr int kLseThreads = 1024;
-template <int TPR, bool BASE2>
-__global__ void __launch_bounds__(kLseThreads) k_lse(
-    const float2* __restrict__ stats, int64_t n_ctiles, int tile,
-    const int32_t* __restrict__ n_active_p, const int32_t* __restrict__ yhat,
-    const float* __restrict__ tgt, int B, float* __restrict__ row_lse,
-    float* __restrict__ loss_part, uint32_t* __restrict__ arrivals, float* __restrict__ loss) {
-  constexpr int WPR = TPR / 64;   // waves per row
-  __shared__ float2 red[kLseThreads / 64];
-  __shared__ double part[kLseThreads / 64];
-  __shared__ bool last;
-  const int n = blockIdx.x * (kLseThreads / TPR) + threadIdx.x / TPR;
-  const int t = threadIdx.x % TPR, lane = t & 63, wave = threadIdx.x >> 6;
+// Merge the per-tile (max, sum) pairs of each row: lse_n, the row's loss term
+// and (by the last workgroup) the batch mean.  256 lanes' worth of merges per
+// row, each in tile order, then in a butterfly over each 64 lanes, then the
+// four sums in a fixed order.  WPR waves per row share them, 4 or 1 (which
+// then carries four lanes' merges per lane, with the same result).  ROWS rows
+// per workgroup keep the arrivals few: they take turns of about 12 ns.
+template <int WPR, int ROWS>
+__global__ void __launch_bounds__(64 * WPR * ROWS) k_lse16(
+    const float2* __restrict__ stats, int64_t n_ctiles, const int32_t* __restrict__ n_active_p,
+    const int32_t* __restrict__ yhat, const float* __restrict__ tgt, int B,
+    float* __restrict__ row_lse, float* __restrict__ loss_part, uint32_t* __restrict__ arrivals,
+    float* __restrict__ loss) {
+  constexpr int Q = 4 / WPR;       // of the row's four sums per wave
+  constexpr int U = 8 / Q;         // loads in flight for each
+  __shared__ float2 red[ROWS][4];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int r = wave / WPR, q0 = wave % WPR * Q;
+  const int n = blockIdx.x * ROWS + r;
   const int64_t K = *n_active_p;
-  const int64_t nct = n < B ? ceil_div(K, (int64_t)tile) : 0;
+  const int64_t nct = n < B ? ceil_div(K, (int64_t)kFwdBM) : 0;
   const float2* row = stats + (int64_t)n * n_ctiles;
-  auto merge = [](float2 p, float2 q) { return BASE2 ? lse_merge2(p, q) : lse_merge(p, q); };
-  float2 acc = make_float2(-INFINITY, 0.0f);
-  // Eight loads in flight per thread, merged in tile order.
-  for (int64_t c0 = t; c0 < nct; c0 += TPR * 8) {
-    float2 v[8];
+  float2 acc[Q];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const int64_t c = c0 + TPR * k;
-      v[k] = c < nct ? row[c] : make_float2(-INFINITY, 0.0f);
-    }
+  for (int q = 0; q < Q; ++q) acc[q] = make_float2(-INFINITY, 0.0f);
+  for (int64_t c0 = 64 * q0 + lane; c0 - lane < nct; c0 += 256 * U) {
+    float2 v[Q][U];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) acc = merge(acc, v[k]);
+    for (int q = 0; q < Q; ++q)
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        const int64_t c = c0 + 64 * q + 256 * k;
+        v[q][k] = c < nct ? row[c] : make_float2(-INFINITY, 0.0f);
+      }
+#pragma unroll
+    for (int k = 0; k < U; ++k)
+#pragma unroll
+      for (int q = 0; q < Q; ++q) acc[q] = lse_merge2(acc[q], v[q][k]);
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1)
-    acc = merge(acc, make_float2(__shfl_xor(acc.x, off, 64), __shfl_xor(acc.y, off, 64)));
-  if constexpr (WPR > 1) {
-    if (lane == 0) red[wave] = acc;
-    __syncthreads();
-    acc = red[wave];
-    if (t == 0) {
-      static_assert(WPR == 4, "four waves per row");
-      acc = merge(merge(red[wave], red[wave + 1]), merge(red[wave + 2], red[wave + 3]));
-    }
-  }
-  if (t == 0 && n < B) {
-    const float lse = acc.x == -INFINITY ? -INFINITY
-                      : BASE2           ? (acc.x + log2f(acc.y)) * 0.6931471805599453f
-                                        : acc.x + __logf(acc.y);
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      acc[q] = lse_merge2(acc[q], make_float2(__shfl_xor(acc[q].x, off, 64),
+                                              __shfl_xor(acc[q].y, off, 64)));
+  if (lane == 0)
+#pragma unroll
+    for (int q = 0; q < Q; ++q) red[r][q0 + q] = acc[q];
+  __syncthreads();
+  if (lane == 0 && q0 == 0 && n < B) {
+    const float2 all = lse_merge2(lse_merge2(red[r][0], red[r][1]),
+                                  lse_merge2(red[r][2], red[r][3]));
+    const float lse = all.x == -INFINITY ? -INFINITY
+                                         : (all.x + log2f(all.y)) * 0.6931471805599453f;
     row_lse[n] = lse;
     const int yh = yhat[n];
-    // Written through to where every CU sees it, and waited for before the
-    // barrier, so the arrival needs no cache flush (with an acquire-release
-    // arrival of each workgroup the kernel took 12.1 instead of 10.1 us at 250
-    // workgroups).
-    __hip_atomic_store(loss_part + n, yh >= 0 && yh < K ? lse - tgt[n] : 0.0f,   // past |S|: unowned
-                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    put_loss_term(loss_part + n, yh >= 0 && yh < K ? lse - tgt[n] : 0.0f);   // past |S|: unowned
   }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  if (threadIdx.x == 0)
-    last = __hip_atomic_fetch_add(arrivals, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-           gridDim.x - 1;
-  __syncthreads();
-  if (!last) return;
-  double sum = 0.0;
-  for (int i = threadIdx.x; i < B; i += kLseThreads)
-    sum += (double)__hip_atomic_load(loss_part + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
-  if ((threadIdx.x & 63) == 0) part[wave] = sum;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double s = 0.0;
-    for (int w = 0; w < kLseThreads / 64; ++w) s += part[w];
-    *loss = (float)(s / (double)B);
-  }
+  mean_by_last<64 * WPR * ROWS>(loss_part, B, arrivals, loss);
 }
 
 template <typename Tag, int NK>
@@ -799,27 +811,6 @@ void launch_fwd16(int d, unsigned grid, hipStream_t stream, const StepArgs& a, c
 
 }  // namespace
 
-hipError_t launch_lse(const StepArgs& a, const StepWs& w, int64_t n_ctiles, int tile, bool base2,
-                      hipStream_t stream) {
-  const int B = (int)a.B;
-  timing_start(3, stream);
-  auto go = [&](auto kernel, int rows) {
-    hipLaunchKernelGGL(kernel, dim3((unsigned)ceil_div(B, rows)), dim3(kLseThreads), 0, stream,
-                       w.stats, n_ctiles, tile, a.n_active, a.labels_mapped, w.tgt, B,
-                       a.row_lse_out, w.loss_part, w.arrivals, a.loss);
-  };
-  // A wave per row while one pass of eight loads per lane covers its pairs.
-  if (n_ctiles <= 512) {
-    if (base2) go(k_lse<64, true>, kLseThreads / 64);
-    else go(k_lse<64, false>, kLseThreads / 64);
-  } else {
-    if (base2) go(k_lse<256, true>, kLseThreads / 256);
-    else go(k_lse<256, false>, kLseThreads / 256);
-  }
-  timing_stop(3, stream);
-  return hipGetLastError();
-}
-
 hipError_t launch_forward(const StepArgs& a, const StepWs& w, hipStream_t stream) {
   if (a.dtype == 0) return launch_forward_f32(a, w, stream);
   hipError_t e = launch_prep(a, w, stream);
@@ -828,8 +819,8 @@ hipError_t launch_forward(const StepArgs& a, const StepWs& w, hipStream_t stream
   Margin mg{a.s, a.m, cosf(a.m), sinf(a.m), a.margin};
   // Narrow tiles while all of them run at once, two per CU (512 on 256 CUs):
   // beyond, their second round costs more than the pipelined tile (d = 512, us
-  // pipelined / narrow: |S| = 10,000, B = 128 20.0 / 13.8; 8,192, 512 21.1 /
-  // 19.6; 32,768, 128 25.5 / 23.9, and with 1,024 tiles 65,536, 128 39.2 / 41.3;
+  // pipelined / narrow: |S| = 10,000, B = 128 20.0 / 15.6; 8,192, 512 21.1 /
+  // 20.6; 32,768, 128 25.5 / 25.3; with 1,024 tiles 65,536, 128 39.2 / 41.3,
   // 8,192, 1024 22.5 / 32.2).
   const bool narrow = w.n_ctiles * ceil_div(B, kNarrowRows) <= 512;
   const int n_rt = (int)ceil_div(B, narrow ? kNarrowRows : kFwdBN);
@@ -858,7 +849,19 @@ hipError_t launch_forward(const StepArgs& a, const StepWs& w, hipStream_t stream
     launch_fwd16<F16Tag>(d, grid, stream, a, w, B, n_rt, n_tiles, per_xcd, mg);
   }
   timing_stop(2, stream);
-  return launch_lse(a, w, w.n_ctiles, kFwdClassTile, true, stream);
+  timing_start(3, stream);
+  auto lse = [&](auto kernel, int wpr, int rows) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)ceil_div(B, rows)), dim3(64 * wpr * rows), 0, stream,
+                       w.stats, w.n_ctiles, a.n_active, a.labels_mapped, w.tgt, B, a.row_lse_out,
+                       w.loss_part, w.arrivals, a.loss);
+  };
+  // At most about 256 arrivals (us: B = 128 5.7 with 2 rows, 6.9 with 4; B =
+  // 777 10.4, 9.6; B = 4096, 196 tiles 22.8 with 4 rows, 16.7 with 16).
+  if (B <= 256) lse(k_lse16<4, 2>, 4, 2);
+  else if (B <= 1024) lse(k_lse16<4, 4>, 4, 4);
+  else lse(k_lse16<1, 16>, 1, 16);
+  timing_stop(3, stream);
+  return hipGetLastError();
 }
 
 }  // namespace pfc

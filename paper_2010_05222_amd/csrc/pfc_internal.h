@@ -66,7 +66,6 @@ struct StepWs {
                          // at the target and past |S|); fp32 path: fp32 cosines
   int64_t ld_cos;        // row stride of lbuf: cap rounded up to 256
   float2* stats;         // [B x n_ctiles] per class tile: (max, sum 2^(f log2 e - max)), base 2
-                         // (fp32 path: base e)
   int64_t n_ctiles;      // class tiles of the forward contraction
   float* tgt;            // [B] margined target logit
   float* tgtc;           // [B] unmargined target cosine
@@ -137,18 +136,12 @@ struct StepArgs {
 hipError_t launch_prep(const StepArgs& a, const StepWs& w, hipStream_t stream);
 hipError_t launch_forward(const StepArgs& a, const StepWs& w, hipStream_t stream);
 hipError_t launch_backward(const StepArgs& a, const StepWs& w, hipStream_t stream);
-// Row log-sum-exp and loss from the (max, sum) pairs of n_ctiles tiles of
-// `tile` classes (in base 2, else base e).
-hipError_t launch_lse(const StepArgs& a, const StepWs& w, int64_t n_ctiles, int tile, bool base2,
-                      hipStream_t stream);
 // The fp32 path (f32.hip).
 hipError_t launch_forward_f32(const StepArgs& a, const StepWs& w, hipStream_t stream);
 hipError_t launch_backward_f32(const StepArgs& a, const StepWs& w, hipStream_t stream);
 // Class splits of the feature gradient.
 int split_f32(int64_t B, int64_t cap);
 int split_16(int64_t B, int64_t d, int64_t cap);
-// Narrowest class tile of the fp32 forward.
-constexpr int kFwdClassTile32 = 32;
 
 // Measurement hook (pfc_timing_begin / pfc_timing_end): launchers bracket a
 // kernel id's launches with these calls; both are no-ops unless armed.

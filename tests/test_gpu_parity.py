@@ -397,6 +397,28 @@ def test_forward_tile_widths(dev, B, d, K, dtype, tau):
           label_span=(0, K + 200), tau=tau, conflicts=4, random_m=False)
 
 
+@pytest.mark.parametrize("dtype,d,tau", [("bf16", 512, None), ("f16", 128, 0.4), ("f32", 200, None),
+                                         ("f32", 512, 0.4)])
+def test_forward_tiles_agree(dev, dtype, d, tau):
+    """A row's log-sum-exp does not depend on the tiles that its batch takes:
+    64 rows of a batch of 600 (the 256-row forward kernel; in fp32 the 64-class
+    tiles), alone (the narrow kernel; 32-class tiles), give the same bits."""
+    from _gpu_util import make_problem
+    B, C, lo = 600, 8000, 128
+    Xd, Wd, _, _, Ld = make_problem(B, d, C, dtype, 68, label_span=(0, C + 900), device=dev,
+                                    conflicts=4)
+    out = []
+    for rows in (slice(0, B), slice(lo, lo + 64)):
+        X, L = Xd[rows].contiguous(), Ld[rows].contiguous()
+        shard = _shard(len(X), d, C, 1.0, dtype, "arcface", 0.5, dev=dev, tau=tau)
+        shard.sample(L, 0)
+        shard.forward(X, Wd)
+        out.append(shard.row_lse)
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(out[0]).all())
+    assert torch.equal(out[0][lo:lo + 64], out[1])
+
+
 # PFC* conflict filter (Sec. 3.3.4, Eq. noise_filtering): some rows sit near
 # the centre of another row's class, so their cosine to that (active)
 # negative is ~0.9 > tau and the logit leaves the row's denominator.
