@@ -259,11 +259,11 @@ __global__ void __launch_bounds__(kLse32Threads) k_lse32(
 // and takes its W pieces straight from memory to registers, since no other
 // wave reads them.  blockDim = 64 x the waves that d needs (at most 4).
 //
-// At B = 250, |S| = 5,003, d = 512 it takes 32 us, at B = 64, |S| = 1,000,
+// At B = 250, |S| = 5,003, d = 512 it takes 30 us, at B = 64, |S| = 1,000,
 // d = 128 10 us; the loop that it replaced, a chain of |S| dependent steps per
 // output, took 1,585 and 266 us.
 template <int NB>
-__global__ void __launch_bounds__(256) k_dx32(
+__global__ void __launch_bounds__(256, NB <= 2 ? 2 : 1) k_dx32(
     const float* __restrict__ W, const int32_t* __restrict__ active,
     const int32_t* __restrict__ n_active_p, const int32_t* __restrict__ yhat,
     const float* __restrict__ row_lse, const float* __restrict__ inv_w,
@@ -280,27 +280,52 @@ __global__ void __launch_bounds__(256) k_dx32(
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l16 = lane & 15, g4 = 4 * (lane >> 4);
 
-  // Coefficients of chunk c into stage st: thread t owns piece t % 16 (four
-  // classes) of rows t / 16, + blockDim / 16, ...
-  auto produce = [&](int64_t c, int st) {
-    const int64_t j = c * kChunk + 4 * (tid & 15);
-    for (int r = tid >> 4; r < kDxRows; r += blockDim.x >> 4) {
-      const int n = n0 + r;
-      f32x4_t g = zero4();
-      if (n < B && j < K) {
-        const f32x4_t cv = load4(cos32 + (int64_t)n * ld_cos + j);
-        const float lse = row_lse[n];
-        const int64_t y = yhat[n];
+  // Coefficients of a chunk: thread t owns piece t % 16 (four classes) of rows
+  // t / 16, + blockDim / 16, ... (RMAX of them at most: one wave).  Their inputs
+  // are requested before the previous chunk's MFMAs (fetch) and turned into
+  // coefficients in LDS after them (produce).
+  constexpr int RMAX = NB == 1 ? kDxRows / 4 : kDxRows / 16;
+  const int rows_step = blockDim.x >> 4, p4 = 4 * (tid & 15);
+  f32x4_t cv[RMAX];
+  float iw[4], lse[RMAX];
+  int yv[RMAX];
+  int32_t id = 0;
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (j + e < K) g[e] = grad_coef(mg, cv[e], j + e == y, lse) * inv_w[j + e];
-      }
-      *reinterpret_cast<f32x4_t*>(&G[st][r][4 * (tid & 15)]) = g;
+  for (int i = 0; i < RMAX; ++i) {
+    const int r = (tid >> 4) + rows_step * i, n = n0 + r;
+    const bool ok = r < kDxRows && n < B;
+    lse[i] = ok ? row_lse[n] : 0.0f;
+    yv[i] = ok ? yhat[n] : -1;
+  }
+  auto fetch = [&](int64_t c) {
+    const int64_t j = c * kChunk + p4;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) iw[e] = j + e < K ? inv_w[j + e] : 0.0f;
+#pragma unroll
+    for (int i = 0; i < RMAX; ++i) {
+      const int r = (tid >> 4) + rows_step * i, n = n0 + r;
+      cv[i] = r < kDxRows && n < B && j < K ? load4(cos32 + (int64_t)n * ld_cos + j) : zero4();
     }
     if (tid < kChunk) {   // ids past |S| (coefficient 0) repeat the last one
-      const int64_t i = c * kChunk + tid;
-      ids[st][tid] = active[i < K ? i : K - 1];
+      const int64_t k = c * kChunk + tid;
+      id = active[k < K ? k : K - 1];
     }
+  };
+  auto produce = [&](int64_t c, int st) {
+    const int64_t j = c * kChunk + p4;
+#pragma unroll
+    for (int i = 0; i < RMAX; ++i) {
+      const int r = (tid >> 4) + rows_step * i;
+      if (r >= kDxRows) break;
+      f32x4_t g = zero4();
+      if (n0 + r < B) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (j + e < K) g[e] = grad_coef(mg, cv[i][e], j + e == yv[i], lse[i]) * iw[e];
+      }
+      *reinterpret_cast<f32x4_t*>(&G[st][r][p4]) = g;
+    }
+    if (tid < kChunk) ids[st][tid] = id;
   };
   f32x4_t acc[2][NB][4];
 #pragma unroll
@@ -320,13 +345,17 @@ __global__ void __launch_bounds__(256) k_dx32(
       for (int q = 0; q < NB; ++q)
         dst[q][s] = col0 + 64 * q < d ? load4(W + (int64_t)row[s] * d + col0 + 64 * q) : zero4();
   };
-  if (c_begin < c_end) produce(c_begin, 0);
+  if (c_begin < c_end) {
+    fetch(c_begin);
+    produce(c_begin, 0);
+  }
   int st = 0;
   for (int64_t c = c_begin; c < c_end; ++c, st ^= 1) {
     // After the barrier chunk c is ready, and the other stage is free.
     __syncthreads();
     load_w(st, 0, w[0]);
-    if (c + 1 < c_end) produce(c + 1, st ^ 1);
+    const bool more = c + 1 < c_end;
+    if (more) fetch(c + 1);
 #pragma unroll
     for (int kb = 0; kb < kChunk / 16; ++kb) {
       if (kb + 1 < kChunk / 16) load_w(st, kb + 1, w[(kb + 1) & 1]);
@@ -344,6 +373,7 @@ __global__ void __launch_bounds__(256) k_dx32(
             for (int m = 0; m < 2; ++m)
               acc[m][q][t] = mfma_16x16x4(a[m][s], w[kb & 1][q][s][t], acc[m][q][t]);
     }
+    if (more) produce(c + 1, st ^ 1);
   }
 #pragma unroll
   for (int m = 0; m < 2; ++m)
@@ -360,44 +390,58 @@ __global__ void __launch_bounds__(256) k_dx32(
     }
 }
 
-// The split partials of a row summed in split order, and the normalisation
-// backward dx = (v - x_hat (x_hat . v)) / ||x||, v = (s / B) * sum.  One
-// workgroup per row.
-__global__ void __launch_bounds__(256) k_dx_final32(const float* __restrict__ part, int n_split,
-                                                    const float* __restrict__ X,
-                                                    const float* __restrict__ inv_x, int B, int d,
-                                                    float sB, float* __restrict__ dX) {
+// The split partials of a row summed, and the normalisation backward
+// dx = (v - x_hat (x_hat . v)) / ||x||, v = (s / B) * sum.  One workgroup per
+// row: each of its runs of 256 threads sums a run of consecutive splits, eight
+// loads in flight per column, and the runs' sums are added in order (the loads'
+// latency bounds it: 63 splits of 128 rows, d = 1024, 21.6 us in one run, 9.3).
+constexpr int kFinalRuns = 4;
+__global__ void __launch_bounds__(256 * kFinalRuns) k_dx_final32(
+    const float* __restrict__ part, int n_split, const float* __restrict__ X,
+    const float* __restrict__ inv_x, int B, int d, float sB, float* __restrict__ dX) {
   constexpr int PER = 4;   // d <= 1024
+  __shared__ float sums[kFinalRuns - 1][256 * PER];
   __shared__ float red[4];
-  const int n = blockIdx.x, t = threadIdx.x;
-  const float ix = inv_x[n];
+  const int n = blockIdx.x, t = threadIdx.x & 255, run = threadIdx.x >> 8;
   const int64_t stride = (int64_t)B * d;
+  const int per = (n_split + kFinalRuns - 1) / kFinalRuns;
+  const int s0 = per * run, s1 = s0 + per < n_split ? s0 + per : n_split;
   float v[PER], xh[PER];
-  float dot = 0.0f;
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
     const int i = t + 256 * k;
     v[k] = 0.0f;
-    xh[k] = 0.0f;
     if (i >= d) continue;
     const float* p = part + (int64_t)n * d + i;
-    float sum = 0.0f;
-    int s = 0;
-    for (; s + 8 <= n_split; s += 8) {
+    for (int s = s0; s < s1; s += 8) {
       float q[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) q[u] = p[(s + u) * stride];
+      for (int u = 0; u < 8; ++u) q[u] = s + u < s1 ? p[(s + u) * stride] : 0.0f;
 #pragma unroll
-      for (int u = 0; u < 8; ++u) sum += q[u];
+      for (int u = 0; u < 8; ++u) v[k] += q[u];
     }
-    for (; s < n_split; ++s) sum += p[s * stride];
-    v[k] = sB * sum;
-    xh[k] = X[(int64_t)n * d + i] * ix;
-    dot = fmaf(xh[k], v[k], dot);
+    if (run) sums[run - 1][i] = v[k];
   }
-  dot = wave_sum(dot);
-  if ((t & 63) == 0) red[t >> 6] = dot;
   __syncthreads();
+  float dot = 0.0f;
+  const float ix = inv_x[n];
+  if (run == 0) {
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int i = t + 256 * k;
+      xh[k] = 0.0f;
+      if (i >= d) continue;
+#pragma unroll
+      for (int u = 0; u < kFinalRuns - 1; ++u) v[k] += sums[u][i];
+      v[k] *= sB;
+      xh[k] = X[(int64_t)n * d + i] * ix;
+      dot = fmaf(xh[k], v[k], dot);
+    }
+    dot = wave_sum(dot);
+    if ((t & 63) == 0) red[t >> 6] = dot;
+  }
+  __syncthreads();
+  if (run) return;
   dot = red[0] + red[1] + red[2] + red[3];
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
@@ -414,7 +458,7 @@ __global__ void __launch_bounds__(256) k_dx_final32(const float* __restrict__ pa
 // rows straight to the registers of the wave that owns their columns.  The
 // accumulators end with four consecutive columns of a class per lane, so the
 // tangent projection, momentum and weight step read and write whole rows in
-// 16-byte pieces.  37 us at B = 250, |S| = 5,003, d = 512 (110 us as one
+// 16-byte pieces.  38 us at B = 250, |S| = 5,003, d = 512 (110 us as one
 // workgroup per class).
 template <int NB>
 __global__ void __launch_bounds__(256) k_dw32(
@@ -433,23 +477,36 @@ __global__ void __launch_bounds__(256) k_dw32(
   const int n_waves = blockDim.x >> 6;
   const int l16 = lane & 15, g4 = 4 * (lane >> 4);
 
-  // Coefficients of rows nb .. nb + 63 into stage st: thread t owns four
-  // classes of rows t / 4, + blockDim / 4, ...
+  // Coefficients of rows nb .. nb + 63: thread t owns four classes of rows
+  // t / 4, + blockDim / 4, ... (RMAX of them at most); requested and produced
+  // around the previous chunk's MFMAs, as in dX.
+  constexpr int RMAX = NB == 1 ? 4 : 1;
+  const int rows_step = blockDim.x >> 2, p4 = 4 * (tid & 3);
+  f32x4_t cv[RMAX];
+  float lse[RMAX], ix[RMAX];
+  int yv[RMAX];
+  auto fetch = [&](int nb) {
+#pragma unroll
+    for (int i = 0; i < RMAX; ++i) {
+      const int r = (tid >> 2) + rows_step * i, n = nb + r;
+      const bool ok = r < kChunk && n < B;
+      cv[i] = ok && j0 + p4 < K ? load4(cos32 + (int64_t)n * ld_cos + j0 + p4) : zero4();
+      lse[i] = ok ? row_lse[n] : 0.0f;
+      ix[i] = ok ? inv_x[n] : 0.0f;
+      yv[i] = ok ? yhat[n] : -1;
+    }
+  };
   auto produce = [&](int nb, int st) {
-    const int q = 4 * (tid & 3);
-    for (int r = tid >> 2; r < kChunk; r += blockDim.x >> 2) {
-      const int n = nb + r;
-      f32x4_t g = zero4();
-      if (n < B && j0 + q < K) {
-        const f32x4_t cv = load4(cos32 + (int64_t)n * ld_cos + j0 + q);
-        const float lse = row_lse[n], ix = inv_x[n];
-        const int64_t y = yhat[n];
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (j0 + q + e < K) g[e] = grad_coef(mg, cv[e], j0 + q + e == y, lse) * ix;
+    for (int i = 0; i < RMAX; ++i) {
+      const int r = (tid >> 2) + rows_step * i;
+      if (r >= kChunk) break;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int64_t j = j0 + p4 + e;
+        G[st][p4 + e][k_pos(r)] =
+            nb + r < B && j < K ? grad_coef(mg, cv[i][e], j == yv[i], lse[i]) * ix[i] : 0.0f;
       }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) G[st][q + e][k_pos(r)] = g[e];
     }
   };
   f32x4_t acc[NB][4];
@@ -470,11 +527,13 @@ __global__ void __launch_bounds__(256) k_dw32(
         dst[q][s] = col0 + 256 * q < d ? load4(X + (int64_t)n * d + col0 + 256 * q) : zero4();
     }
   };
-  produce(0, 0);
+  fetch(0);
   load_x(0, x[0]);
+  produce(0, 0);
   for (int nb = 0, st = 0; nb < B; nb += kChunk, st ^= 1) {
     __syncthreads();   // the chunk is ready, the other stage free
-    if (nb + kChunk < B) produce(nb + kChunk, st ^ 1);
+    const bool more = nb + kChunk < B;
+    if (more) fetch(nb + kChunk);
 #pragma unroll
     for (int kb = 0; kb < kChunk / 16; ++kb) {
       load_x(nb + 16 * (kb + 1), x[(kb + 1) & 1]);
@@ -487,6 +546,7 @@ __global__ void __launch_bounds__(256) k_dw32(
           for (int t = 0; t < 4; ++t)
             acc[q][t] = mfma_16x16x4(a[s], x[kb & 1][q][s][t], acc[q][t]);
     }
+    if (more) produce(nb + kChunk, st ^ 1);
   }
 
   // Update: lane l owns columns col0 + 256 q .. + 3 of classes 4 (l / 16) + r.
@@ -603,7 +663,7 @@ hipError_t launch_backward_f32(const StepArgs& a, const StepWs& w, hipStream_t s
   });
   timing_stop(4, stream);
   timing_start(5, stream);
-  hipLaunchKernelGGL(k_dx_final32, dim3((unsigned)B), dim3(256), 0, stream, w.dx_part, w.n_split,
+  hipLaunchKernelGGL(k_dx_final32, dim3((unsigned)B), dim3(256 * kFinalRuns), 0, stream, w.dx_part, w.n_split,
                      (const float*)a.X, w.inv_x, B, d, sB, a.dX);
   timing_stop(5, stream);
   timing_start(6, stream);
