@@ -25,7 +25,7 @@
 //
 // This replaces ten launches (clear, mark, plan, key digits and histogram, top
 // digit, collect, refine, scan, write, remap), whose time was mostly that of
-// empty launches: 10 K classes 55 -> 13 us, 100 K 46 -> 17 us, 2M 49 -> 27 us.
+// empty launches: 10 K classes 55 -> 13 us, 100 K 46 -> 15 us, 2M 49 -> 25 us.
 #include <math.h>
 
 #include "pfc_internal.h"
@@ -110,6 +110,28 @@ __device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t* smem, uint3
   return before + incl - v;
 }
 
+// Three of them at once (v[i] becomes its exclusive prefix).
+template <int kWaves>
+__device__ __forceinline__ void block_scan3(uint32_t (&v)[3], uint32_t (*smem)[kWaves],
+                                            uint32_t (&total)[3]) {
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  uint32_t incl[3];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    incl[i] = wave_scan(v[i]);
+    if (lane_id() == 63) smem[i][wave] = incl[i];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const uint32_t sums = wave_scan(lane_id() < kWaves ? smem[i][lane_id()] : 0u);
+    total[i] = (uint32_t)__builtin_amdgcn_readlane((int)sums, kWaves - 1);
+    const uint32_t before = wave ? (uint32_t)__builtin_amdgcn_readlane((int)sums, wave - 1) : 0u;
+    v[i] = before + incl[i] - v[i];
+  }
+  __syncthreads();
+}
+
 // Find the bin holding the k-th (1-based) element of an LDS histogram of kBins
 // bins (two per thread of 1,024).  Returns through shared out[0] = bin, out[1] = count
 // before the bin, out[2] = count of the bin (the last bin and zero counts if
@@ -161,17 +183,50 @@ __device__ __forceinline__ uint32_t live16(int64_t c0, int64_t C) {
   return c0 >= C ? 0u : C - c0 >= kPerThread ? 0xFFFFu : (1u << (C - c0)) - 1u;
 }
 
+// f(k, labels[k]) for every label, once across the workgroup, U loads in
+// flight per thread (eight of 256 threads: one at a time they were 6 of k_keys'
+// 16 us at B = 4096; fewer of 1,024 threads, whose code is then shorter);
+// `before` runs once the first ones are requested.
+template <int U, typename Before, typename F>
+__device__ __forceinline__ void for_labels(const int64_t* labels, int64_t B, Before&& before,
+                                           F&& f) {
+  uint64_t y[U];
+  auto load = [&](int64_t k0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t k = k0 + (int64_t)u * blockDim.x;
+      y[u] = k < B ? (uint64_t)labels[k] : 0;
+    }
+  };
+  load(threadIdx.x);
+  before();
+#pragma unroll 1
+  for (int64_t k0 = threadIdx.x; k0 < B; k0 += (int64_t)U * blockDim.x) {
+    if (k0 != threadIdx.x) load(k0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t k = k0 + (int64_t)u * blockDim.x;
+      if (k < B) f(k, y[u]);
+    }
+  }
+}
+
 // The positives among the classes [c_lo, c_lo + n) (n a multiple of 32), as a
 // bitmap in LDS.  Ends with a barrier.
+template <int U>
 __device__ __forceinline__ void mark_positives(const int64_t* labels, int64_t B, int64_t a,
                                                int64_t c_lo, int n, uint32_t* bits) {
-  for (int i = threadIdx.x; i < n / 32; i += blockDim.x) bits[i] = 0u;
-  __syncthreads();
-  for (int64_t k = threadIdx.x; k < B; k += blockDim.x) {
-    // Unsigned: a label before the range wraps far past its end.
-    const uint64_t c = (uint64_t)labels[k] - (uint64_t)(a + c_lo);
-    if (c < (uint64_t)n) atomicOr(&bits[c >> 5], 1u << (c & 31));
-  }
+  for_labels<U>(
+      labels, B,
+      [&] {
+        for (int i = threadIdx.x; i < n / 32; i += blockDim.x) bits[i] = 0u;
+        __syncthreads();
+      },
+      [&](int64_t, uint64_t y) {
+        // Unsigned: a label before the range wraps far past its end.
+        const uint64_t c = y - (uint64_t)(a + c_lo);
+        if (c < (uint64_t)n) atomicOr(&bits[c >> 5], 1u << (c & 31));
+      });
   __syncthreads();
 }
 
@@ -217,7 +272,7 @@ __global__ void __launch_bounds__(kGroupThreads) k_keys(
   const int64_t g0 = (int64_t)blockIdx.x * run;
   const int n = (int)(n_groups - g0 < run ? n_groups - g0 : run);
   const int t = threadIdx.x;
-  mark_positives(labels, B, a, g0 * kGroupClasses, n * kGroupClasses, bits);
+  mark_positives<8>(labels, B, a, g0 * kGroupClasses, n * kGroupClasses, bits);
 #pragma unroll 1
   for (int i = 0; i < n; ++i) {
     const int64_t g = g0 + i;
@@ -415,19 +470,19 @@ __device__ __forceinline__ void map_labels(const int64_t* labels, int64_t B, int
                                            int64_t c_lo, int n, const uint32_t* out,
                                            const uint32_t* where, int64_t cap,
                                            int32_t* labels_mapped) {
-  for (int64_t k = threadIdx.x; k < B; k += kThreads) {
-    const uint64_t y = (uint64_t)labels[k] - (uint64_t)a;
+  for_labels<1>(labels, B, [] { __syncthreads(); }, [&](int64_t k, uint64_t label) {
+    const uint64_t y = label - (uint64_t)a;
     if (y >= (uint64_t)C) {
       if (c_lo == 0) labels_mapped[k] = -1;
-      continue;
+      return;
     }
     const uint64_t c = y - (uint64_t)c_lo;
-    if (c >= (uint64_t)n * kSpan) continue;
+    if (c >= (uint64_t)n * kSpan) return;
     const uint32_t p = where[c / kPerThread];
     const int i = (int)(c % kPerThread);
     const int64_t o = (int64_t)out[c / kSpan] + (p >> 16) + __popc(p & ((1u << i) - 1u));
     labels_mapped[k] = ((p >> i) & 1u) && o < cap ? (int32_t)o : -1;
-  }
+  });
 }
 
 // Of `tie` ties, those taken when `before` precede them.
@@ -452,7 +507,7 @@ __global__ void __launch_bounds__(kThreads) k_sample_one(
   __shared__ uint32_t out;
   const int t = threadIdx.x;
   const int64_t c0 = t * kPerThread;
-  mark_positives(labels, B, a, 0, kSpan, bits);
+  mark_positives<2>(labels, B, a, 0, kSpan, bits);
   uint64_t m;
   uint32_t total, n_pos;
   {
@@ -485,7 +540,6 @@ __global__ void __launch_bounds__(kThreads) k_sample_one(
     *n_active = clamp_count((uint64_t)n_pos + (uint64_t)n_neg, cap);
   }
   write_span(settle(m, list, k, th, c0, C, a, seed), th, 0, 0, c0, cap, active, L.scan, where);
-  __syncthreads();
   map_labels(labels, B, C, a, 0, 1, &out, where, cap, labels_mapped);
 }
 
@@ -536,6 +590,7 @@ __global__ void __launch_bounds__(kThreads) k_resolve_write(
   __shared__ uint32_t where[kThreads];
   __shared__ uint32_t start[kMergeGroups + 1];   // of each group's candidates in the list
   __shared__ uint32_t cnt[2][kMergeGroups];
+  __shared__ uint32_t scan3[3][16];
   __shared__ uint32_t out, tie_before;
   const int t = threadIdx.x;
   const int64_t c0 = ((int64_t)blockIdx.x * kThreads + t) * kPerThread;
@@ -544,11 +599,10 @@ __global__ void __launch_bounds__(kThreads) k_resolve_write(
   const uint64_t m = own ? w.masks[c0 / kPerThread] : 0;
   const uint32_t sure = t < n_groups ? w.grp_sure[t] : 0u;
   const uint32_t n_cand = t < n_groups ? w.grp_cand[t] : 0u;
-  uint32_t pos, below, cand;
-  block_scan<16>(sure >> 16, L.scan, &pos);
-  block_scan<16>((sure & 0xFFFFu) - (sure >> 16), L.scan, &below);
-  const uint32_t first = block_scan<16>(n_cand, L.scan, &cand);
-  if (t < n_groups) start[t] = first;
+  uint32_t v[3] = {sure >> 16, (sure & 0xFFFFu) - (sure >> 16), n_cand}, sum[3];
+  block_scan3<16>(v, scan3, sum);
+  const uint32_t pos = sum[0], below = sum[1], cand = sum[2];
+  if (t < n_groups) start[t] = v[2];
   if (t == 0) start[n_groups] = cand;
   __syncthreads();
   int64_t n_neg;
@@ -577,15 +631,20 @@ __global__ void __launch_bounds__(kThreads) k_resolve_write(
   }
 
   const int lanes = 1 << count_bits, sub = t & (lanes - 1);
-  // Each group's classes in S and its ties, summed over its lanes.
+  // Each group's classes in S and its ties: its lanes' votes, counted by all of
+  // them (sums by lane moves, ten LDS round trips a group, took 5 us of 17 on
+  // 245 groups).
+  const uint64_t group_lanes = (lanes == 64 ? ~0ull : ((1ull << lanes) - 1ull) << (lane_id() & ~(lanes - 1)));
 #pragma unroll 1
   for (int g = t >> count_bits; g < n_groups; g += kThreads >> count_bits) {
     uint32_t s = 0, e = 0;
     if (k > 0) {
-      const uint64_t* src = fits ? list + start[g] : w.cand_key + (int64_t)g * kGroupClasses;
-      for (uint32_t i = sub; i < start[g + 1] - start[g]; i += lanes) {
-        s += th.below(src[i]);
-        e += th.tie(src[i]);
+      const uint32_t n = start[g + 1] - start[g];
+      for (uint32_t i = sub; i < n; i += lanes) {
+        const uint64_t key =
+            fits ? list[start[g] + i] : w.cand_key[(int64_t)g * kGroupClasses + i];
+        s += __popcll(__ballot(th.below(key)) & group_lanes);
+        e += __popcll(__ballot(th.tie(key)) & group_lanes);
       }
     } else if (k < 0) {
       for (int v = sub; v < kGroupThreads; v += lanes) {
@@ -595,12 +654,12 @@ __global__ void __launch_bounds__(kThreads) k_resolve_write(
         s += __popc(st.x);
         e += __popc(st.y);
       }
+      for (int off = 1; off < lanes; off <<= 1) {
+        s += __shfl_xor(s, off, 64);
+        e += __shfl_xor(e, off, 64);
+      }
     }
-    for (int off = 1; off < lanes; off <<= 1) {
-      s += __shfl_xor(s, off, 64);
-      e += __shfl_xor(e, off, 64);
-    }
-    if (sub == 0) {
+    if (sub == 0) {   // in every vote of the group
       cnt[0][g] = s;
       cnt[1][g] = e;
     }
@@ -623,7 +682,6 @@ __global__ void __launch_bounds__(kThreads) k_resolve_write(
   const uint64_t* keys = w.cand_key + c0 / kGroupClasses * kGroupClasses;
   const uint2 st = own ? settle(m, keys, k, th, c0, C, a, seed) : make_uint2(0u, 0u);
   write_span(st, th, out, tie_before, c0, cap, active, L.scan, where);
-  __syncthreads();
   map_labels(labels, B, C, a, (int64_t)blockIdx.x * kSpan, 1, &out, where, cap, labels_mapped);
 }
 
@@ -739,7 +797,6 @@ __global__ void __launch_bounds__(kThreads) k_write(
     write_span(st, th, w.grp_out[(s0 + i) * kSpanGroups], w.grp_tie_off[(s0 + i) * kSpanGroups],
                c0, cap, active, smem, where + kThreads * i);
   }
-  __syncthreads();
   map_labels(labels, B, C, a, s0 * kSpan, n, out, where, cap, labels_mapped);
 }
 
