@@ -70,6 +70,16 @@ __shared__ __attribute__((aligned(16))) float wQ0[kBwKC], wQ1[kBwKC], wQ2[kBwKC]
 __shared__ __attribute__((aligned(1024))) uint16_t wG0[kDwCls * kBwKC], wG1[kDwCls * kBwKC],
     wG2[kDwCls * kBwKC];
 
+// The same at d = 128, where a stage is a quarter as large: two workgroups then
+// share a CU (a dX workgroup has two waves there, and alone left half of the
+// SIMDs idle).
+constexpr int kRowLd128 = 144;   // 256 B + 32 B
+__shared__ __attribute__((aligned(1024))) uint16_t xV0[kBwKC * kRowLd128],
+    xV1[kBwKC * kRowLd128], xV2[kBwKC * kRowLd128];
+// dW: the three stages together also hold the update's 32 staged rows of 132 floats.
+constexpr int kTLd128 = 132;
+__shared__ __attribute__((aligned(1024))) uint16_t wV[3][128 * kBwKC];
+
 #define PFC_STAGE3(name, T, a0, a1, a2)          \
   template <int S>                               \
   __device__ __forceinline__ T* name() {         \
@@ -77,16 +87,28 @@ __shared__ __attribute__((aligned(1024))) uint16_t wG0[kDwCls * kBwKC], wG1[kDwC
     else if constexpr (S == 1) return a1;        \
     else return a2;                              \
   }
-PFC_STAGE3(dx_w, uint16_t, xW0, xW1, xW2)
 PFC_STAGE3(dx_r, int16_t, xR0, xR1, xR2)
 PFC_STAGE3(dx_i, float, xI0, xI1, xI2)
 PFC_STAGE3(dx_s, float, xS0, xS1, xS2)
 PFC_STAGE3(dx_g, uint16_t, xG0, xG1, xG2)
-PFC_STAGE3(dw_x, uint16_t, wX0, wX1, wX2)
 PFC_STAGE3(dw_r, int16_t, wR0, wR1, wR2)
 PFC_STAGE3(dw_q, float, wQ0, wQ1, wQ2)
 PFC_STAGE3(dw_g, uint16_t, wG0, wG1, wG2)
 #undef PFC_STAGE3
+template <int S, int WI>
+__device__ __forceinline__ uint16_t* dx_w() {
+  if constexpr (WI == 1) return S == 0 ? xV0 : S == 1 ? xV1 : xV2;
+  else if constexpr (S == 0) return xW0;
+  else if constexpr (S == 1) return xW1;
+  else return xW2;
+}
+template <int S, int WI>
+__device__ __forceinline__ uint16_t* dw_x() {
+  if constexpr (WI == 1) return wV[S];
+  else if constexpr (S == 0) return wX0;
+  else if constexpr (S == 1) return wX1;
+  else return wX2;
+}
 
 // Target term of a row, (p_t - 1) * slope_t, from its unmargined target cosine.
 __device__ __forceinline__ float target_coef(const Margin& mg, float c, float lse) {
@@ -134,12 +156,12 @@ __device__ __forceinline__ uint4 frag_of(const u32x2_t& lo, const u32x2_t& hi) {
 }
 __device__ __forceinline__ uint4 as_uint4(const u32x4_t& v) { return make_uint4(v.x, v.y, v.z, v.w); }
 
-template <typename T>
-__device__ __forceinline__ void zero_acc(T (&acc)[4][2]) {
+template <typename T, int NB>
+__device__ __forceinline__ void zero_acc(T (&acc)[4][NB]) {
 #pragma unroll
   for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb)
+    for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[mb][nb][r] = 0.0f;
 }
@@ -151,19 +173,27 @@ __device__ __forceinline__ void zero_acc(T (&acc)[4][2]) {
 // Pipeline per chunk c (32 classes): the raw cosines and 1/||w|| of chunk
 // c + 3 and the W rows of chunk c + 2 are requested, the coefficients of
 // chunk c + 1 are produced, and chunk c is contracted.
+//
+// At d = 128 four waves own [0, 128) and 32 rows each (4 x 1 blocks), and two
+// workgroups share a CU: two waves of 64 rows left half of the SIMDs idle (B =
+// 1024, |S| = 400,000: 445 -> 342 us; the class gradient, whose eight waves now
+// come twice to a CU as well, 478 -> 398).
+constexpr int dx_threads(int wi) { return wi == 1 ? 256 : 128 * wi; }
 template <typename Tag, int WI>
-__global__ void __launch_bounds__(128 * WI) k_dx16(
+__global__ void __launch_bounds__(dx_threads(WI)) k_dx16(
     const uint16_t* __restrict__ W, const int32_t* __restrict__ act_pad,
     const int32_t* __restrict__ n_active_p, const float* __restrict__ inv_w,
     const float* __restrict__ inv_w_max, const uint16_t* __restrict__ lbuf, int64_t ld_cos,
     const float* __restrict__ gscale, int64_t ld_g, int B, int n_rt, int n_split,
     int64_t n_tiles, int64_t per_xcd, float* __restrict__ dx_part) {
   constexpr int D = 128 * WI;
-  constexpr int NT = 128 * WI;              // threads
-  constexpr int NW = 2 * WI;                // waves
+  constexpr int NT = dx_threads(WI);        // threads
+  constexpr int NW = NT / 64;               // waves
+  constexpr int NBD = WI == 1 ? 1 : 2;      // 32-row blocks of a wave
   constexpr int WROWS = kBwKC / NW;         // W rows DMA'd by each wave per chunk
   constexpr int RDMA = 8 / NW;              // 1-KB logit-store blocks DMA'd by each wave
   constexpr int GROUPS = 512 / NT;          // 8-coefficient groups per thread per chunk
+  constexpr int LD = WI == 1 ? kRowLd128 : kRowLd;   // LDS row stride of the W rows
   constexpr int PER_ITER = WROWS + RDMA + 3;  // DMAs a wave issues per chunk
   const int64_t t = (int64_t)(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
   if (t >= n_tiles) return;
@@ -181,7 +211,7 @@ __global__ void __launch_bounds__(128 * WI) k_dx16(
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wi = wave >> 1, wn = wave & 1;
+  const int wi = WI == 1 ? 0 : wave >> 1, wn = WI == 1 ? wave : wave & 1;
   const float scale = dx_operand_scale(Tag{}, *inv_w_max);
 
   // Coefficient-producer slots of this thread (fixed for the whole kernel):
@@ -249,7 +279,7 @@ __global__ void __launch_bounds__(128 * WI) k_dx16(
 #pragma unroll
     for (int v = 0; v < WROWS; ++v) {
       const int r = wave * WROWS + v;
-      if (lane < D / 8) dma16(W + (int64_t)rows_pf[v] * D + 8 * lane, dx_w<S>() + r * kRowLd);
+      if (lane < D / 8) dma16(W + (int64_t)rows_pf[v] * D + 8 * lane, dx_w<S, WI>() + r * LD);
     }
   };
   // Coefficients of chunk c (K-major, rows of 32 classes): the LDS reads are
@@ -304,11 +334,11 @@ __global__ void __launch_bounds__(128 * WI) k_dx16(
   // frag_k_major32): W rows MN-major, coefficients K-major.
   const int fg = lane >> 4, fsrc = lane & 15;
   const uint32_t a_lane =
-      ((8 * (fg >> 1) + (fsrc >> 2)) * kRowLd + 16 * (fg & 1) + 4 * (fsrc & 3) + 128 * wi) * 2;
-  const uint32_t b_lane0 = k_major32_offset(64 * wn + (lane & 31), lane >> 5) * 2;
-  const uint32_t b_lane1 = k_major32_offset(64 * wn + (lane & 31), 2 + (lane >> 5)) * 2;
+      ((8 * (fg >> 1) + (fsrc >> 2)) * LD + 16 * (fg & 1) + 4 * (fsrc & 3) + 128 * wi) * 2;
+  const uint32_t b_lane0 = k_major32_offset(32 * NBD * wn + (lane & 31), lane >> 5) * 2;
+  const uint32_t b_lane1 = k_major32_offset(32 * NBD * wn + (lane & 31), 2 + (lane >> 5)) * 2;
 
-  f32x16_t acc[4][2];
+  f32x16_t acc[4][NBD];
   zero_acc(acc);
 
   if (c_begin < c_stop) {
@@ -347,25 +377,25 @@ __global__ void __launch_bounds__(128 * WI) k_dx16(
         read_ids(cu + 2, idv);
         ProdIn pin;
         produce_load(std::integral_constant<int, (u + 1) % 3>{}, pin);
-        const uint32_t wb = lds_addr(dx_w<u>()) + a_lane;
+        const uint32_t wb = lds_addr(dx_w<u, WI>()) + a_lane;
         const uint32_t gb0 = lds_addr(dx_g<u>()) + b_lane0;
         const uint32_t gb1 = lds_addr(dx_g<u>()) + b_lane1;
         u32x2_t alo[2][4], ahi[2][4];
-        u32x4_t bq[2][2];
+        u32x4_t bq[2][NBD];
         static_for<0, 4>([&](auto mm) {
           constexpr int mb = decltype(mm)::value;
-          ds_read_tr_b64<(0 * kRowLd + 32 * mb) * 2>(alo[0][mb], wb);
-          ds_read_tr_b64<(4 * kRowLd + 32 * mb) * 2>(ahi[0][mb], wb);
+          ds_read_tr_b64<(0 * LD + 32 * mb) * 2>(alo[0][mb], wb);
+          ds_read_tr_b64<(4 * LD + 32 * mb) * 2>(ahi[0][mb], wb);
         });
         ds_read_128<0>(bq[0][0], gb0);
-        ds_read_128<32 * 64>(bq[0][1], gb0);
+        if constexpr (NBD > 1) ds_read_128<32 * 64>(bq[0][1], gb0);
         static_for<0, 4>([&](auto mm) {
           constexpr int mb = decltype(mm)::value;
-          ds_read_tr_b64<(16 * kRowLd + 32 * mb) * 2>(alo[1][mb], wb);
-          ds_read_tr_b64<(20 * kRowLd + 32 * mb) * 2>(ahi[1][mb], wb);
+          ds_read_tr_b64<(16 * LD + 32 * mb) * 2>(alo[1][mb], wb);
+          ds_read_tr_b64<(20 * LD + 32 * mb) * 2>(ahi[1][mb], wb);
         });
         ds_read_128<0>(bq[1][0], gb1);
-        ds_read_128<32 * 64>(bq[1][1], gb1);
+        if constexpr (NBD > 1) ds_read_128<32 * 64>(bq[1][1], gb1);
         // ... then later chunks' loads; the next coefficients are produced
         // while the first k-step's MFMAs run.
         dma_raw(std::integral_constant<int, u>{}, cu + 3);
@@ -373,20 +403,20 @@ __global__ void __launch_bounds__(128 * WI) k_dx16(
         static_for<0, 2>([&](auto kq) {
           constexpr int kk = decltype(kq)::value;
           if constexpr (kk == 0) {
-            lgkm_wait<10>(alo[0][0], alo[0][1], alo[0][2], alo[0][3], ahi[0][0], ahi[0][1],
-                          ahi[0][2], ahi[0][3], bq[0][0], bq[0][1], idv);
+            lgkm_wait<8 + NBD>(alo[0][0], alo[0][1], alo[0][2], alo[0][3], ahi[0][0], ahi[0][1],
+                          ahi[0][2], ahi[0][3], bq[0], idv);
             // W rows of chunk cu + 2, from the ids read above.
             rows_of(idv);
             dma_w(std::integral_constant<int, (u + 2) % 3>{});
           } else {
             produce_store(std::integral_constant<int, (u + 1) % 3>{}, cu + 1, pin);
             lgkm_wait<0>(alo[1][0], alo[1][1], alo[1][2], alo[1][3], ahi[1][0], ahi[1][1],
-                         ahi[1][2], ahi[1][3], bq[1][0], bq[1][1]);
+                         ahi[1][2], ahi[1][3], bq[1]);
           }
 #pragma unroll
           for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
+            for (int nb = 0; nb < NBD; ++nb)
               acc[mb][nb] = mfma_32x32x16(frag_of(alo[kk][mb], ahi[kk][mb]), as_uint4(bq[kk][nb]),
                                           acc[mb][nb], Tag{});
         });
@@ -398,8 +428,8 @@ __global__ void __launch_bounds__(128 * WI) k_dx16(
   const float inv_scale = 1.0f / scale;
   const int half = lane >> 5, l32 = lane & 31;
 #pragma unroll
-  for (int nb = 0; nb < 2; ++nb) {
-    const int n = n0 + 64 * wn + 32 * nb + l32;
+  for (int nb = 0; nb < NBD; ++nb) {
+    const int n = n0 + 32 * (NBD * wn + nb) + l32;
     if (n >= B) continue;
     float* out = dx_part + ((int64_t)split * B + n) * D;
 #pragma unroll
@@ -555,7 +585,7 @@ __global__ void __launch_bounds__(THREADS) k_dx_final(
 // than the waves have slots, several waves load and write the same bytes, so
 // that all waves' load counts stay alike.
 template <typename Tag, int WI, bool MASTER, int CLS>
-__global__ void __launch_bounds__(512) k_dw16(
+__global__ void __launch_bounds__(512, WI == 1 ? 4 : 2) k_dw16(
     const uint16_t* __restrict__ xbT, const void* __restrict__ X,
     uint16_t* __restrict__ W, float* __restrict__ W_master, float* __restrict__ M,
     const int32_t* __restrict__ active, const int32_t* __restrict__ n_active_p,
@@ -681,7 +711,7 @@ __global__ void __launch_bounds__(512) k_dw16(
     const int m = wave * XDMA + v;
     const int i = 16 * m + (lane >> 2);
     const int piece = (lane & 3) ^ ((i >> 2) & 3);
-    dma16(xbT + ((int64_t)cc * D + i) * kBwKC + 8 * piece, dw_x<S>() + 512 * m);
+    dma16(xbT + ((int64_t)cc * D + i) * kBwKC + 8 * piece, dw_x<S, WI>() + 512 * m);
   };
   auto dma_x = [&](auto st, int c) __attribute__((always_inline)) {
 #pragma unroll
@@ -796,7 +826,7 @@ __global__ void __launch_bounds__(512) k_dw16(
       // complete.
       wait_vmcnt_lgkm0<PER_ITER>();
       stage_barrier();
-      const uint32_t xs = lds_addr(dw_x<u>());
+      const uint32_t xs = lds_addr(dw_x<u, WI>());
       const uint32_t gs = lds_addr(dw_g<u>());
       u32x4_t a0[MB], b0[NB];
       static_for<0, MB>([&](auto mm) {
@@ -870,8 +900,9 @@ __global__ void __launch_bounds__(512) k_dw16(
   constexpr int NH = D > 256 ? 2 : 1;         // 256-entry halves of a row
   constexpr int LPH = (D > 256 ? 256 : D) / 4;  // lanes that own entries
   constexpr int RPW = 32 / NW;                // rows of a pass per wave
-  float* const tlo = reinterpret_cast<float*>(wX0);
-  float* const thi = reinterpret_cast<float*>(wX1);
+  constexpr int TLD = WI == 1 ? kTLd128 : kTLd;
+  float* const tlo = reinterpret_cast<float*>(dw_x<0, WI>());
+  float* const thi = reinterpret_cast<float*>(dw_x<1, WI>());
   const bool lane_on = LPH == 64 || lane < LPH;
   const int kt = (int)(K - j0);               // classes from the tile's first on that exist (>= 1)
   int* const hits = reinterpret_cast<int*>(wG0);   // NW lists of kHitCap entries
@@ -933,7 +964,7 @@ __global__ void __launch_bounds__(512) k_dw16(
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const int d0 = DW * wd + 32 * mb + 8 * g + 4 * half;
-        *reinterpret_cast<float4*>((d0 >= 256 ? thi : tlo) + l32 * kTLd + (d0 & 255)) =
+        *reinterpret_cast<float4*>((d0 >= 256 ? thi : tlo) + l32 * TLD + (d0 & 255)) =
             make_float4(acc[mb][p % NB][4 * g], acc[mb][p % NB][4 * g + 1],
                         acc[mb][p % NB][4 * g + 2], acc[mb][p % NB][4 * g + 3]);
       }
@@ -946,7 +977,7 @@ __global__ void __launch_bounds__(512) k_dw16(
     for (int h = 0; h < NH; ++h) {
       const uint2 x4 = *reinterpret_cast<const uint2*>(
           reinterpret_cast<const uint16_t*>(X) + (int64_t)nn * D + 256 * h + 4 * lane);
-      float4* t = reinterpret_cast<float4*>((h ? thi : tlo) + r * kTLd + 4 * lane);
+      float4* t = reinterpret_cast<float4*>((h ? thi : tlo) + r * TLD + 4 * lane);
       float4 a = *t;
       a.x = fmaf(gt, to_float<Tag>((uint16_t)(x4.x & 0xFFFF)), a.x);
       a.y = fmaf(gt, to_float<Tag>((uint16_t)(x4.x >> 16)), a.y);
@@ -977,7 +1008,7 @@ __global__ void __launch_bounds__(512) k_dw16(
       for (int h = 0; h < NH; ++h) {
         if (!lane_on) continue;
         const float4 wf = wf_of(bt.wv[k][h]);
-        const float4 a4 = *reinterpret_cast<const float4*>((h ? thi : tlo) + r * kTLd + 4 * lane);
+        const float4 a4 = *reinterpret_cast<const float4*>((h ? thi : tlo) + r * TLD + 4 * lane);
         dot = fmaf(wf.x, a4.x, dot);
         dot = fmaf(wf.y, a4.y, dot);
         dot = fmaf(wf.z, a4.z, dot);
@@ -1005,7 +1036,7 @@ __global__ void __launch_bounds__(512) k_dw16(
           if (!lane_on) continue;
           const uint32_t o = 256u * h + 4u * (uint32_t)lane;
           const float4 wf = wf_of(bt.wv[k][h]);
-          const float4 a4 = *reinterpret_cast<const float4*>((h ? thi : tlo) + r * kTLd + 4 * lane);
+          const float4 a4 = *reinterpret_cast<const float4*>((h ? thi : tlo) + r * TLD + 4 * lane);
           const float wo[4] = {wf.x, wf.y, wf.z, wf.w};
           const float ao[4] = {a4.x, a4.y, a4.z, a4.w};
           float mo[4] = {bt.mv[k][h].x, bt.mv[k][h].y, bt.mv[k][h].z, bt.mv[k][h].w};
@@ -1117,8 +1148,10 @@ __global__ void __launch_bounds__(512) k_dw16(
 }  // namespace
 
 // Class splits of the feature gradient: workgroups of 128 batch rows, one per
-// CU, in one round (`kDxWgs` of them; one more would be a second round, as
-// ceil(256 / n_rt) gave at B = 777: 90 us for 45).  On few classes fewer
+// CU, in one round (one more would be a second round, as ceil(256 / n_rt) gave
+// at B = 777: 90 us for 45).  At d = 128 two share a CU once 24 chunks are left
+// to one of 256 (B = 1024, |S| = 32,768, 32 chunks, 47 -> 41 us; with 8 chunks,
+// B = 128, |S| = 65,536, 20 -> 25).  On few classes fewer
 // splits: a split costs its partial sums, written and read again (8 B d bytes
 // at the copy rate, 4.7 MB/us), and saves its share of the 1.2 us that a
 // chunk of 32 classes takes, so their sum is least at
@@ -1126,9 +1159,10 @@ __global__ void __launch_bounds__(512) k_dw16(
 // At B = 128, |S| = 10,000, d = 512 that is 59 splits instead of 256: the sum
 // of the partials takes 5.7 instead of 26.8 us, dX 21.6 instead of 21.0.
 int split_16(int64_t B, int64_t d, int64_t cap) {
-  constexpr int64_t kDxWgs = 256;
-  const int64_t most = kDxWgs / ceil_div(B, kDxRows);   // B <= 8192: at least 4
+  const int64_t n_rt = ceil_div(B, kDxRows);
   const double chunks = (double)ceil_div(cap, kBwKC);
+  const bool two = d == 128 && chunks * (double)n_rt >= 24.0 * 256.0;
+  const int64_t most = (two ? 512 : 256) / n_rt;   // B <= 8192: at least 4
   const int64_t best = (int64_t)ceil(sqrt(1.2 * 4.7e6 / 8.0 * chunks / ((double)B * (double)d)));
   const int64_t ns = best < most ? best : most;
   return (int)(ns < (int64_t)chunks ? ns : (int64_t)chunks);
@@ -1172,7 +1206,7 @@ void launch_bwd16(const StepArgs& a, const StepWs& w, const Margin& mg, float sB
   // Row scales of the logit store from the lse the gradient is normalised with.
   hipLaunchKernelGGL(k_scales, dim3((unsigned)ceil_div(w.n_groups * w.ld_g, 4 * 256)), dim3(256), 0,
                      stream, w.gmax, a.row_lse, B, w.ld_g, w.n_groups, a.n_active, w.gscale);
-  hipLaunchKernelGGL((k_dx16<Tag, WI>), dim3((unsigned)(8 * per_xcd)), dim3(128 * WI), 0, stream,
+  hipLaunchKernelGGL((k_dx16<Tag, WI>), dim3((unsigned)(8 * per_xcd)), dim3(dx_threads(WI)), 0, stream,
                      (const uint16_t*)a.W, w.act_pad, a.n_active, w.inv_w, w.inv_w_max,
                      (const uint16_t*)w.lbuf, w.ld_cos, w.gscale, w.ld_g, B, n_rt, w.n_split,
                      n_tiles, per_xcd, w.dx_part);
