@@ -70,9 +70,8 @@ __shared__ __attribute__((aligned(16))) float wQ0[kBwKC], wQ1[kBwKC], wQ2[kBwKC]
 __shared__ __attribute__((aligned(1024))) uint16_t wG0[kDwCls * kBwKC], wG1[kDwCls * kBwKC],
     wG2[kDwCls * kBwKC];
 
-// The same at d = 128, where a stage is a quarter as large: two workgroups then
-// share a CU (a dX workgroup has two waves there, and alone left half of the
-// SIMDs idle).
+// The same at d = 128, where a stage is a quarter as large, so that two
+// workgroups share a CU (why: at k_dx16).
 constexpr int kRowLd128 = 144;   // 256 B + 32 B
 __shared__ __attribute__((aligned(1024))) uint16_t xV0[kBwKC * kRowLd128],
     xV1[kBwKC * kRowLd128], xV2[kBwKC * kRowLd128];
