@@ -649,14 +649,13 @@ __global__ void __launch_bounds__(kFwdThreads, 2) k_fwd16n(
             tgt[n] = ft;
             tgtc[n] = c;
             ft2[nb] = ft * kLog2e;
+            redt[half][32 * nb + l32] = ft2[nb];   // as the sum below needs it, whatever its value
           }
         }
         acc[nb][4 * g + e] = v;
         mx[nb] = fmaxf(mx[nb], v);
       }
     }
-    // The target's term by the half that holds it, as the sum below needs it.
-    if (ft2[nb] > -INFINITY) redt[half][32 * nb + l32] = ft2[nb];
     mx[nb] = fmaxf(mx[nb], ft2[nb]);
     mx[nb] = fmaxf(mx[nb], __shfl_xor(mx[nb], 32, 64));
     if (half == 0) redm[wave][32 * nb + l32] = mx[nb];

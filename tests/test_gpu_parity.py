@@ -419,6 +419,28 @@ def test_forward_tiles_agree(dev, dtype, d, tau):
     assert torch.equal(out[0][lo:lo + 64], out[1])
 
 
+@pytest.mark.parametrize("dtype,d,tau", [("bf16", 512, None), ("f16", 128, 0.4), ("bf16", 256, 0.4)])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_non_finite_centre_reaches_every_row(dev, dtype, d, tau, bad):
+    """A class centre with a NaN or an infinity has a NaN cosine to every row,
+    so each row's log-sum-exp and the loss are NaN, in both forward kernels and
+    also in the rows that are labelled with the class."""
+    from _gpu_util import make_problem
+    B, C, c = 600, 8000, 4321
+    Xd, Wd, _, _, Ld = make_problem(B, d, C, dtype, 69, device=dev)
+    Ld[130:190:7] = c
+    Wd[c, 3] = bad
+    for rows in (slice(0, B), slice(128, 192)):       # 256-row tiles; 64-row tiles
+        X, L = Xd[rows].contiguous(), Ld[rows].contiguous()
+        print(f"\nnon-finite centre: {dtype} d={d} tau={tau} {bad} rows {rows}", flush=True)
+        shard = _shard(len(X), d, C, 1.0, dtype, "arcface", 0.5, dev=dev, tau=tau)
+        shard.sample(L, 0)
+        shard.forward(X, Wd)
+        torch.cuda.synchronize()
+        assert bool(torch.isnan(shard.row_lse).all())
+        assert bool(torch.isnan(shard.loss).all())
+
+
 # PFC* conflict filter (Sec. 3.3.4, Eq. noise_filtering): some rows sit near
 # the centre of another row's class, so their cosine to that (active)
 # negative is ~0.9 > tau and the logit leaves the row's denominator.
