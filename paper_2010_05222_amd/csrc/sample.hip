@@ -374,10 +374,11 @@ __device__ __forceinline__ Threshold kth_key(Each&& each, int64_t k, uint64_t fr
   }
 }
 
-// The threshold over all keys of the shard's non-positives, recomputed.
-__device__ __attribute__((noinline)) Threshold kth_of_all(const uint64_t* masks, int64_t C,
-                                                          int64_t a, uint64_t seed, int64_t n_neg,
-                                                          ResolveLds& L) {
+// The threshold over all keys of the shard's non-positives, recomputed.  Inlined:
+// as a function it saved its callers' registers on the stack, and a kernel with
+// a stack makes the runtime allocate device memory at its first launch.
+__device__ __forceinline__ Threshold kth_of_all(const uint64_t* masks, int64_t C, int64_t a,
+                                                uint64_t seed, int64_t n_neg, ResolveLds& L) {
   Threshold th = kth_key(
       [&](auto&& f) {
         for (int64_t v = threadIdx.x; v * kPerThread < C; v += kThreads) {

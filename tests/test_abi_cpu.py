@@ -5,6 +5,8 @@ before touching the GPU (no kernel is ever launched by these tests)."""
 import ctypes
 import os
 import re
+import shutil
+import subprocess
 
 import pytest
 import torch
@@ -264,6 +266,19 @@ def test_sample_noalloc_rejects_before_launch(kw, status):
     with pytest.raises(pfc.PfcError) as e:
         pfc.pfc_sample_noalloc(**_noalloc_args(**kw))
     assert e.value.status == status
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="no hipcc")
+def test_sampler_kernels_use_no_private_memory():
+    """No kernel of the sampler has a stack or spills: the runtime would allocate
+    device memory for it at the first launch, behind calls that allocate nothing."""
+    from paper_2010_05222_amd import build
+    out = subprocess.run(["hipcc", *build.HIPCC_FLAGS, "--cuda-device-only", "-S", "-o", "-",
+                          os.path.join(build.CSRC, "sample.hip")], capture_output=True, text=True,
+                         check=True).stdout
+    sizes = re.findall(r"\.private_segment_fixed_size: *(\d+)", out)
+    assert len(sizes) >= 6 and set(sizes) == {"0"}, sizes
+    assert set(re.findall(r"\.uses_dynamic_stack: *(\w+)", out)) == {"false"}
 
 
 def test_noalloc_limit_matches_header():
