@@ -25,7 +25,7 @@
 //
 // This replaces ten launches (clear, mark, plan, key digits and histogram, top
 // digit, collect, refine, scan, write, remap), whose time was mostly that of
-// empty launches: 10 K classes 55 -> 13 us, 100 K 46 -> 15 us, 2M 49 -> 25 us.
+// empty launches: 10 K classes 55 -> 13 us, 100 K 46 -> 16 us, 2M 49 -> 23 us, 8M 75 -> 53 us.
 #include <math.h>
 
 #include "pfc_internal.h"
@@ -311,7 +311,6 @@ struct Threshold {
   uint64_t key;
   int64_t ties;
   bool all_ties;
-  bool all_keys;    // found over all keys: the candidates do not decide
   __device__ bool below(uint64_t k) const { return k < key || (all_ties && k == key); }
   __device__ bool tie(uint64_t k) const { return !all_ties && k == key; }
 };
@@ -349,7 +348,7 @@ __device__ __forceinline__ Threshold kth_key(Each&& each, int64_t k, uint64_t fr
     k -= L.found[1];
     const int64_t n = L.found[2];
     to = from + ((1ull << shift) - 1ull);
-    if (shift == 0) return Threshold{from, k, k == n, false};
+    if (shift == 0) return Threshold{from, k, k == n};
     if (n <= kLastKeys) {
       each([&](uint64_t key) {
         if (key < from || key > to) return;
@@ -365,7 +364,7 @@ __device__ __forceinline__ Threshold kth_key(Each&& each, int64_t k, uint64_t fr
           less += L.last[i] < key;
           equal += L.last[i] == key;
         }
-        if (less < k && k <= less + equal) L.th = Threshold{key, k - less, k == less + equal, false};
+        if (less < k && k <= less + equal) L.th = Threshold{key, k - less, k == less + equal};
       }
       __syncthreads();
       return L.th;
@@ -379,7 +378,7 @@ __device__ __forceinline__ Threshold kth_key(Each&& each, int64_t k, uint64_t fr
 // a stack makes the runtime allocate device memory at its first launch.
 __device__ __forceinline__ Threshold kth_of_all(const uint64_t* masks, int64_t C, int64_t a,
                                                 uint64_t seed, int64_t n_neg, ResolveLds& L) {
-  Threshold th = kth_key(
+  return kth_key(
       [&](auto&& f) {
         for (int64_t v = threadIdx.x; v * kPerThread < C; v += kThreads) {
           uint64_t keys[20];
@@ -389,8 +388,6 @@ __device__ __forceinline__ Threshold kth_of_all(const uint64_t* masks, int64_t C
         }
       },
       n_neg, 0, ~0ull, L);
-  th.all_keys = true;
-  return th;
 }
 
 // From the shard's |P|, its non-positives below the window and its candidates:
@@ -524,7 +521,7 @@ __global__ void __launch_bounds__(kThreads) k_sample_one(
   int64_t n_neg;
   const int64_t k = candidate_rank(budget, n_pos, (int64_t)(total & 0xFFFFu) - n_pos, total >> 16,
                                    &n_neg);
-  Threshold th{0, 0, false, false};
+  Threshold th{0, 0, false};
   if (k > 0) {   // kth_key's first barrier completes the list
     th = kth_key(
         [&](auto&& f) {
@@ -613,7 +610,7 @@ __global__ void __launch_bounds__(kThreads) k_resolve_write(
     for_candidates(w.cand_key, n_groups, lane_bits,
                    [&](int64_t g) { return start[g + 1] - start[g]; }, f);
   };
-  Threshold th{0, 0, false, false};
+  Threshold th{0, 0, false};
   if (k > 0) {
     if (fits)
       from_memory([&](int64_t g, uint32_t i, uint64_t key) { list[start[g] + i] = key; });
@@ -686,89 +683,186 @@ __global__ void __launch_bounds__(kThreads) k_resolve_write(
   map_labels(labels, B, C, a, (int64_t)blockIdx.x * kSpan, 1, &out, where, cap, labels_mapped);
 }
 
-// More groups: the threshold, then the groups' counts (kept in grp_out and
-// grp_tie_off), turned into their offsets in tiles of one group per thread
-// with running totals.  One workgroup, 1 << lane_bits <= 64 lanes per group.
+// More groups: the threshold, then each group's classes in S and ties, turned
+// into offsets.  One workgroup, 1 << lane_bits <= 64 lanes of a wave per group.
+// Bound by memory latency: the candidates of up to kHeldGroups groups are read
+// once, into LDS, if they fit, and counted there by votes (8M classes, B = 1024:
+// 22 us; 38 with two passes over memory for the threshold and a third that
+// summed each group's counts by lane moves).  LDS holds the upper
+// 32 bits of a candidate's place in the window; where they do not tell the
+// threshold from a neighbour (4e-6 of draws), and for longer lists, every pass
+// reads memory, eight groups' loads in flight per thread.
+constexpr int kHeldGroups = 8 * kThreads;
+constexpr int kHeldPer = kHeldGroups / kThreads;
+constexpr int kHeldMax = 28672;
 __global__ void __launch_bounds__(kThreads) k_resolve(SampleWs w, int64_t n_groups, int lane_bits,
                                                       int64_t C, int64_t a, uint64_t seed,
                                                       int64_t budget, uint32_t lo, uint32_t hi,
                                                       int64_t cap, int32_t* n_active) {
   __shared__ ResolveLds L;
+  __shared__ uint32_t list[kHeldMax];
+  __shared__ uint16_t start[kHeldGroups + 1];   // of each group's candidates in the list
+  __shared__ uint16_t counts[kHeldGroups];      // of the held candidates that are taken
+  __shared__ uint32_t scan3[3][16];
   const int t = threadIdx.x;
   const int lanes = 1 << lane_bits, sub = t & (lanes - 1);
-  uint32_t pos = 0, below = 0, cand = 0, sum;
-  for (int64_t g = t; g < n_groups; g += kThreads) {
-    const uint32_t s = w.grp_sure[g];
-    pos += s >> 16;
-    below += (s & 0xFFFFu) - (s >> 16);
-    cand += w.grp_cand[g];
+  const uint64_t group_lanes =
+      lanes == 64 ? ~0ull : ((1ull << lanes) - 1ull) << (lane_id() & ~(lanes - 1));
+  const uint64_t from = (uint64_t)lo << 32, to = ((uint64_t)hi << 32) | 0xFFFFFFFFu;
+  // Eight consecutive groups per thread and pass.
+  uint32_t v[3] = {0u, 0u, 0u}, sum[3], nc[kHeldPer];
+#pragma unroll 1
+  for (int64_t base = kHeldPer * t; base < n_groups; base += kHeldGroups) {
+    uint32_t sure[kHeldPer];
+#pragma unroll
+    for (int i = 0; i < kHeldPer; ++i) {
+      sure[i] = base + i < n_groups ? w.grp_sure[base + i] : 0u;
+      nc[i] = base + i < n_groups ? w.grp_cand[base + i] : 0u;
+    }
+#pragma unroll
+    for (int i = 0; i < kHeldPer; ++i) {
+      v[0] += sure[i] >> 16;
+      v[1] += (sure[i] & 0xFFFFu) - (sure[i] >> 16);
+      v[2] += nc[i];
+    }
   }
-  block_scan<16>(pos, L.scan, &sum);
-  pos = sum;
-  block_scan<16>(below, L.scan, &sum);
-  below = sum;
-  block_scan<16>(cand, L.scan, &sum);
-  cand = sum;
+  block_scan3<16>(v, scan3, sum);
+  const uint32_t pos = sum[0], below = sum[1], cand = sum[2];
   int64_t n_neg;
   const int64_t k = candidate_rank(budget, pos, below, cand, &n_neg);
-  Threshold th{0, 0, false, false};
-  if (k > 0) {
+  bool held = k > 0 && n_groups <= kHeldGroups && cand <= (uint32_t)kHeldMax;
+  Threshold th{0, 0, false};
+  if (held) {
+#pragma unroll
+    for (int i = 0; i < kHeldPer; ++i) {
+      if (kHeldPer * t + i >= n_groups) break;
+      start[kHeldPer * t + i] = (uint16_t)v[2];
+      v[2] += nc[i];
+    }
+    if (t == 0) start[n_groups] = (uint16_t)cand;
+    __syncthreads();
+    // The window is hi - lo + 1 <= 2^drop times 2^32 keys.
+    const int drop = hi > lo ? 32 - __clz((int)(hi - lo)) : 0;
+    for_candidates(w.cand_key, n_groups, lane_bits,
+                   [&](int64_t g) { return (uint32_t)start[g + 1] - start[g]; },
+                   [&](int64_t g, uint32_t i, uint64_t key) {
+                     list[start[g] + i] = (uint32_t)((key - from) >> drop);
+                   });
+    // kth_key's first barrier completes the list.
+    const Threshold at = kth_key(
+        [&](auto&& f) {
+          for (uint32_t i = t; i < cand; i += kThreads) f((uint64_t)list[i]);
+        },
+        k, 0, 0xFFFFFFFFull, L);
+    held = at.all_ties;   // all candidates with these 32 bits are taken
+    if (held) {
+      th = Threshold{from + (((at.key + 1) << drop) - 1), at.ties, true};
+#pragma unroll 1
+      for (int g = t >> lane_bits; g < (int)n_groups; g += kThreads >> lane_bits) {
+        const uint32_t first = start[g], n = start[g + 1] - first;
+        uint32_t s = 0;
+        for (uint32_t i = sub; i < n; i += lanes)
+          s += __popcll(__ballot(list[first + i] <= (uint32_t)at.key) & group_lanes);
+        if (sub == 0) counts[g] = (uint16_t)s;   // sub 0 is in every vote of the group
+      }
+    }
+  }
+  if (!held && k > 0) {
     th = kth_key(
         [&](auto&& f) {
           for_candidates(w.cand_key, n_groups, lane_bits, [&](int64_t g) { return w.grp_cand[g]; },
                          [&](int64_t, uint32_t, uint64_t key) { f(key); });
         },
-        k, (uint64_t)lo << 32, ((uint64_t)hi << 32) | 0xFFFFFFFFu, L);
-  } else if (k < 0) {
-    th = kth_of_all(w.masks, C, a, seed, n_neg, L);
-  }
+        k, from, to, L);
+    constexpr int U = 8;
+    const int64_t step = kThreads >> lane_bits;
 #pragma unroll 1
-  for (int64_t g = t >> lane_bits; g < n_groups; g += kThreads >> lane_bits) {
-    uint32_t s = 0, e = 0;
-    if (k > 0) {
-      const uint32_t n = w.grp_cand[g];
-      for (uint32_t i = sub; i < n; i += lanes) {
-        const uint64_t key = w.cand_key[g * kGroupClasses + i];
-        s += th.below(key);
-        e += th.tie(key);
+    for (int64_t g0 = t >> lane_bits; g0 < n_groups; g0 += U * step) {
+      uint32_t n[U], s[U], e[U];
+      uint64_t key[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t g = g0 + u * step;
+        n[u] = g < n_groups ? w.grp_cand[g] : 0u;
+        s[u] = g < n_groups ? w.grp_sure[g] & 0xFFFFu : 0u;
       }
-    } else if (k < 0) {
-      for (int v = sub; v < kGroupThreads; v += lanes) {
-        const int64_t at = g * kGroupThreads + v;
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        key[u] = sub < n[u] ? w.cand_key[(g0 + u * step) * kGroupClasses + sub] : 0;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        s[u] += __popcll(__ballot(sub < n[u] && th.below(key[u])) & group_lanes);
+        e[u] = __popcll(__ballot(sub < n[u] && th.tie(key[u])) & group_lanes);
+#pragma unroll 1
+        for (uint32_t i = sub + lanes; i < n[u]; i += lanes) {   // longer than expected
+          const uint64_t more = w.cand_key[(g0 + u * step) * kGroupClasses + i];
+          s[u] += __popcll(__ballot(th.below(more)) & group_lanes);
+          e[u] += __popcll(__ballot(th.tie(more)) & group_lanes);
+        }
+        if (sub == 0 && g0 + u * step < n_groups) {
+          w.grp_out[g0 + u * step] = s[u];
+          w.grp_tie_off[g0 + u * step] = e[u];
+        }
+      }
+    }
+  } else if (!held) {
+    if (k < 0) th = kth_of_all(w.masks, C, a, seed, n_neg, L);
+#pragma unroll 1
+    for (int64_t g = t >> lane_bits; g < n_groups; g += kThreads >> lane_bits) {
+      uint32_t s = 0, e = 0;
+      for (int u = sub; k < 0 && u < kGroupThreads; u += lanes) {
+        const int64_t at = g * kGroupThreads + u;
         const uint2 st = settle_all((uint32_t)(w.masks[at] & 0xFFFFu), at * kPerThread, C, a,
                                     seed, th);
         s += __popc(st.x);
         e += __popc(st.y);
       }
-    }
-    for (int off = 1; off < lanes; off <<= 1) {
-      s += __shfl_xor(s, off, 64);
-      e += __shfl_xor(e, off, 64);
-    }
-    if (sub == 0) {
-      w.grp_out[g] = s + (k >= 0 ? w.grp_sure[g] & 0xFFFFu : 0u);
-      w.grp_tie_off[g] = e;
+      for (int off = 1; off < lanes; off <<= 1) {
+        s += __shfl_xor(s, off, 64);
+        e += __shfl_xor(e, off, 64);
+      }
+      if (sub == 0) {
+        w.grp_out[g] = k < 0 ? s : w.grp_sure[g] & 0xFFFFu;
+        w.grp_tie_off[g] = e;
+      }
     }
   }
   __syncthreads();
+  const bool part = !th.all_ties && th.ties;   // only some of the ties are taken
   uint64_t all_tie = 0, all_sel = 0;
 #pragma unroll 1
-  for (int64_t base = 0; base < n_groups; base += kThreads) {
-    const int64_t g = base + t;
-    const uint32_t s = g < n_groups ? w.grp_out[g] : 0u;
-    const uint32_t e = g < n_groups ? w.grp_tie_off[g] : 0u;
-    const uint64_t tb = all_tie + block_scan<16>(e, L.scan, &sum);
-    all_tie += sum;
-    const uint64_t ob =
-        all_sel + block_scan<16>(s + taken(th, (int64_t)tb, e), L.scan, &sum);
-    all_sel += sum;
-    if (g < n_groups) {
-      w.grp_out[g] = (uint32_t)ob;
-      w.grp_tie_off[g] = (uint32_t)tb;
+  for (int64_t base = kHeldPer * t; base - kHeldPer * t < n_groups; base += kHeldGroups) {
+    uint32_t s[kHeldPer], e[kHeldPer], s_all = 0, e_all = 0, total;
+#pragma unroll
+    for (int i = 0; i < kHeldPer; ++i) {
+      const int64_t g = base + i;
+      const bool in = g < n_groups;
+      s[i] = !in ? 0u : held ? counts[g] + (w.grp_sure[g] & 0xFFFFu) : w.grp_out[g];
+      e[i] = in && part ? w.grp_tie_off[g] : 0u;
+      e_all += e[i];
+    }
+    if (part) {
+      uint64_t tb = all_tie + block_scan<16>(e_all, L.scan, &total);
+      all_tie += total;
+#pragma unroll
+      for (int i = 0; i < kHeldPer; ++i) {
+        if (base + i < n_groups) w.grp_tie_off[base + i] = (uint32_t)tb;
+        s[i] += taken(th, (int64_t)tb, e[i]);
+        tb += e[i];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < kHeldPer; ++i) s_all += s[i];
+    uint64_t ob = all_sel + block_scan<16>(s_all, L.scan, &total);
+    all_sel += total;
+#pragma unroll
+    for (int i = 0; i < kHeldPer; ++i) {
+      if (base + i < n_groups) w.grp_out[base + i] = (uint32_t)ob;
+      ob += s[i];
     }
   }
   if (t == 0) {
-    *w.state = SampleState{th.key, th.ties, k, th.all_ties, th.all_keys};
+    *w.state = SampleState{th.key, th.ties, k, th.all_ties};
     *n_active = clamp_count(all_sel, cap);
   }
 }
@@ -785,7 +879,7 @@ __global__ void __launch_bounds__(kThreads) k_write(
   const int64_t n_spans = ceil_div(n_groups, (int64_t)kSpanGroups);
   const int n = (int)(n_spans - s0 < run ? n_spans - s0 : run);
   const SampleState z = *w.state;
-  const Threshold th{z.thresh, z.ties, z.all_ties, z.all_keys};
+  const Threshold th{z.thresh, z.ties, z.all_ties};
   if (t < n) out[t] = w.grp_out[(s0 + t) * kSpanGroups];
 #pragma unroll 1
   for (int i = 0; i < n; ++i) {

@@ -274,6 +274,18 @@ def test_sampler_group_edges(dev, B, C, a, r):
     _sampler_case(dev, labels, C, a, r, 64)
 
 
+@pytest.mark.parametrize("B,C,a,r", [
+    (128, 3000001, 1, 0.1),           # above 512 groups, candidates held in LDS
+    (8192, 8000001, 2, 0.5),          # 22,300 candidates: held
+    (8192, 20000001, 0, 0.5),         # 30,600: more than are held
+    (64, 8192 * 4096, 0, 0.001),      # the most groups whose candidates are held
+    (64, 8192 * 4096 + 1, 3, 0.001),
+])
+def test_sampler_above_512_groups(dev, B, C, a, r):
+    labels = np.random.default_rng(70).integers(a - 1, a + C + 1, size=B)
+    _sampler_case(dev, labels, C, a, r, 71)
+
+
 @pytest.mark.parametrize("C,b,seed", [
     (1000, 1, 4572), (9001, 1, 60), (1100003, 1, 2488), (2200003, 1, 4342),
     (100, 99, 10856), (2200003, 2200002, 413),
