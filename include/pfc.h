@@ -67,6 +67,8 @@ typedef enum {
  * `active_cap` every other call must be given.  Also reports the workspace
  * size needed by a step with these sizes and compute dtype; every call that
  * takes `ws` needs it at a 256-byte aligned device address (hipMalloc's are).
+ * The size does not fall when B or C grows, so a workspace made for the
+ * largest batch also serves smaller ones.
  *
  * 1 <= B <= PFC_MAX_BATCH; 1 <= C <= PFC_MAX_CLASSES; 0 < r <= 1;
  * 8 <= d <= 1024 with d a multiple of 8 (else PFC_ERR_INVALID_ARG); compute

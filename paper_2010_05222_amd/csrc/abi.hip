@@ -87,7 +87,9 @@ WsLayout ws_layout(int64_t B, int64_t d, int64_t C, int64_t cap, int compute) {
   L.off_cos = take((size_t)B * L.ld_cos * cos_elt);
   L.off_stats = take(compute == PFC_F32 ? 0 : (size_t)B * L.n_ctiles * 8);
   L.off_tgt = take((size_t)B * 4);
-  L.off_dx = take((size_t)L.n_split * B * d * 4);
+  // Room for any smaller batch's partial sums too (more splits of fewer rows).
+  L.off_dx = take((size_t)(compute == PFC_F32 ? part_rows_f32(B, cap) : part_rows_16(B, d, cap)) *
+                  d * 4);
   L.off_loss = take((size_t)B * 4);
   L.off_tgtc = take((size_t)B * 4);
   L.off_gmax = take(compute == PFC_F32 ? 0 : (size_t)L.n_lgroups * L.ld_g * 4);

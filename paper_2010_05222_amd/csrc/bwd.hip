@@ -1157,14 +1157,32 @@ __global__ void __launch_bounds__(512, WI == 1 ? 4 : 2) k_dw16(
 // sqrt(1.2 chunks 4.7e6 / (8 B d)).
 // At B = 128, |S| = 10,000, d = 512 that is 59 splits instead of 256: the sum
 // of the partials takes 5.7 instead of 26.8 us, dX 21.6 instead of 21.0.
+namespace {
+// Workgroups of one round; and how many elements of a partial sum cost a chunk's time.
+int64_t dx_round(int64_t n_rt, int64_t d, double chunks) {
+  return d == 128 && chunks * (double)n_rt >= 24.0 * 256.0 ? 512 : 256;
+}
+constexpr double kChunkElements = 1.2 * 4.7e6 / 8.0;
+}  // namespace
+
 int split_16(int64_t B, int64_t d, int64_t cap) {
   const int64_t n_rt = ceil_div(B, kDxRows);
   const double chunks = (double)ceil_div(cap, kBwKC);
-  const bool two = d == 128 && chunks * (double)n_rt >= 24.0 * 256.0;
-  const int64_t most = (two ? 512 : 256) / n_rt;   // B <= 8192: at least 4
-  const int64_t best = (int64_t)ceil(sqrt(1.2 * 4.7e6 / 8.0 * chunks / ((double)B * (double)d)));
+  const int64_t most = dx_round(n_rt, d, chunks) / n_rt;   // B <= 8192: at least 4
+  const int64_t best = (int64_t)ceil(sqrt(kChunkElements * chunks / ((double)B * (double)d)));
   const int64_t ns = best < most ? best : most;
   return (int)(ns < (int64_t)chunks ? ns : (int64_t)chunks);
+}
+
+// splits x B is at most each of the three: a round's rows, ceil(x) B <= x B + B, and
+// chunks x B; none of them falls when B grows.
+int64_t part_rows_16(int64_t B, int64_t d, int64_t cap) {
+  const double chunks = (double)ceil_div(cap, kBwKC);
+  const int64_t round = dx_round(ceil_div(B, kDxRows), d, chunks) * kDxRows;
+  const int64_t best = (int64_t)ceil(sqrt(kChunkElements * chunks * (double)B / (double)d)) + B;
+  const int64_t one_each = (int64_t)chunks * B;
+  const int64_t rows = best < round ? best : round;
+  return rows < one_each ? rows : one_each;
 }
 
 namespace {

@@ -623,6 +623,11 @@ int split_f32(int64_t B, int64_t cap) {
   return (int)(ns < 1 ? 1 : ns);
 }
 
+int64_t part_rows_f32(int64_t B, int64_t cap) {
+  const int64_t most = 512 * kDxRows, one_each = ceil_div(cap, kChunk) * B;
+  return one_each < most ? one_each : most;
+}
+
 hipError_t launch_forward_f32(const StepArgs& a, const StepWs& w, hipStream_t stream) {
   const int B = (int)a.B, d = (int)a.d;
   const Margin mg{a.s, a.m, cosf(a.m), sinf(a.m), a.margin};

@@ -140,9 +140,12 @@ hipError_t launch_backward(const StepArgs& a, const StepWs& w, hipStream_t strea
 // The fp32 path (f32.hip).
 hipError_t launch_forward_f32(const StepArgs& a, const StepWs& w, hipStream_t stream);
 hipError_t launch_backward_f32(const StepArgs& a, const StepWs& w, hipStream_t stream);
-// Class splits of the feature gradient.
+// Class splits of the feature gradient, and a bound on the rows of its partial
+// sums, splits x batch, that holds for every batch up to B.
 int split_f32(int64_t B, int64_t cap);
 int split_16(int64_t B, int64_t d, int64_t cap);
+int64_t part_rows_f32(int64_t B, int64_t cap);
+int64_t part_rows_16(int64_t B, int64_t d, int64_t cap);
 
 // Measurement hook (pfc_timing_begin / pfc_timing_end): launchers bracket a
 // kernel id's launches with these calls; both are no-ops unless armed.

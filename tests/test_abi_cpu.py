@@ -56,6 +56,20 @@ def test_workspace_and_capacity_of_each_workload(name):
     assert nbytes < 2 * (cfg["B"] * cap * elt + cfg["C"] * 10) + (256 << 20)
 
 
+@pytest.mark.parametrize("code,d", [(0, 8), (0, 512), (0, 1024), (1, 128), (2, 256), (1, 512)])
+@pytest.mark.parametrize("C,r", [(30, 0.5), (1000, 0.1), (10000, 0.1), (100000, 0.1),
+                                 (300000, 0.2), (1000000, 1.0)])
+def test_workspace_serves_smaller_batches(C, r, code, d):
+    """The size never falls when the batch grows, although the feature
+    gradient takes fewer class splits then."""
+    top = 4096 if code == pfc.PFC_F32 else pfc.PFC_MAX_BATCH
+    batches = sorted({*range(1, 300), *range(300, top + 1, 61), *range(128, top + 1, 128),
+                      *range(129, top + 1, 128), top})
+    sizes = [pfc.pfc_workspace_bytes(B, d, C, r, code)[0] for B in batches]
+    falls = [(a, b) for a, b, m, n in zip(batches, batches[1:], sizes, sizes[1:]) if n < m]
+    assert not falls, falls[:5]
+
+
 def test_batch_limit_matches_header():
     text = open(HEADER).read()
     assert int(re.search(r"#define PFC_MAX_BATCH (\d+)", text).group(1)) == pfc.PFC_MAX_BATCH
