@@ -821,7 +821,13 @@ hipError_t launch_forward(const StepArgs& a, const StepWs& w, hipStream_t stream
   // pipelined / narrow: |S| = 10,000, B = 128 20.0 / 15.6; 8,192, 512 21.1 /
   // 20.6; 32,768, 128 25.5 / 25.3; with 1,024 tiles 65,536, 128 39.2 / 41.3,
   // 8,192, 1024 22.5 / 32.2).
-  const bool narrow = w.n_ctiles * ceil_div(B, kNarrowRows) <= 512;
+  // They load X as the caller gave it straight to LDS, 16 bytes at a time, which a
+  // batch that starts inside a 16-byte piece does not allow; the pipelined tile
+  // loads the workspace's copy, with the same results.  (The copy in the narrow
+  // tile too: d = 256, |S| = 10,000, B = 256 25.4 us for 23.8, |S| = 20,000, B = 100
+  // 27 for 23.3.)
+  const bool narrow =
+      w.n_ctiles * ceil_div(B, kNarrowRows) <= 512 && ((uintptr_t)a.X & 15) == 0;
   const int n_rt = (int)ceil_div(B, narrow ? kNarrowRows : kFwdBN);
   const int64_t n_tiles = w.n_ctiles * n_rt;
   const int64_t per_xcd = ceil_div(n_tiles, 8);

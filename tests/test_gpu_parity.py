@@ -137,6 +137,31 @@ def test_f32_rows_need_no_16_byte_alignment(dev):
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("B,d,K,dtype", [
+    (70, 128, 1500, "f16"), (70, 256, 1500, "bf16"), (70, 512, 1500, "bf16"),   # 64-row tiles, if aligned
+    (513, 256, 8192, "bf16"),                                                   # 256-row tiles
+])
+def test_16_bit_batch_needs_no_16_byte_alignment(dev, B, d, K, dtype):
+    """Embeddings that start 2 or 8 bytes past a 16-byte boundary give the
+    aligned ones' results bit for bit."""
+    from _gpu_util import make_problem
+    Xd, Wd, Md, _, Ld = make_problem(B, d, K, dtype, 72, device=dev)
+    outs = []
+    for off in (0, 1, 4):
+        print(f"\nbatch alignment: B={B} d={d} K={K} {dtype} offset {off}", flush=True)
+        X = torch.empty(Xd.numel() + 8, dtype=Xd.dtype, device=dev)[off:off + Xd.numel()]
+        X = X.view_as(Xd).copy_(Xd)
+        assert X.data_ptr() % 16 == 2 * off
+        W, M = Wd.clone(), Md.clone()
+        shard = _shard(B, d, K, 1.0, dtype, "arcface", 0.5, dev=dev)
+        shard.step(X, Ld, W, M, 72)
+        torch.cuda.synchronize()
+        outs.append((shard.loss, shard.row_lse, shard.dX, W, M))
+    for out in outs[1:]:
+        for x, y in zip(out, outs[0]):
+            assert torch.equal(x, y)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_single_class_shard(dev, dtype):
     # The smallest shard: one class, taken at r = 1.  Rows labelled with it
