@@ -612,7 +612,7 @@ __global__ void __launch_bounds__(512, WI == 1 ? 4 : 2) k_dw16(
   const int K = *n_active_p;
   const int64_t j0 = (int64_t)blockIdx.x * CLS;
   if (j0 >= K) return;
-  // Start gates (n_gate > 0 on a long grid, one workgroup per CU): workgroup
+  // Start gates (n_gate > 0 on a long grid of one workgroup per CU, d >= 256): workgroup
   // 2 i + 1 of the first wave starts once workgroup 2 i has finished its
   // contraction, which it signals by writing this launch's number to gate[i].
   // Otherwise all CUs run the contraction and then the memory-bound update in
@@ -621,7 +621,7 @@ __global__ void __launch_bounds__(512, WI == 1 ? 4 : 2) k_dw16(
   // time from the start.  The wait is bounded (kGateSpins polls), and the
   // results never depend on it: a gate that is never opened, or holds the
   // number by chance, only changes when the workgroup starts.
-  const bool gated = (int)blockIdx.x < 2 * n_gate;
+  const bool gated = WI > 1 && (int)blockIdx.x < 2 * n_gate;
   if (gated && (blockIdx.x & 1)) {
     if (threadIdx.x == 0) {
       const int32_t* g = gate + blockIdx.x / 2;
@@ -1156,7 +1156,12 @@ __global__ void __launch_bounds__(512, WI == 1 ? 4 : 2) k_dw16(
 // chunk of 32 classes takes, so their sum is least at
 // sqrt(1.2 chunks 4.7e6 / (8 B d)).
 // At B = 128, |S| = 10,000, d = 512 that is 59 splits instead of 256: the sum
-// of the partials takes 5.7 instead of 26.8 us, dX 21.6 instead of 21.0.
+// of the partials takes 5.7 instead of 26.8 us, dX 21.6 instead of 21.0.  The 1.2
+// us are a chunk's at d = 512.  With half or twice that, dX and its sum together
+// change by at most 7 % either way at any d (B = 32 to 1024, |S| = 1,000 to 120,000;
+// d = 128, B = 128, |S| = 50,000 32.5 us, 30.9 with 0.6; B = 1024, |S| = 4,096 29.0, 30.8).
+// The counts are those of 256 CUs whatever the device has, since the layout of the
+// workspace follows from them.
 namespace {
 // Workgroups of one round; and how many elements of a partial sum cost a chunk's time.
 int64_t dx_round(int64_t n_rt, int64_t d, double chunks) {
@@ -1200,13 +1205,19 @@ void launch_bwd16(const StepArgs& a, const StepWs& w, const Margin& mg, float sB
                   hipStream_t stream) {
   const int B = (int)a.B;
   // Start gates on grids of at least four waves of one workgroup per CU; each
-  // launch writes a number of its own to the gates it opens.
+  // launch writes a number of its own to the gates it opens.  Not at d = 128,
+  // where two workgroups share a CU, so that one already updates while the other
+  // contracts: B = 1024, |S| = 131,072 107 us with gates, 101 without; B = 4096 310,
+  // 286; |S| = 262,144, B = 1024 204, 198 (219 with gates for all resident pairs).
   static std::atomic<int> launches{0};
   const int n_cu = device_cu_count();
-  // A workgroup fills its CU.  A shard whose 128-class tiles leave half of the
-  // CUs idle goes in tiles of 64 or 32 classes (d = 512, us with 128 -> now:
+  // A shard whose 128-class tiles leave half of the CUs without a workgroup goes
+  // in tiles of 64 or 32 classes (d = 512, us with 128 -> now:
   // |S| = 8,192, B = 128 28 -> 17, B = 1024 52 -> 34, B = 4096 140 -> 102; |S| =
-  // 16,384 34 -> 26, 56 -> 46, 149 -> 134).  The last round of a longer grid
+  // 16,384 34 -> 26, 56 -> 46, 149 -> 134).  Also at d = 128, whose two workgroups
+  // per CU share its matrix cores: up to half of 512 workgroups is worse there
+  // (|S| = 16,384, B = 1024 29 -> 36, B = 4096 74 -> 104; |S| = 32,768, B = 1024 37 ->
+  // 39, but B = 128 21.8 -> 20.6).  The last round of a longer grid
   // does not: cut that way in the same kernel it made the full tiles 2 % slower,
   // in a launch of its own it cost what it saved (|S| = 100,000 with a master
   // 311 -> 304 us, |S| = 45,000, d = 256 66 -> 68).
@@ -1214,7 +1225,7 @@ void launch_bwd16(const StepArgs& a, const StepWs& w, const Margin& mg, float sB
   const int n_slots = n_cu > 0 ? n_cu : 256;
   const int cls = tiles * 4 <= n_slots ? 32 : tiles * 2 <= n_slots ? 64 : kDwCls;
   const int n_gate =
-      (n_cu > 0 && tiles >= 4LL * n_cu) ? (n_cu / 2 < kDwGates ? n_cu / 2 : kDwGates) : 0;
+      (WI > 1 && n_cu > 0 && tiles >= 4LL * n_cu) ? (n_cu / 2 < kDwGates ? n_cu / 2 : kDwGates) : 0;
   const int epoch = 1 + (launches.fetch_add(1, std::memory_order_relaxed) & 0x3FFFFFFF);
   const int n_rt = (int)ceil_div(B, kDxRows);
   const int64_t n_tiles = (int64_t)n_rt * w.n_split;
