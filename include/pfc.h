@@ -120,8 +120,7 @@ int pfc_sample(const int64_t* labels, int64_t B, int64_t C,
  * C above PFC_NOALLOC_MAX_CLASSES is PFC_ERR_SCRATCH (checked before any
  * launch; use pfc_sample with a workspace instead).  The call allocates
  * nothing and enqueues the same kernels as pfc_sample; the scratch keeps the
- * last call's contents and every call clears what must start at zero.  All
- * calls on one device share the one scratch: calls that overlap on a device
+ * last call's contents, which no call relies on.  All calls on one device share the one scratch: calls that overlap on a device
  * (concurrent streams, or host threads) race and give undefined results.
  */
 #define PFC_NOALLOC_MAX_CLASSES (1LL << 21)
@@ -207,8 +206,10 @@ const char* pfc_status_string(int status);
  */
 typedef enum {
   PFC_K_SAMPLE = 0,     /* the whole sampling + remap sequence of pfc_sample */
-  PFC_K_PREP = 1,       /* inverse norms of X rows and active W rows */
-  PFC_K_FWD_GEMM = 2,   /* cosine contraction + margin + per-tile softmax statistics */
+  PFC_K_PREP = 1,       /* 16-bit paths: inverse norms and operand copies of X, padded ids
+                           (no launch in fp32, whose forward sums the norms of both sides) */
+  PFC_K_FWD_GEMM = 2,   /* cosine contraction, norms of the active W rows; 16-bit: + margin
+                           + per-tile softmax statistics */
   PFC_K_LSE = 3,        /* per-row log-sum-exp and the loss */
   PFC_K_DX_GEMM = 4,    /* split-K contraction of the feature gradient */
   PFC_K_DX_FINAL = 5,   /* split reduction + normalisation backward of X */

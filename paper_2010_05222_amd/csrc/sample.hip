@@ -17,15 +17,17 @@
 //              order, and the labels' places in it.
 // A shard of at most four groups does both in one launch (k_sample_one), and one with
 // more than kMergeGroups groups finds the threshold once (k_resolve) before
-// k_write.  If the count below the window or up to its end turns out wrong
-// (3e-7 of all draws, 5e-5 of those with a budget of one), the threshold is
-// found over all keys, recomputed: slow, and the same result.  When the budget
-// is the whole shard nothing is drawn (k_take_all).  No host synchronisation,
-// and no state that has to be cleared first.
+// k_write.  If the count below the window or up to its end turns out wrong, the
+// threshold is found over all keys, recomputed: 2.6 ms per million classes, and
+// the same result.  That is 6e-7 of draws, but 2e-6 with a budget of 100 classes,
+// 8e-6 with 10 and 5e-5 with one; and where only a few classes are left out, 2e-6
+// with 100 of them, 4e-5 with 10 and 5e-4 with two.  When the budget is the whole
+// shard nothing is drawn (k_take_all).  No host synchronisation, and no state
+// that has to be cleared first.
 //
 // This replaces ten launches (clear, mark, plan, key digits and histogram, top
 // digit, collect, refine, scan, write, remap), whose time was mostly that of
-// empty launches: 10 K classes 55 -> 13 us, 100 K 46 -> 16 us, 2M 49 -> 23 us, 8M 75 -> 53 us.
+// empty launches: 10 K classes 55 -> 13 us, 100 K 46 -> 16 us, 2M 50 -> 23 us, 8M 76 -> 51 us.
 #include <math.h>
 
 #include "pfc_internal.h"
@@ -915,8 +917,9 @@ __global__ void __launch_bounds__(256) k_take_all(const int64_t* labels, int64_t
 // keys below t is binomial with mean F = t C; the threshold lies where the
 // non-positives among them are b - |P|, that is where F is between b - |P|
 // (no positive below) and b (all of them), |P| <= min(B, C), give or take the
-// deviation of F: five of its standard deviations (at F = b, where it is no
-// smaller) and, for small budgets, four classes more.
+// deviation of F: five of its standard deviations at F = b, and four classes
+// more.  (At the window's ends the deviation is another one, by a good part of
+// itself where b or C - b is below a hundred: hence the rates of the misses above.)
 void sample_window(int64_t B, int64_t C, int64_t budget, uint32_t* lo, uint32_t* hi) {
   const double b = (double)budget, c = (double)C, two32 = 4294967296.0;
   const double slack = 5.0 * sqrt(b * (1.0 - b / c)) + 4.0;
