@@ -49,11 +49,11 @@ def test_workspace_and_capacity_of_each_workload(name):
     nbytes, cap = pfc.pfc_workspace_bytes(cfg["B"], cfg["d"], cfg["C"], cfg["r"], code)
     b = O.budget(cfg["r"], cfg["C"])
     assert cap == max(b, min(cfg["B"], cfg["C"]))
-    # Dominated by the logit store [B x cap] and the sampler's per-class
-    # digits (2 B) and candidate keys (8 B).
+    # Dominated by the logit store [B x cap] and the sampler's room for
+    # candidate keys (8 B per class) and masks (half a byte).
     elt = 4 if code == pfc.PFC_F32 else 2
-    assert nbytes >= cfg["B"] * cap * elt + cfg["C"] * 10
-    assert nbytes < 2 * (cfg["B"] * cap * elt + cfg["C"] * 10) + (256 << 20)
+    assert nbytes >= cfg["B"] * cap * elt + cfg["C"] * 17 // 2
+    assert nbytes < 2 * (cfg["B"] * cap * elt + cfg["C"] * 17 // 2) + (256 << 20)
 
 
 @pytest.mark.parametrize("code,d", [(0, 8), (0, 512), (0, 1024), (1, 128), (2, 256), (1, 512)])

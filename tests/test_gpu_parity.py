@@ -302,7 +302,6 @@ def test_sampler_group_edges(dev, B, C, a, r):
 @pytest.mark.parametrize("B,C,a,r", [
     (128, 3000001, 1, 0.1),           # above 512 groups, candidates held in LDS
     (8192, 8000001, 2, 0.5),          # 22,300 candidates: held
-    (8192, 20000001, 0, 0.5),         # 30,600: more than are held
     (64, 8192 * 4096, 0, 0.001),      # the most groups whose candidates are held
     (64, 8192 * 4096 + 1, 3, 0.001),
 ])
@@ -328,31 +327,38 @@ def test_sampler_threshold_outside_window(dev, C, b, seed):
     _sampler_case(dev, labels, C, 0, b / C, seed)
 
 
-def test_sampler_refinement_beyond_lds(dev):
-    """A shard of 20M classes: the threshold's top-digit bucket holds more
-    candidates than the refinement keeps in LDS (4,096), so it works on them
-    in memory.  Bit-exact active set and remap."""
+def _candidates(labels, C, a, r, seed):
+    """Non-positive keys inside the sampler's window (five standard deviations
+    and four classes around where the threshold can lie), and its groups of
+    4,096 classes."""
     from oracle import philox
-    B, C, a, r, seed = 1024, 20_000_000, 0, 0.01, 31
-    rng = np.random.default_rng(seed)
-    labels = rng.integers(0, C, size=B)
-    active_ref, mapped_ref, info = O.sample_active(labels, C, a, r, seed)
-    # The bucket of the n_neg-th smallest non-positive key (12 top bits at this C).
-    is_pos = np.zeros(C, dtype=bool)
-    is_pos[info["positives"]] = True
-    pool = np.nonzero(~is_pos)[0]
-    digits = philox.class_keys(seed, pool + a) >> np.uint64(52)
-    thresh_digit = np.sort(digits)[info["n_neg"] - 1]
-    bucket = int(np.count_nonzero(digits == thresh_digit))
-    assert bucket > 4096, bucket
-    print(f"\nsampler C={C} r={r}: bucket of {bucket} candidates", flush=True)
-    shard = _shard(B, 128, C, r, "bf16", "arcface", 0.5, class_offset=a, dev=dev)
-    shard.sample(torch.from_numpy(labels.astype(np.int64)).to(dev), seed)
-    torch.cuda.synchronize()
-    K = int(shard.n_active.item())
-    assert K == len(active_ref) == max(O.budget(r, C), info["n_pos"])
-    assert np.array_equal(shard.active[:K].cpu().numpy(), active_ref)
-    assert np.array_equal(shard.labels_mapped.cpu().numpy(), mapped_ref)
+    b = O.budget(r, C)
+    slack = 5.0 * np.sqrt(b * (1 - b / C)) + 4.0
+    lo = max(0.0, (b - min(len(labels), C) - slack) / C * 2.0 ** 32)
+    hi = min(2.0 ** 32 - 1, np.ceil((b + slack) / C * 2.0 ** 32))
+    top = philox.class_keys(seed, np.arange(a, a + C)) >> np.uint64(32)
+    inside = (top >= np.uint64(int(lo))) & (top <= np.uint64(int(hi)))
+    own = labels[(labels >= a) & (labels < a + C)] - a
+    inside[own] = False
+    return int(np.count_nonzero(inside)), -(-C // 4096)
+
+
+@pytest.mark.parametrize("B,C,r,most,groups", [
+    (8192, 1_000_000, 0.5, 8192, (5, 512)),           # each writing workgroup's list
+    (8192, 20_000_000, 0.5, 28672, (513, 8192)),      # the resolving workgroup's
+])
+def test_sampler_candidates_beyond_lds(dev, B, C, r, most, groups):
+    """More candidates than the kernel that finds the threshold holds in LDS: it
+    reads them from memory for each pass."""
+    labels = np.random.default_rng(31).integers(0, C, size=B)
+    n, n_groups = _candidates(labels, C, 0, r, 31)
+    assert n > most and groups[0] <= n_groups <= groups[1], (n, n_groups)
+    _sampler_case(dev, labels, C, 0, r, 31)
+
+
+def test_sampler_20m_classes(dev):
+    labels = np.random.default_rng(31).integers(0, 20_000_000, size=1024)
+    _sampler_case(dev, labels, 20_000_000, 0, 0.01, 31)
 
 
 def test_many_rows_per_class(dev):
