@@ -336,7 +336,7 @@ __device__ __forceinline__ Threshold kth_key(Each&& each, int64_t k, uint64_t fr
   const int t = threadIdx.x;
 #pragma unroll 1
   for (;;) {
-    const int width = 64 - __clzll((long long)(to - from));   // to > from
+    const int width = 64 - __clzll((long long)(to - from));
     const int shift = width > 11 ? width - 11 : 0;
     *reinterpret_cast<uint2*>(L.hist + 2 * t) = make_uint2(0u, 0u);
     if (t == 0) L.n_last = 0;
@@ -349,7 +349,9 @@ __device__ __forceinline__ Threshold kth_key(Each&& each, int64_t k, uint64_t fr
     from += (uint64_t)L.found[0] << shift;
     k -= L.found[1];
     const int64_t n = L.found[2];
-    to = from + ((1ull << shift) - 1ull);
+    // The bin's end, not past the range's: from there on it may not be a number.
+    const uint64_t span = (1ull << shift) - 1ull;
+    to = to - from < span ? to : from + span;
     if (shift == 0) return Threshold{from, k, k == n};
     if (n <= kLastKeys) {
       each([&](uint64_t key) {

@@ -327,6 +327,27 @@ def test_sampler_threshold_outside_window(dev, C, b, seed):
     _sampler_case(dev, labels, C, 0, b / C, seed)
 
 
+@pytest.mark.parametrize("B,C,b,seed", [
+    (5000, 13001, 13000, 1), (4000, 16385, 16384, 1), (2000, 61282, 61281, 2),
+    (8192, 2200003, 2200002, 0),
+])
+def test_sampler_threshold_in_the_last_bin(dev, B, C, b, seed):
+    """A budget that leaves one class out of a shard with many positives: the
+    window of candidates ends with the last key, and the threshold lies in a
+    bin of it that would end past 2^64."""
+    from oracle import philox
+    labels = np.random.default_rng(seed).integers(0, C + C // 4, size=B)
+    slack = 5.0 * np.sqrt(b * (1 - b / C)) + 4.0
+    lo = int(max(0.0, (b - min(B, C) - slack) / C * 2.0 ** 32)) << 32
+    shift = (2 ** 64 - 1 - lo).bit_length() - 11
+    keys = philox.class_keys(seed, np.arange(C))
+    keep = keys >= np.uint64(lo)
+    keep[labels[labels < C]] = False
+    threshold = int(np.sort(keys[keep])[b - C - 1])
+    assert lo + ((((threshold - lo) >> shift) + 1) << shift) > 2 ** 64
+    _sampler_case(dev, labels, C, 0, b / C, seed)
+
+
 def _candidates(labels, C, a, r, seed):
     """Non-positive keys inside the sampler's window (five standard deviations
     and four classes around where the threshold can lie), and its groups of
