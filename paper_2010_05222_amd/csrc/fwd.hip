@@ -770,8 +770,8 @@ __global__ void __launch_bounds__(64 * WPR * ROWS) k_lse16(
     for (int q = 0; q < Q; ++q) red[r][q0 + q] = acc[q];
   __syncthreads();
   if (lane == 0 && q0 == 0 && n < B) {
-    const float2 all = lse_merge2(lse_merge2(red[r][0], red[r][1]),
-                                  lse_merge2(red[r][2], red[r][3]));
+    const float2 all = lse_merge2(lse_merge2(red[r][1], red[r][0]),
+                                  lse_merge2(red[r][3], red[r][2]));
     const float lse = all.x == -INFINITY ? -INFINITY
                                          : (all.x + log2f(all.y)) * 0.6931471805599453f;
     row_lse[n] = lse;

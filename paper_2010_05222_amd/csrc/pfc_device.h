@@ -156,11 +156,13 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
-// Merge two (max, sum 2^(. - max)) pairs (base-2 log-sum-exp).
+// Merge two (max, sum 2^(. - max)) pairs (base-2 log-sum-exp).  Which product is
+// rounded before the sum is written out: left to the compiler, it differs from one
+// kernel to the next, and so does the last bit of a few rows' results.
 __device__ __forceinline__ float2 lse_merge2(float2 a, float2 b) {
   const float mx = fmaxf(a.x, b.x);
   if (mx == -INFINITY) return make_float2(-INFINITY, 0.0f);
-  return make_float2(mx, a.y * exp2f(a.x - mx) + b.y * exp2f(b.x - mx));
+  return make_float2(mx, fmaf(a.y, exp2f(a.x - mx), b.y * exp2f(b.x - mx)));
 }
 
 // Merge two (max, sum exp(. - max)) pairs.

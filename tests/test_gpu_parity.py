@@ -483,6 +483,32 @@ def test_forward_tiles_agree(dev, dtype, d, tau):
     assert torch.equal(out[0][lo:lo + 64], out[1])
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_row_merges_agree(dev, dtype):
+    """A row's log-sum-exp does not depend on the form of the row merge that its
+    batch takes: 4,096 rows at once (one wave per row), and by 1,024, 256 and
+    128 of them (four waves per row), give the same bits.  Scale 1, so that all
+    of a row's 430 tiles count in its sum."""
+    from _gpu_util import make_problem
+    B, d, C = 4096, 128, 55000
+    Xd, Wd, _, _, Ld = make_problem(B, d, C, dtype, 73, device=dev)
+    out = []
+    for rows in (4096, 1024, 256, 128):
+        print(f"\nrow merges: {dtype} batches of {rows}", flush=True)
+        shard = _shard(rows, d, C, 1.0, dtype, "arcface", 0.5, dev=dev)
+        shard.s = 1.0
+        lse = []
+        for k in range(0, B, rows):
+            shard.sample(Ld[k:k + rows].contiguous(), 0)
+            shard.forward(Xd[k:k + rows].contiguous(), Wd)
+            lse.append(shard.row_lse.clone())
+        out.append(torch.cat(lse))
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(out[0]).all())
+    for lse in out[1:]:
+        assert torch.equal(out[0], lse), int((out[0] != lse).sum())
+
+
 @pytest.mark.parametrize("dtype,d,tau", [("bf16", 512, None), ("f16", 128, 0.4), ("bf16", 256, 0.4)])
 @pytest.mark.parametrize("bad", [float("nan"), float("inf")])
 def test_non_finite_centre_reaches_every_row(dev, dtype, d, tau, bad):
