@@ -443,8 +443,9 @@ __global__ void __launch_bounds__(kFwdThreads, 2) k_fwd16(
     const int n = n0 + nl;
     if (half == 0) {
       fRed[wm][nl] = make_float2(mx, sm);
-      // reference of the row's 128-class group, the tile's
-      if (n < B) gmax[ct * ld_g + n] = mx == -INFINITY ? 0.0f : mx;
+      // reference of the row's 128-class group, the tile's (-inf: no live logit, and
+      // so scale 0 in the backward, whatever the row's lse)
+      if (n < B) gmax[ct * ld_g + n] = mx;
     }
   };
   // Rows 64 wave + 32 nb .. + 31 of the tile, which this wave alone wrote:
@@ -714,7 +715,7 @@ __global__ void __launch_bounds__(kFwdThreads, 2) k_fwd16n(
         sm += __builtin_amdgcn_exp2f(redt[half][r] - mref);
       sm += __shfl_xor(sm, 32, 64);
       if (half == 0 && n < B) {
-        gmax[ct * ld_g + n] = mref;
+        gmax[ct * ld_g + n] = mx[nb];
         stats[(int64_t)n * n_ctiles + ct] = make_float2(mx[nb], sm);
       }
     }

@@ -70,7 +70,7 @@ struct StepWs {
   int64_t n_ctiles;      // class tiles of the forward contraction
   float* tgt;            // [B] margined target logit
   float* tgtc;           // [B] unmargined target cosine
-  float* gmax;           // [n_groups x ld_g] reference m of each (group, row)
+  float* gmax;           // [n_groups x ld_g] reference m of each (group, row), -inf without a live logit
   float* gscale;         // [n_groups x ld_g] 2^(m - lse log2 e), so p = E * gscale (0 past B)
   int64_t ld_g;          // B rounded up to 128
   int64_t n_groups;      // ld_cos / 128

@@ -611,6 +611,27 @@ def test_conflict_filter_empty_denominator(dev, dtype):
     assert bool((shard.dX[empty] == 0).all())
 
 
+@pytest.mark.parametrize("dtype,B", [("bf16", 60), ("f16", 60), ("bf16", 600), ("f32", 60)])
+def test_only_the_target_is_live(dev, dtype, B):
+    """A filter that drops every negative and a margin that puts the target's
+    logit far below zero (CosFace m = 3: lse around -190): probability 1, no
+    gradient, and no NaN from the 128-class groups without a live logit."""
+    from _gpu_util import make_problem
+    d, C = 128, 9000
+    print(f"\nonly the target live: {dtype} B={B}", flush=True)
+    Xd, Wd, Md, _, Ld = make_problem(B, d, C, dtype, 74, random_m=False, device=dev)
+    shard = _shard(B, d, C, 1.0, dtype, "cosface", 3.0, dev=dev, tau=-2.0)
+    W0 = Wd.clone()
+    shard.step(Xd, Ld, Wd, Md, 74)
+    torch.cuda.synchronize()
+    # lse = f_y up to the rounding of a logarithm and an exponential near 2^8
+    # (2^-16 and less), which is also the most by which p can miss 1.
+    assert bool((shard.row_lse < -100).all())
+    assert float(shard.loss.abs()) <= 1e-4
+    assert float(shard.dX.abs().max()) <= 1e-3 and float(Md.abs().max()) <= 1e-2
+    assert bool(torch.isfinite(Wd).all()) and float((Wd.float() - W0.float()).abs().max()) <= 2e-3
+
+
 @pytest.mark.parametrize("d,dtype,margin,m,seed", [
     (512, "f16", "arcface", 0.5, 20),
     (256, "bf16", "cosface", 0.4, 22),
